@@ -24,6 +24,28 @@ using BatchShapesN16 = ShapeList<Shape<4, 256, 2, 16>, Shape<4, 256, 2, 8>, Shap
 using BatchDefaultN32 = ShapeList<DefaultShape<4>>;
 using BatchDefaultN16 = ShapeList<DefaultShape<4>>;
 
+// One canonical chunk c of the run described by A: groups wave, wave + W, ... of the chunk on each of
+// the workgroup's W waves, their sums in the accumulator slots, then the chunk's record.
+template <class S, class Eval>
+__device__ __forceinline__ void process_chunk(const Eval& ev, const AmpArgs& A, uint64_t c, uint64_t n_chunks, double* smem) {
+    constexpr int BS = S::BS;
+    const int tid = threadIdx.x;
+    const int nlev = A.s + 1;
+    double* acc = smem + kBoxMullerTable + size_t(3 * A.D + 2) * BS;
+    for (int i = tid; i < kChunkSlots * nlev * 3; i += BS) acc[i] = 0.0;
+    __syncthreads();
+    const uint64_t n_groups = (A.n_paths + 63) / 64;
+    for (int i = tid >> 6; i < kChunkGroups; i += BS / 64) {
+        const uint64_t g = c * kChunkGroups + uint64_t(i);
+        if (g >= n_groups) break;                         // wave-uniform: the rest of the chunk is empty
+        const GroupSink k{acc + (i % kChunkSlots) * nlev * 3, nullptr, 0};
+        process_group<S, Eval>(ev, A, g, k, smem, smem + kBoxMullerTable + tid);
+    }
+    __syncthreads();
+    write_chunk(acc, nlev, A.hier, A.partials, n_chunks, c, A.n_paths, tid);
+    __syncthreads();
+}
+
 // Persistent kernel over the (task, chunk) items of one class (level p, launch shape): each
 // workgroup takes `grab` consecutive items at a time from an atomic counter until the queue is
 // empty (every wave of every workgroup reaches the exit test with the same value). Items are
@@ -66,16 +88,15 @@ k_batch(const BatchTask* __restrict__ tasks, int n_tasks, uint64_t n_items, unsi
             A.key.stream = T[lo].stream;
             A.first_path = 0;
             A.n_paths = T[lo].n_paths;
-            A.n_chunks = T[lo].n_chunks;
+            A.work = PathWork{};
             A.s = T[lo].s;
             A.D = T[lo].s - S::U;
             A.hier = hier;
             A.partials = T[lo].partials;
             A.dump = nullptr;
-            A.queue = nullptr;
             Eval ev = ev0;
             ev.tab = T[lo].tab;
-            process_chunk<S, Eval>(ev, A, item - T[lo].item0, smem);
+            process_chunk<S, Eval>(ev, A, item - T[lo].item0, T[lo].n_chunks, smem);
         }
     }
 }

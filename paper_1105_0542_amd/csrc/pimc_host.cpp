@@ -296,7 +296,7 @@ int stage_problem(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t stream,
     // general-potential mode: derivative tables
     const size_t off_dpoly = (off_deg + P.deg.size() * 4 + 15) & ~size_t(15);
     const size_t off_dsech = off_dpoly + P.gen.dpoly.size() * 8;
-    // the chunk counter of the persistent kernel, on its own 256-byte line
+    // the two work counters of the persistent kernel, zero, on a 256-byte line of their own
     const size_t off_queue = (off_dsech + P.gen.dsech.size() * 8 + 255) & ~size_t(255);
     const size_t total = off_queue + 256;
     std::vector<unsigned char> host(total, 0);
@@ -329,7 +329,7 @@ int stage_problem(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t stream,
     A.tab64 = reinterpret_cast<const double*>(base + off_tab);
     A.tab32 = reinterpret_cast<const float*>(base + off_tab32);
     A.gdeg = reinterpret_cast<const int*>(base + off_deg);
-    A.queue = reinterpret_cast<unsigned long long*>(base + off_queue);
+    A.work.queue = reinterpret_cast<unsigned long long*>(base + off_queue);
     A.gK = int(P.deg.size());
     A.gstride = P.stride;
     A.a = P.a;
@@ -356,10 +356,9 @@ int stage_problem(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t stream,
     return PIMC_OK;
 }
 
-int launch_grid(pimc_ctx* c, const Problem& P, uint64_t n_chunks) {
-    const int resident = amplitude_resident_blocks(P.kind, P.p, P.U, amp_lds_bytes(P.D, P.s, 256), c->device);
-    const uint64_t g = std::min<uint64_t>(n_chunks, uint64_t(std::max(resident, 1)));
-    return int(std::max<uint64_t>(g, 1));
+// Resident workgroups of the problem's kernel.
+int resident_blocks(pimc_ctx* c, const Problem& P) {
+    return std::max(1, amplitude_resident_blocks(P.kind, P.p, P.U, amp_lds_bytes(P.D, P.s, kBlock), c->device));
 }
 
 int check_args(const pimc_potential* V, double m, double a, double b, double T, uint32_t N, int p,
@@ -406,6 +405,8 @@ int amplitude_core(pimc_ctx* c, const Problem& P, uint64_t n_samples, uint64_t s
     const uint64_t n_chunks = (n_samples + chunk_paths - 1) / chunk_paths;
     const int slots = hier ? nlev : 1;            // partial slot of level n: n, or 0 for level s alone
     const size_t partial_bytes = size_t(slots) * n_chunks * 4 * 8;
+    const int resident = resident_blocks(c, P);
+    PathWork pw;
     double* partials;
     double* red_dev;
     uint64_t* seg;
@@ -415,6 +416,10 @@ int amplitude_core(pimc_ctx* c, const Problem& P, uint64_t n_samples, uint64_t s
                             "%llu samples x %d levels need %zu bytes of chunk sums, the workspace holds %zu",
                             (unsigned long long)n_samples, slots, partial_bytes, work->partial_cap);
         partials = work->partials;
+        // the group sums take what the chunk records leave of the workspace
+        const size_t left = work->partial_cap - partial_bytes;
+        pw = split_paths(n_samples, P.s, slots, std::min(left, kFineBytes), uint64_t(resident) * (kBlock / 64));
+        pw.gsum = partials + partial_bytes / 8;
         red_dev = work->red;
         seg = work->seg;
     } else {
@@ -424,6 +429,10 @@ int amplitude_core(pimc_ctx* c, const Problem& P, uint64_t n_samples, uint64_t s
         if (st) return st;
         st = ensure(c, reinterpret_cast<void**>(&c->d_seg), &c->seg_bytes, size_t(slots) * 2 * 8);
         if (st) return st;
+        pw = split_paths(n_samples, P.s, slots, kFineBytes, uint64_t(resident) * (kBlock / 64));
+        st = ensure(c, reinterpret_cast<void**>(&c->d_gsum), &c->gsum_bytes, group_sum_bytes(pw, slots));
+        if (st) return st;
+        pw.gsum = c->d_gsum;
         partials = c->d_partials;
         red_dev = c->d_red;
         seg = c->d_seg;
@@ -431,6 +440,8 @@ int amplitude_core(pimc_ctx* c, const Problem& P, uint64_t n_samples, uint64_t s
     AmpArgs A;
     st = stage_problem(c, P, seed, stream, A, work);
     if (st) return st;
+    pw.queue = A.work.queue;
+    A.work = pw;
     c->h_seg.assign(size_t(slots) * 2, 0);
     for (int k = 0; k < slots; ++k) {
         c->h_seg[size_t(k)] = uint64_t(k) * n_chunks * 4;
@@ -439,15 +450,14 @@ int amplitude_core(pimc_ctx* c, const Problem& P, uint64_t n_samples, uint64_t s
     HIP_TRY(c, hipMemcpyAsync(seg, c->h_seg.data(), c->h_seg.size() * 8, hipMemcpyHostToDevice, c->stream));
     A.first_path = 0;
     A.n_paths = n_samples;
-    A.n_chunks = n_chunks;
     A.hier = hier ? 1 : 0;
     A.partials = partials;
     A.dump = nullptr;
-    const int grid = launch_grid(c, P, n_chunks);
-    HIP_TRY(c, launch_fill_u64(A.queue, 1, 0ull, c->stream));
+    const int grid = work_grid(A.work, kBlock / 64, resident);
     HIP_TRY(c, hipEventRecord(c->ev0, c->stream));
     HIP_TRY(c, launch_amplitude(A, P.kind, P.p, P.U, grid, c->stream));
     HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
+    HIP_TRY(c, launch_group_chunks(A.work, slots, n_samples, partials, c->stream));
     HIP_TRY(c, launch_seg_reduce(partials, seg, seg + slots, uint64_t(slots), red_dev, c->stream));
     double red[4 * (PIMC_MAX_S + 1)];
     HIP_TRY(c, hipMemcpyAsync(red, red_dev, size_t(slots) * 4 * 8, hipMemcpyDeviceToHost, c->stream));
@@ -483,15 +493,16 @@ int path_actions_core(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t str
     if (st) return st;
     st = ensure(c, reinterpret_cast<void**>(&c->d_dump), &c->dump_bytes, size_t(k_paths) * nlev * 8);
     if (st) return st;
-    const uint64_t chunk_paths = kChunkPaths;
     A.first_path = first_path;
     A.n_paths = k_paths;
-    A.n_chunks = (k_paths + chunk_paths - 1) / chunk_paths;
     A.hier = (flags & PIMC_HIERARCHY) ? 1 : 0;
     A.partials = nullptr;
     A.dump = c->d_dump;
-    const int grid = launch_grid(c, P, A.n_chunks);
-    HIP_TRY(c, launch_fill_u64(A.queue, 1, 0ull, c->stream));
+    const int resident = resident_blocks(c, P);
+    unsigned long long* const queue = A.work.queue;
+    A.work = split_paths(k_paths, P.s, 0, 0, uint64_t(resident) * (kBlock / 64));
+    A.work.queue = queue;
+    const int grid = work_grid(A.work, kBlock / 64, resident);
     HIP_TRY(c, launch_amplitude(A, P.kind, P.p, P.U, grid, c->stream));
     HIP_TRY(c, hipMemcpyAsync(S_out, c->d_dump, size_t(k_paths) * nlev * 8, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -595,6 +606,7 @@ int pimc_destroy(pimc_ctx* c) {
     (void)hipFree(c->d_red);
     (void)hipFree(c->d_seg);
     (void)hipFree(c->d_dump);
+    (void)hipFree(c->d_gsum);
     if (c->ev0) (void)hipEventDestroy(c->ev0);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);

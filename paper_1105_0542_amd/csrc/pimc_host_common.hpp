@@ -24,6 +24,7 @@ struct pimc_ctx {
     uint64_t* d_seg = nullptr;      size_t seg_bytes = 0;
     std::vector<uint64_t> h_seg;    // segment base/len of the last reduction (kept alive for the async copy)
     double* d_dump = nullptr;       size_t dump_bytes = 0;
+    double* d_gsum = nullptr;       size_t gsum_bytes = 0;     // group sums of the fine chunks (at most kFineBytes)
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     // last estimation
     const double* last_partials_ptr = nullptr;   // chunk partials of the last run (context buffer or workspace)

@@ -40,6 +40,50 @@ struct Shape {
 template <int U>
 using DefaultShape = Shape<U, 256, 2, 16>;
 
+// The paths of one launch (pimc_chunks.hpp): chunks 0 .. n_coarse-1 whole, the groups of the others
+// (fine groups) one by one.
+struct PathWork {
+    uint64_t n_groups;                 // ceil(n_paths / 64)
+    uint64_t n_chunks;                 // ceil(n_paths / kChunkPaths)
+    uint64_t n_coarse;
+    uint64_t n_static;                 // fine groups dealt to the waves in turn (none when n_coarse > 0)
+    double* gsum;                      // device [slot][fine group][3], or null (per-path actions only)
+    unsigned long long* queue;         // device: the coarse and the fine counter, 0 at launch
+    uint32_t grab;                     // fine groups per ticket
+    uint64_t fine() const { return n_groups > n_coarse * kChunkGroups ? n_groups - n_coarse * kChunkGroups : 0; }
+};
+
+// Group sums a run may keep: 24 bytes per group and level, 993 chunks (63,552 groups) with the eleven
+// levels of N = 1024, thirty times the waves of the GPU.
+constexpr size_t kFineBytes = size_t(16) << 20;
+
+// Split of a run of n_paths paths of N = 2^s slices over `slots` evaluated levels: as many chunks from
+// the end fine as fine_bytes of group sums hold (all of them when slots = 0: nothing is summed). The
+// last two rounds of the `waves` resident waves go by single ticket when a group is long (N >= 64),
+// everything is dealt when it is short; short groups behind a coarse phase go by 16.
+inline PathWork split_paths(uint64_t n_paths, int s, int slots, size_t fine_bytes, uint64_t waves) {
+    PathWork w{};
+    w.n_groups = (n_paths + 63) / 64;
+    w.n_chunks = (n_paths + kChunkPaths - 1) / kChunkPaths;
+    const uint64_t fit = slots ? fine_bytes / (size_t(slots) * kChunkGroups * 24) : w.n_chunks;
+    w.n_coarse = w.n_chunks > fit ? w.n_chunks - fit : 0;
+    const bool is_short = s < 6;
+    w.grab = is_short && w.n_coarse ? 16 : 1;
+    if (!w.n_coarse) {
+        const uint64_t rounds = w.n_groups / (waves ? waves : 1);
+        w.n_static = is_short || rounds < 1 ? w.n_groups : (rounds > 2 ? (rounds - 2) * waves : 0);
+    }
+    return w;
+}
+// Bytes of its group sums.
+inline size_t group_sum_bytes(const PathWork& w, int slots) { return size_t(slots) * size_t(w.fine()) * 24; }
+// Workgroups of `waves_per_wg` waves that this work can occupy, at most `resident`.
+inline int work_grid(const PathWork& w, int waves_per_wg, int resident) {
+    const uint64_t wgs = w.n_coarse + ((w.fine() + w.grab - 1) / w.grab + uint64_t(waves_per_wg) - 1) / uint64_t(waves_per_wg);
+    const uint64_t most = uint64_t(resident < 1 ? 1 : resident);
+    return int(wgs < 1 ? 1 : (wgs < most ? wgs : most));
+}
+
 // Arguments of one estimation launch (passed by value in the kernel argument segment, so every
 // field is wave-uniform and scalar-loaded).
 struct AmpArgs {
@@ -56,14 +100,12 @@ struct AmpArgs {
     RngKey key;
     uint64_t first_path;               // path index of local path 0
     uint64_t n_paths;                  // local paths 0..n_paths-1
-    uint64_t n_chunks;                 // ceil(n_paths / kChunkPaths)
+    PathWork work;                     // how the paths are shared out (not used by the batched kernel)
     int s;                             // N = 2^s
     int D;                             // s - U: levels walked with the explicit stack
     int hier;                          // evaluate every level (else level s only)
     double* partials;                  // device [level][chunk][4] or null
     double* dump;                      // device [path][s+1] or null
-    unsigned long long* queue;         // device chunk counter, 0 at launch (persistent kernel), or null
-                                       // for a grid-stride loop over the chunks
 };
 
 // Tanh64P: the Poeschl-Teller tables with the compile-time shape of level p (K = p groups of degree
@@ -123,6 +165,10 @@ PIMC_GEN_HI_DECLARE(18)
 // Raw standard normals of heap nodes 1..n_nodes for k_paths paths: out[path][node-1] (device).
 hipError_t launch_normals(const RngKey& key, uint64_t first_path, uint64_t k_paths, uint32_t n_nodes, double* out,
                           hipStream_t st);
+
+// Adds the group sums of a run's fine chunks into their chunk records, each chunk in the canonical
+// order (group g to slot g mod kChunkSlots in increasing g, then the slots in order).
+hipError_t launch_group_chunks(const PathWork& w, int slots, uint64_t n_paths, double* partials, hipStream_t st);
 
 // Canonical reduction: segment i = len[i] chunk sums of 4 doubles at partials + base[i], added in a
 // fixed order that depends only on len[i]; out[i][4] (all device).

@@ -48,6 +48,50 @@ hipError_t launch_normals(const RngKey& key, uint64_t first_path, uint64_t k_pat
 }
 
 // ---------------------------------------------------------------------------- chunk reduction
+// Group sums into chunk records (pimc_chunks.hpp). Four lanes per (slot, chunk): lane q adds groups
+// q, q + 4, ... of the chunk -- an accumulator slot -- and then the four slots are added in order.
+// Bound by latency: a chunk's 64 x 24 bytes are read with 16 loads in flight per lane.
+__global__ void __launch_bounds__(kBlock) k_group_chunks(const double* __restrict__ gsum, uint64_t first_chunk,
+                                                         uint64_t n_fine, uint64_t n_chunks, uint64_t n_paths,
+                                                         double* __restrict__ partials) {
+    const uint64_t i = uint64_t(blockIdx.x) * kBlock + threadIdx.x;
+    const int q = int(i & 3u);
+    const uint64_t fc = i >> 2;
+    const uint64_t slot = blockIdx.y;
+    const bool live = first_chunk + fc < n_chunks;
+    double s[3] = {0.0, 0.0, 0.0};
+    const double* p = gsum + (slot * n_fine + fc * kChunkGroups) * 3;
+#pragma unroll
+    for (int k = 0; k < kChunkGroups / kChunkSlots; ++k) {
+        const int g = k * kChunkSlots + q;
+        if (live && fc * kChunkGroups + uint64_t(g) < n_fine) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) s[j] += p[g * 3 + j];
+        }
+    }
+    double t[3];
+    const int lane0 = int(threadIdx.x & 63u) & ~3;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        t[j] = 0.0;
+#pragma unroll
+        for (int k = 0; k < kChunkSlots; ++k) t[j] += __shfl(s[j], lane0 + k, 64);
+    }
+    if (!live) return;
+    const uint64_t rem = n_paths - (first_chunk + fc) * kChunkPaths;
+    const double cnt = double(rem < kChunkPaths ? rem : kChunkPaths);
+    partials[(slot * n_chunks + first_chunk + fc) * 4 + q] = q == 0 ? cnt : (q == 1 ? t[0] : (q == 2 ? t[1] : t[2]));
+}
+
+hipError_t launch_group_chunks(const PathWork& w, int slots, uint64_t n_paths, double* partials, hipStream_t st) {
+    if (w.n_coarse >= w.n_chunks || slots < 1) return hipSuccess;
+    const uint64_t blocks = ((w.n_chunks - w.n_coarse) * 4 + kBlock - 1) / kBlock;
+    if (blocks > 0x7fffffffull) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_group_chunks, dim3(uint32_t(blocks), uint32_t(slots)), dim3(kBlock), 0, st, w.gsum, w.n_coarse,
+                       w.fine(), w.n_chunks, n_paths, partials);
+    return hipGetLastError();
+}
+
 // Canonical reduction: segment i (one level of one run) is the sequence of chunk sums
 // partials[base[i] + c*4 .. +3], c = 0..len[i]-1. One workgroup of kBlock threads per segment:
 // thread t adds chunks t, t + kBlock, ... in order, then a fixed halving tree over the threads.

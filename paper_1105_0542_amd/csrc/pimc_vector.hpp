@@ -94,7 +94,7 @@ struct VecArgs {
     RngKey key;
     uint64_t first_path;
     uint64_t n_paths;
-    uint64_t n_chunks;                 // ceil(n_paths / kChunkPaths)
+    PathWork work;                     // how the paths are shared out
     int s;                             // N = 2^s
     int D;                             // s - U: levels walked with the explicit stack
     int hier;                          // every level (else level s only)

@@ -355,7 +355,9 @@ int stage_vector(pimc_ctx* c, const VecProblem& P, uint64_t seed, uint32_t strea
     const size_t off_shift = nlev * 8;
     const size_t off_tab = 2 * nlev * 8;
     const size_t off_shape = off_tab + n_tab * 8;
-    const size_t total = off_shape + P.shape.size() * 4 + 16;
+    // the two work counters of the persistent kernel, zero, on a 256-byte line of their own
+    const size_t off_queue = (off_shape + P.shape.size() * 4 + 255) & ~size_t(255);
+    const size_t total = off_queue + 256;
     std::vector<unsigned char> host(total, 0);
     std::memcpy(host.data(), P.sig.data(), nlev * 8);
     std::memcpy(host.data() + off_shift, P.shift.data(), nlev * 8);
@@ -371,6 +373,7 @@ int stage_vector(pimc_ctx* c, const VecProblem& P, uint64_t seed, uint32_t strea
     A.shift = reinterpret_cast<const double*>(base + off_shift);
     A.tab = reinterpret_cast<const double*>(base + off_tab);
     A.shape = reinterpret_cast<const int*>(base + off_shape);
+    A.work.queue = reinterpret_cast<unsigned long long*>(base + off_queue);
     A.stride = P.stride;
     for (int k = 0; k < kVecMaxDim; ++k) {
         A.a[k] = k < P.dim ? P.a[k] : 0.0;
@@ -395,12 +398,11 @@ int check_lds(pimc_ctx* c, const VecProblem& P) {
     return PIMC_OK;
 }
 
-int vector_grid(pimc_ctx* c, const VecProblem& P, uint64_t n_chunks) {
+// Resident workgroups of the problem's kernel.
+int vector_resident(pimc_ctx* c, const VecProblem& P) {
     const size_t lds = vec_lds_bytes(P.dim, P.D, P.s);
-    const int resident = P.poly ? vector_poly_resident(P.dim, P.U, lds, c->device)
-                                : vector_resident_blocks(P.dim, P.p, P.U, P.specialized, lds, c->device);
-    const uint64_t g = std::min<uint64_t>(n_chunks, uint64_t(std::max(resident, 1)));
-    return int(std::max<uint64_t>(g, 1));
+    return std::max(1, P.poly ? vector_poly_resident(P.dim, P.U, lds, c->device)
+                              : vector_resident_blocks(P.dim, P.p, P.U, P.specialized, lds, c->device));
 }
 
 int vector_amplitude_core(pimc_ctx* c, const VecProblem& P, uint64_t n_samples, uint64_t seed, uint32_t stream,
@@ -425,6 +427,13 @@ int vector_amplitude_core(pimc_ctx* c, const VecProblem& P, uint64_t n_samples, 
     const int slots = hier ? nlev : 1;
     st = ensure(c, reinterpret_cast<void**>(&c->d_partials), &c->partial_bytes, size_t(slots) * n_chunks * 4 * 8);
     if (st) return st;
+    const int resident = vector_resident(c, P);
+    unsigned long long* const queue = A.work.queue;
+    A.work = split_paths(n_samples, P.s, slots, kFineBytes, uint64_t(resident) * (kVecBlock / 64));
+    A.work.queue = queue;
+    st = ensure(c, reinterpret_cast<void**>(&c->d_gsum), &c->gsum_bytes, group_sum_bytes(A.work, slots));
+    if (st) return st;
+    A.work.gsum = c->d_gsum;
     st = ensure(c, reinterpret_cast<void**>(&c->d_red), &c->red_bytes, size_t(slots) * 4 * 8);
     if (st) return st;
     st = ensure(c, reinterpret_cast<void**>(&c->d_seg), &c->seg_bytes, size_t(slots) * 2 * 8);
@@ -437,15 +446,15 @@ int vector_amplitude_core(pimc_ctx* c, const VecProblem& P, uint64_t n_samples, 
     HIP_TRY(c, hipMemcpyAsync(c->d_seg, c->h_seg.data(), c->h_seg.size() * 8, hipMemcpyHostToDevice, c->stream));
     A.first_path = 0;
     A.n_paths = n_samples;
-    A.n_chunks = n_chunks;
     A.hier = hier ? 1 : 0;
     A.partials = c->d_partials;
     A.dump = nullptr;
-    const int grid = vector_grid(c, P, n_chunks);
+    const int grid = work_grid(A.work, kVecBlock / 64, resident);
     HIP_TRY(c, hipEventRecord(c->ev0, c->stream));
     HIP_TRY(c, P.poly ? launch_vector_poly(A, P.dim, P.U, grid, c->stream)
                       : launch_vector(A, P.dim, P.p, P.U, P.specialized, grid, c->stream));
     HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
+    HIP_TRY(c, launch_group_chunks(A.work, slots, n_samples, c->d_partials, c->stream));
     HIP_TRY(c, launch_seg_reduce(c->d_partials, c->d_seg, c->d_seg + slots, uint64_t(slots), c->d_red, c->stream));
     std::vector<double> red(size_t(slots) * 4);
     HIP_TRY(c, hipMemcpyAsync(red.data(), c->d_red, red.size() * 8, hipMemcpyDeviceToHost, c->stream));
@@ -480,14 +489,16 @@ int vector_path_actions_core(pimc_ctx* c, const VecProblem& P, uint64_t seed, ui
     if (st) return st;
     st = ensure(c, reinterpret_cast<void**>(&c->d_dump), &c->dump_bytes, size_t(k_paths) * nlev * 8);
     if (st) return st;
-    const uint64_t chunk_paths = kChunkPaths;
     A.first_path = first_path;
     A.n_paths = k_paths;
-    A.n_chunks = (k_paths + chunk_paths - 1) / chunk_paths;
     A.hier = (flags & PIMC_HIERARCHY) ? 1 : 0;
     A.partials = nullptr;
     A.dump = c->d_dump;
-    const int grid = vector_grid(c, P, A.n_chunks);
+    const int resident = vector_resident(c, P);
+    unsigned long long* const queue = A.work.queue;
+    A.work = split_paths(k_paths, P.s, 0, 0, uint64_t(resident) * (kVecBlock / 64));
+    A.work.queue = queue;
+    const int grid = work_grid(A.work, kVecBlock / 64, resident);
     HIP_TRY(c, P.poly ? launch_vector_poly(A, P.dim, P.U, grid, c->stream)
                       : launch_vector(A, P.dim, P.p, P.U, P.specialized, grid, c->stream));
     HIP_TRY(c, hipMemcpyAsync(S_out, c->d_dump, size_t(k_paths) * nlev * 8, hipMemcpyDeviceToHost, c->stream));

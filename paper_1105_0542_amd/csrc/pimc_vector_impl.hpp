@@ -14,6 +14,7 @@
 // by k_seg_reduce: the result does not depend on the grid.
 #pragma once
 
+#include "pimc_chunks.hpp"
 #include "pimc_vector.hpp"
 
 namespace pimc {
@@ -461,94 +462,47 @@ __device__ __forceinline__ void walk_path(const Eval& ev, const VecArgs& A, cons
 }
 
 // ---------------------------------------------------------------------------- estimation kernel
-__device__ __forceinline__ void reduce_level(const VecArgs& A, double* a, int lane, int n, double S, bool valid) {
-    const double d = valid ? expm1(-(S - as_const(A.shift)[n])) : 0.0;
-    const bool bad = valid && !isfinite(d);
-    const double sd = wave_sum(d);
-    const double sd2 = wave_sum(d * d);
-    const unsigned long long badmask = __ballot(bad);
-    if (lane == 0) {
-        a[0] += sd;
-        a[1] += sd2;
-        a[2] += double(__popcll(badmask));
-    }
-}
-
-// One canonical chunk c: paths c*kChunkPaths + 64 g + lane, groups g = wave, wave + 4, ... (the
-// order of the one-dimensional kernels); writes the chunk's four sums per evaluated level to
-// A.partials[(slot * n_chunks + c) * 4] and/or the per-path level actions to A.dump. smem: the
-// Box-Muller table, the per-lane stack, the accumulator slots.
+// One group: paths 64 g + lane (the group of the one-dimensional kernels); level sums to the sink k,
+// per-path level actions to A.dump. bm: the Box-Muller table, top: this lane's stack (both LDS).
 template <int DIM, int U, class Eval>
-__device__ __forceinline__ void process_chunk(const Eval& ev, const VecArgs& A, uint64_t c, double* smem) {
-    constexpr int WAVES = kVecBlock / 64;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
+__device__ __forceinline__ void process_group(const Eval& ev, const VecArgs& A, uint64_t g, const GroupSink& k,
+                                              const double* bm, double* top) {
+    const int lane = threadIdx.x & 63;
     const int D = A.D;
-    const int nlev = A.s + 1;
-    const double* bm = smem;
-    double* top = smem + kBoxMullerTable + tid;
-    double* acc = smem + kBoxMullerTable + size_t(vec_top_slots(DIM, D)) * kVecBlock;
-    const uint64_t first = c * kChunkPaths;
-    if (A.partials) {
-        for (int i = tid; i < kChunkSlots * nlev * 3; i += kVecBlock) acc[i] = 0.0;
-        __syncthreads();
-    }
-    for (int g = wave; g < kChunkGroups; g += WAVES) {
-        const uint64_t group0 = first + uint64_t(g) * 64;
-        if (group0 >= A.n_paths) break;                   // wave-uniform: the rest of the chunk is empty
-        const uint64_t local = group0 + uint64_t(lane);
-        const bool valid = local < A.n_paths;
-        double Ssub[U + 1];
-        const VecSource<DIM> src{A.key, path_rng(A.key, A.first_path + local), bm};
-        walk_path<DIM, U, Eval>(ev, A, src, top, Ssub);
-        if (A.dump && valid) {
-            double* o = A.dump + local * uint64_t(nlev);
-            for (int n = 0; n < D; ++n) o[n] = A.hier ? top[n * kVecBlock] : 0.0;
+    const uint64_t local = g * 64 + uint64_t(lane);
+    const bool valid = local < A.n_paths;
+    double Ssub[U + 1];
+    const VecSource<DIM> src{A.key, path_rng(A.key, A.first_path + local), bm};
+    walk_path<DIM, U, Eval>(ev, A, src, top, Ssub);
+    if (A.dump && valid) {
+        double* o = A.dump + local * uint64_t(A.s + 1);
+        for (int n = 0; n < D; ++n) o[n] = A.hier ? top[n * kVecBlock] : 0.0;
 #pragma unroll
-            for (int j = 0; j <= U; ++j) o[D + j] = (A.hier || j == U) ? Ssub[j] : 0.0;
-        }
-        if (A.partials) {
-            double* a = acc + (g % kChunkSlots) * nlev * 3;
-            if (A.hier) {
-                for (int n = 0; n < D; ++n) reduce_level(A, a + n * 3, lane, n, top[n * kVecBlock], valid);
-#pragma unroll
-                for (int j = 0; j < U; ++j) reduce_level(A, a + (D + j) * 3, lane, D + j, Ssub[j], valid);
-            }
-            reduce_level(A, a + (D + U) * 3, lane, D + U, Ssub[U], valid);
-        }
+        for (int j = 0; j <= U; ++j) o[D + j] = (A.hier || j == U) ? Ssub[j] : 0.0;
     }
     if (A.partials) {
-        __syncthreads();
-        const int slots = A.hier ? nlev : 1;
-        if (tid < slots) {
-            const int lev = A.hier ? tid : nlev - 1;
-            const uint64_t rem = A.n_paths - first;
-            const double cnt = double(rem < kChunkPaths ? rem : kChunkPaths);
-            double s1 = 0.0, s2 = 0.0, nb = 0.0;
-            for (int q = 0; q < kChunkSlots; ++q) {
-                const double* a = acc + (q * nlev + lev) * 3;
-                s1 += a[0];
-                s2 += a[1];
-                nb += a[2];
-            }
-            double* o = A.partials + (uint64_t(tid) * A.n_chunks + c) * 4;
-            o[0] = cnt;
-            o[1] = s1;
-            o[2] = s2;
-            o[3] = nb;
+        const const_ptr<double> shift = as_const(A.shift);
+        if (A.hier) {
+            for (int n = 0; n < D; ++n) reduce_level(k, lane, n, top[n * kVecBlock], shift[n], valid);
+#pragma unroll
+            for (int j = 0; j < U; ++j) reduce_level(k, lane, D + j, Ssub[j], shift[D + j], valid);
         }
-        __syncthreads();
+        reduce_level(k, lane, A.hier ? D + U : 0, Ssub[U], shift[D + U], valid);
     }
 }
 
+// LDS of a workgroup: the Box-Muller table, the per-lane stacks, the accumulator slots.
 template <int DIM, int U, class Eval>
 __global__ void __launch_bounds__(kVecBlock) __attribute__((amdgpu_waves_per_eu(2)))
 k_amplitude_vec(VecArgs A, Eval ev) {
     extern __shared__ double smem[];
     load_bm_table(smem, kVecBlock);
     __syncthreads();
-    for (uint64_t c = blockIdx.x; c < A.n_chunks; c += gridDim.x) process_chunk<DIM, U, Eval>(ev, A, c, smem);
+    double* top = smem + kBoxMullerTable + threadIdx.x;
+    double* acc = smem + kBoxMullerTable + size_t(vec_top_slots(DIM, A.D)) * kVecBlock;
+    run_groups<kVecBlock>(A.work, A.s + 1, A.hier, A.n_paths, A.partials, acc, [&](uint64_t g, const GroupSink& k) __attribute__((always_inline)) {
+        process_group<DIM, U, Eval>(ev, A, g, k, smem, top);
+    });
 }
 
 // ---------------------------------------------------------------------------- dispatch
