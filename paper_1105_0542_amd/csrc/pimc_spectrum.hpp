@@ -22,15 +22,27 @@ struct SpecTable {
 // y = sm x, i, j < n (device M, ld >= n).
 hipError_t launch_evolution_matrix(const SpecTable& tb, double L, double D, double sm, double t, double pref,
                                    uint32_t n, double* M, uint64_t ld, hipStream_t st);
-// Packed symmetric storage: tiles (I, J), I <= J, of kTile x kTile doubles, row-major within a tile,
-// tile t at M + t * kTile^2 with map[t] = I << 16 | J in the order t = I*nb - I(I-1)/2 + (J - I),
-// nb = ceil(n / kTile); elements beyond n are zero.
+// Packed symmetric band: tiles (I, J), I <= J <= I + bw, of kTile x kTile doubles, row-major within a
+// tile, tile t at M + t * kTile^2 with map[t] = I << 16 | J, in the order of I, then J (row I starts at
+// tile first(I)); nb = ceil(n / kTile) row blocks, elements beyond n are zero. bw < nb leaves out tiles
+// whose elements are all exactly zero (the cut of k_evolution_matrix); bw = nb - 1 is the upper triangle.
 constexpr int kTile = 64;
+struct TileBand {
+    uint32_t nb, bw;
+    __host__ __device__ uint64_t first(uint32_t I) const {
+        const uint64_t e = I > nb - bw ? I - (nb - bw) : 0;        // row r has bw + 1 tiles, less from r = nb - bw on
+        return uint64_t(I) * (bw + 1) - e * (e + 1) / 2;
+    }
+    uint64_t tiles() const { return first(nb); }
+};
+// The band that holds every element with |y_j - y_i| of step `dy` per index and exponent
+// (y_j - y_i)^2 / (2t) within the cut, with a margin beyond the rounding of the kernel's test.
+TileBand tile_band(uint32_t n, double dy, double t);
 hipError_t launch_evolution_tiles(const SpecTable& tb, double L, double D, double sm, double t, double pref,
                                   uint32_t n, const uint32_t* map, uint32_t ntiles, double* M, hipStream_t st);
-// y = M x from the packed tiles: partial products per tile (prow, pcol: ntiles * kTile doubles each)
+// y = M x from the packed tiles: partial products per tile (prow, pcol: tiles * kTile doubles each)
 // then a fixed-order reduction per row block; x is read for indices < n only.
-hipError_t launch_symv_tiles(const double* M, const uint32_t* map, uint32_t ntiles, uint32_t nb, uint32_t n,
+hipError_t launch_symv_tiles(const double* M, const uint32_t* map, const TileBand& band, uint32_t n,
                              const double* x, double* prow, double* pcol, double* y, hipStream_t st);
 // y = M x (ld even; M and x 16-byte aligned).
 hipError_t launch_gemv(const double* M, uint64_t ld, uint32_t n, const double* x, double* y, hipStream_t st);

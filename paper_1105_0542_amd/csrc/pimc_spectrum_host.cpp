@@ -247,12 +247,12 @@ int pimc_spectrum(pimc_ctx* c, const pimc_potential* V, double m, double t, int 
     if (!(tol > 0.0 && tol < 1.0)) return ctx_fail(c, PIMC_EINVAL, "tol outside (0, 1)");
     HIP_TRY(c, hipSetDevice(c->device));
     const uint64_t ld = (uint64_t(n) + 63) / 64 * 64;
-    // the matrix as packed upper tiles (it is exactly symmetric): half the bytes per product
-    const uint32_t nb = (n + kTile - 1) / kTile;
-    const uint32_t ntiles = nb * (nb + 1) / 2;
+    // the matrix as the packed upper tiles (it is exactly symmetric) that are not zero throughout
+    const TileBand band = tile_band(n, std::sqrt(m) * 2.0 * L / double(n), t);
+    const uint32_t ntiles = uint32_t(band.tiles());
     std::vector<uint32_t> map(ntiles);
-    for (uint32_t I = 0, q = 0; I < nb; ++I)
-        for (uint32_t J = I; J < nb; ++J) map[q++] = (I << 16) | J;
+    for (uint32_t I = 0, q = 0; I < band.nb; ++I)
+        for (uint32_t J = I; J < band.nb && J <= I + band.bw; ++J) map[q++] = (I << 16) | J;
     DevBuf Mb, Qb, wb, ab, bb, hb, tab, mapb, prb, pcb;
     if ((st = dev_alloc(c, Mb, size_t(ntiles) * kTile * kTile * 8))) return st;
     if ((st = dev_alloc(c, mapb, size_t(ntiles) * 4))) return st;
@@ -298,7 +298,7 @@ int pimc_spectrum(pimc_ctx* c, const pimc_potential* V, double m, double t, int 
     const uint32_t check_every = 16;
     for (uint32_t j = 0; j < max_iter; ++j) {
         double* qj = Q + uint64_t(j) * ld;
-        HIP_TRY(c, launch_symv_tiles(M, dmap, ntiles, nb, n, qj, prow, pcol, w, c->stream));
+        HIP_TRY(c, launch_symv_tiles(M, dmap, band, n, qj, prow, pcol, w, c->stream));
         // w = (1 - Q Q^T) M q_j by classical Gram-Schmidt, twice: in exact arithmetic the first pass
         // removes alpha_j q_j + beta_{j-1} q_{j-1} (the three-term recurrence) and nothing else, so
         // alpha_j = <q_j, M q_j> is its coefficient of q_j, and beta_j = |w| afterwards

@@ -1,0 +1,35 @@
+"""The eigenvalue iteration keeps only the tiles of the matrix that the cut does not zero: its energies
+against a dense eigensolver on the full matrix of pimc_evolution_matrix, at sizes around the tile and
+band edges.
+
+Tolerance: every Ritz pair ends with |M y - theta y| <= 1e-10 theta_0, so |theta - lambda| <= 1e-10
+lambda_0; the dense solver adds n eps lambda_0; E = -ln(lambda)/t has dE = dlambda / (lambda t)."""
+import math
+
+import numpy as np
+import pytest
+
+import paper_1105_0542_amd as P
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [63, 65, 129, 500, 640, 1025])
+@pytest.mark.parametrize("m,t,L", [(1.0, 0.02, 8.0),      # band of 1.26 of 16
+                                   (2.0, 0.02, 6.0),      # mass in the step
+                                   (1.0, 0.0005, 2.0),    # a band within one tile of the diagonal
+                                   (1.0, 0.5, 3.0)])      # no zeros: the whole triangle
+def test_energies_from_the_band_match_the_dense_matrix(n, m, t, L):
+    import torch
+    k = 4
+    coefs = [0.0, 0.2, 0.5, 0.0, 0.4]
+    with P.Context() as ctx:
+        M = torch.zeros(n, n, dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        ctx.evolution_matrix(coefs, m, t, 6, L, n, M.data_ptr(), n)
+        lam = np.linalg.eigvalsh(M.cpu().numpy())[::-1]
+        E, _, info, _ = ctx.spectrum(coefs, m, t, 6, L, n, k, max_iter=n)
+    assert info.converged == 1
+    ref = -np.log(lam[:k]) / t
+    tol = (1e-10 + n * 2.0 ** -52) * lam[0] / (lam[:k] * t)
+    assert np.all(np.abs(E - ref) <= tol), (E - ref, tol)
