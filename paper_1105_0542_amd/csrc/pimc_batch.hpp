@@ -24,51 +24,49 @@ using BatchShapesN16 = ShapeList<Shape<4, 256, 2, 16>, Shape<4, 256, 2, 8>, Shap
 using BatchDefaultN32 = ShapeList<DefaultShape<4>>;
 using BatchDefaultN16 = ShapeList<DefaultShape<4>>;
 
-// One canonical chunk c of the run described by A: groups wave, wave + W, ... of the chunk on each of
-// the workgroup's W waves, their sums in the accumulator slots, then the chunk's record.
-template <class S, class Eval>
-__device__ __forceinline__ void process_chunk(const Eval& ev, const AmpArgs& A, uint64_t c, uint64_t n_chunks, double* smem) {
-    constexpr int BS = S::BS;
-    const int tid = threadIdx.x;
-    const int nlev = A.s + 1;
-    double* acc = smem + kBoxMullerTable + size_t(3 * A.D + 2) * BS;
-    for (int i = tid; i < kChunkSlots * nlev * 3; i += BS) acc[i] = 0.0;
-    __syncthreads();
-    const uint64_t n_groups = (A.n_paths + 63) / 64;
-    for (int i = tid >> 6; i < kChunkGroups; i += BS / 64) {
-        const uint64_t g = c * kChunkGroups + uint64_t(i);
-        if (g >= n_groups) break;                         // wave-uniform: the rest of the chunk is empty
-        const GroupSink k{acc + (i % kChunkSlots) * nlev * 3, nullptr, 0};
-        process_group<S, Eval>(ev, A, g, k, smem, smem + kBoxMullerTable + tid);
-    }
-    __syncthreads();
-    write_chunk(acc, nlev, A.hier, A.partials, n_chunks, c, A.n_paths, tid);
-    __syncthreads();
-}
-
-// Persistent kernel over the (task, chunk) items of one class (level p, launch shape): each
-// workgroup takes `grab` consecutive items at a time from an atomic counter until the queue is
-// empty (every wave of every workgroup reaches the exit test with the same value). Items are
-// numbered task by task (task t owns items item0[t] .. item0[t] + n_chunks[t] - 1), so an item maps
-// to its task by binary search over the wave-uniform task records; the chunk itself is processed
-// by the same code as a single-task launch, so results do not depend on which workgroup took which
-// item, nor on the shape.
+// Persistent kernel over the items of one class (level p, launch shape), numbered task by task (task t
+// owns items item0[t] .. item0[t+1] - 1), so an item maps to its task by binary search over the
+// wave-uniform task records. An item is
+//   * by group (small batches): `block` consecutive groups, taken by one wave, whose sums are stored and
+//     added into the chunk records afterwards (pimc_chunks.hpp: the same sums as any other split). A
+//     task of 20,000 paths has 5 chunks, a class of 85 such tasks 425 of them for 512 resident
+//     workgroups, those with N = 512 16 times as long as those with N = 32;
+//   * a whole chunk (large batches, whose group sums would not fit), taken by a workgroup.
+// Items are taken `grab` at a time from an atomic counter until it passes n_items; every wave (by
+// group) or workgroup (by chunk) reaches the exit test with one value.
 template <class S, class Eval>
 __global__ void __launch_bounds__(S::BS) __attribute__((amdgpu_waves_per_eu(S::WPE)))
 k_batch(const BatchTask* __restrict__ tasks, int n_tasks, uint64_t n_items, unsigned long long* queue,
-        uint32_t grab, RngKey key, int hier, Eval ev0) {
+        uint32_t grab, int by_group, RngKey key, int hier, Eval ev0) {
     extern __shared__ double smem[];
     __shared__ unsigned long long s_item;
+    constexpr int WAVES = S::BS / 64;
     const const_ptr<BatchTask> T = as_const(tasks);
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     load_bm_table(smem, S::BS);
+    __syncthreads();
+    auto take = [&]() -> unsigned long long {
+        unsigned long long t = 0;
+        if ((tid & 63) == 0) t = atomicAdd(queue, (unsigned long long)grab);
+        return t;
+    };
+    unsigned long long ticket = by_group ? take() : 0ull;
     while (true) {
-        __syncthreads();
-        if (threadIdx.x == 0) s_item = atomicAdd(queue, (unsigned long long)grab);
-        __syncthreads();
-        const uint64_t first = uniform_u64(s_item);
-        if (first >= n_items) break;
-        const uint64_t last = first + grab < n_items ? first + grab : n_items;
-        for (uint64_t item = first; item < last; ++item) {
+        uint64_t first;
+        if (by_group) {
+            first = uniform_u64(ticket);
+            if (first >= n_items) break;
+            ticket = take();
+        } else {
+            __syncthreads();
+            if (tid == 0) s_item = atomicAdd(queue, (unsigned long long)grab);
+            __syncthreads();
+            first = uniform_u64(s_item);
+            if (first >= n_items) break;
+        }
+        const uint64_t end = first + grab < n_items ? first + grab : n_items;
+        for (uint64_t item = first; item < end; ++item) {
             int lo = 0, hi = n_tasks - 1;                  // last task with item0 <= item
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
@@ -96,7 +94,33 @@ k_batch(const BatchTask* __restrict__ tasks, int n_tasks, uint64_t n_items, unsi
             A.dump = nullptr;
             Eval ev = ev0;
             ev.tab = T[lo].tab;
-            process_chunk<S, Eval>(ev, A, item - T[lo].item0, T[lo].n_chunks, smem);
+            const int nlev = A.s + 1;
+            const uint64_t n_groups = (A.n_paths + 63) / 64;
+            double* acc = smem + kBoxMullerTable + size_t(3 * A.D + 2) * S::BS;
+            uint64_t g = item - T[lo].item0, last, step = 1;
+            if (by_group) {
+                g *= T[lo].block;
+                last = g + T[lo].block;
+            } else {
+                for (int i = tid; i < kChunkSlots * nlev * 3; i += S::BS) acc[i] = 0.0;
+                __syncthreads();
+                g = g * kChunkGroups + uint64_t(wave);
+                last = g - uint64_t(wave) + kChunkGroups;
+                step = WAVES;
+            }
+            if (last > n_groups) last = n_groups;
+            for (; g < last; g += step) {
+                GroupSink k;
+                k.acc = by_group ? nullptr : acc + int(g % kChunkSlots) * nlev * 3;
+                k.out = T[lo].gsum + g * 3;
+                k.stride = n_groups * 3;
+                process_group<S, Eval>(ev, A, g, k, smem, smem + kBoxMullerTable + tid);
+            }
+            if (!by_group) {
+                __syncthreads();
+                write_chunk(acc, nlev, hier, A.partials, T[lo].n_chunks, item - T[lo].item0, A.n_paths, tid);
+                __syncthreads();
+            }
         }
     }
 }
@@ -107,7 +131,7 @@ struct BatchLauncher;
 
 template <int P>
 struct BatchLauncher<P, ShapeList<>> {
-    static hipError_t launch(int, const BatchTask*, int, uint64_t, unsigned long long*, uint32_t, const RngKey&, int, int,
+    static hipError_t launch(int, const BatchTask*, int, uint64_t, unsigned long long*, uint32_t, int, const RngKey&, int, int,
                              size_t, hipStream_t) {
         return hipErrorInvalidValue;
     }
@@ -119,11 +143,11 @@ template <int P, class S0, class... Ss>
 struct BatchLauncher<P, ShapeList<S0, Ss...>> {
     using Rest = BatchLauncher<P, ShapeList<Ss...>>;
     static hipError_t launch(int idx, const BatchTask* tasks, int n_tasks, uint64_t n_items, unsigned long long* queue,
-                             uint32_t grab, const RngKey& key, int hier, int grid, size_t lds, hipStream_t st) {
-        if (idx != 0) return Rest::launch(idx - 1, tasks, n_tasks, n_items, queue, grab, key, hier, grid, lds, st);
+                             uint32_t grab, int by_group, const RngKey& key, int hier, int grid, size_t lds, hipStream_t st) {
+        if (idx != 0) return Rest::launch(idx - 1, tasks, n_tasks, n_items, queue, grab, by_group, key, hier, grid, lds, st);
         QuarticEval64<P> ev{nullptr};
         hipLaunchKernelGGL((k_batch<S0, QuarticEval64<P>>), dim3(grid), dim3(S0::BS), lds, st, tasks, n_tasks, n_items,
-                           queue, grab, key, hier, ev);
+                           queue, grab, by_group, key, hier, ev);
         return hipGetLastError();
     }
     static int resident(int idx, size_t lds, int device) {
@@ -146,17 +170,17 @@ struct BatchLauncher<P, ShapeList<S0, Ss...>> {
 // The tuned classes of level P (defined in pimc_batch_p<P>.hip).
 #define PIMC_BATCH_TUNED_DECL(P)                                                                                      \
     hipError_t launch_batch_tuned_##P(bool n16, int idx, const BatchTask* tasks, int n_tasks, uint64_t n_items,        \
-                                      unsigned long long* queue, uint32_t grab, const RngKey& key, int hier, int grid,  \
+                                      unsigned long long* queue, uint32_t grab, int by_group, const RngKey& key, int hier, int grid,  \
                                       size_t lds, hipStream_t st);                                                      \
     int resident_batch_tuned_##P(bool n16, int idx, size_t lds, int device);
 
 #define PIMC_BATCH_TUNED_DEF(P)                                                                                       \
     hipError_t launch_batch_tuned_##P(bool n16, int idx, const BatchTask* tasks, int n_tasks, uint64_t n_items,        \
-                                      unsigned long long* queue, uint32_t grab, const RngKey& key, int hier, int grid,  \
+                                      unsigned long long* queue, uint32_t grab, int by_group, const RngKey& key, int hier, int grid,  \
                                       size_t lds, hipStream_t st) {                                                     \
-        return n16 ? BatchLauncher<P, BatchShapesN16>::launch(idx, tasks, n_tasks, n_items, queue, grab, key, hier,    \
+        return n16 ? BatchLauncher<P, BatchShapesN16>::launch(idx, tasks, n_tasks, n_items, queue, grab, by_group, key, hier,    \
                                                              grid, lds, st)                                             \
-                   : BatchLauncher<P, BatchShapesN32>::launch(idx, tasks, n_tasks, n_items, queue, grab, key, hier,    \
+                   : BatchLauncher<P, BatchShapesN32>::launch(idx, tasks, n_tasks, n_items, queue, grab, by_group, key, hier,    \
                                                              grid, lds, st);                                            \
     }                                                                                                                  \
     int resident_batch_tuned_##P(bool n16, int idx, size_t lds, int device) {                                          \

@@ -753,6 +753,10 @@ int pimc_last_kernel_ms(pimc_ctx* c, double* ms) {
 }  // extern "C"
 
 // ============================================================================================ batch
+// Group sums a batch may keep (24 bytes per group and level): beyond, its items are whole chunks. A batch
+// of this size has 2.8e6 groups, a thousand rounds of the GPU's waves, and no longer needs the balance.
+static constexpr size_t kBatchGroupBytes = size_t(64) << 20;
+
 struct pimc_batch {
     pimc_ctx* ctx = nullptr;
     hipStream_t stream = nullptr;              // capture/replay stream (owned)
@@ -775,7 +779,8 @@ struct pimc_batch {
         ShapeDesc d{};
         int n_tasks = 0;
         size_t first = 0;                      // first position in the device task array
-        uint64_t n_items = 0;
+        uint64_t n_items = 0;                  // canonical chunks
+        uint64_t n_work = 0;                   // queue items: blocks of groups (by group), else the chunks
         int smax = 0;                          // largest s of the class
         size_t lds = 0;
         int resident = 0;
@@ -786,6 +791,8 @@ struct pimc_batch {
     void* d_blob = nullptr;
     BatchTask* d_tasks = nullptr;
     double* d_partials = nullptr;
+    double* d_gsum = nullptr;                  // group sums (by group), else null
+    GroupSegment* d_gseg = nullptr;
     uint64_t* d_seg = nullptr;
     double* d_red = nullptr;
     unsigned long long* d_queue = nullptr;
@@ -837,7 +844,7 @@ hipError_t launch_class(pimc_batch* b, size_t k, hipStream_t st) {
     const auto& C = b->classes[k];
     RngKey key{uint32_t(b->seed), uint32_t(b->seed >> 32), 0u};
     const int hier = (b->flags & PIMC_HIERARCHY) ? 1 : 0;
-    return launch_batch(b->d_tasks + C.first, C.n_tasks, C.n_items, b->d_queue + k, b->grab, key, hier, C.p, C.n16,
+    return launch_batch(b->d_tasks + C.first, C.n_tasks, C.n_work, b->d_queue + k, b->grab, b->d_gsum != nullptr, key, hier, C.p, C.n16,
                         C.shape, class_grid(b, C), C.lds, st);
 }
 
@@ -864,7 +871,8 @@ int capture_graph(pimc_batch* b) {
     hipError_t e = launch_fill_u64(b->d_queue, int(b->classes.size()), 0ull, b->stream);
     for (size_t k = 0; k < b->classes.size() && e == hipSuccess; ++k) e = launch_class(b, k, b->stream);
     if (e == hipSuccess)
-        e = launch_seg_reduce(b->d_partials, b->d_seg, b->d_seg + b->n_seg, b->n_seg, b->d_red, b->stream);
+        e = b->d_gsum ? launch_seg_groups(b->d_gseg, b->n_seg, b->d_red, b->stream)
+                      : launch_seg_reduce(b->d_partials, b->d_seg, b->d_seg + b->n_seg, b->n_seg, b->d_red, b->stream);
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->h_red, b->d_red, b->n_seg * 4 * 8, hipMemcpyDeviceToHost, b->stream);
     hipGraph_t g = nullptr;
@@ -958,12 +966,15 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
             scale_for_endpoint_sum(blob.data() + at, lv.back().deg);     // quartic evaluator form
         }
     }
-    // ---- per task: sigma, S_ref, chunking; device order grouped by p, then N = 16 before N >= 32
+    // ---- per task: sigma, S_ref, chunking; device order grouped by p, then N = 16 before N >= 32, then
+    // the long paths first (what is left at the end of a class is short)
     auto is_n16 = [&](size_t i) { return tasks[i].N == 16; };
     std::vector<size_t> order(n_tasks);
     for (size_t i = 0; i < n_tasks; ++i) order[i] = i;
     std::stable_sort(order.begin(), order.end(), [&](size_t x, size_t y) {
-        return tasks[x].p != tasks[y].p ? tasks[x].p < tasks[y].p : (is_n16(x) && !is_n16(y));
+        if (tasks[x].p != tasks[y].p) return tasks[x].p < tasks[y].p;
+        if (is_n16(x) != is_n16(y)) return is_n16(x);
+        return tasks[x].N > tasks[y].N;
     });
     b->t_s.resize(n_tasks);
     b->t_logpref.resize(n_tasks);
@@ -1006,8 +1017,8 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
         blob.insert(blob.end(), b->t_shift[i].begin(), b->t_shift[i].end());
     }
     // partial slots and segments
-    std::vector<uint64_t> t_chunks(n_tasks), t_part_off(n_tasks);
-    uint64_t part_total = 0;
+    std::vector<uint64_t> t_chunks(n_tasks), t_part_off(n_tasks), t_gsum_off(n_tasks);
+    uint64_t part_total = 0, gsum_total = 0;
     std::vector<uint64_t> seg_base, seg_len;
     for (size_t pos = 0; pos < n_tasks; ++pos) {
         const size_t i = order[pos];
@@ -1020,7 +1031,10 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
             seg_len.push_back(t_chunks[i]);
         }
         part_total += uint64_t(slots) * t_chunks[i];
+        t_gsum_off[i] = gsum_total * 3;
+        gsum_total += uint64_t(slots) * ((tasks[i].n_samples + 63) / 64);
     }
+    const bool by_group = gsum_total <= kBatchGroupBytes / 24;
     b->n_seg = seg_base.size();
     // ---- device buffers
     int st;
@@ -1032,6 +1046,10 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
     if ((st = dmalloc(&b->d_blob, blob.size() * 8))) return fail(st);
     if ((st = dmalloc(reinterpret_cast<void**>(&b->d_tasks), n_tasks * sizeof(BatchTask)))) return fail(st);
     if ((st = dmalloc(reinterpret_cast<void**>(&b->d_partials), part_total * 4 * 8))) return fail(st);
+    if (by_group) {
+        if ((st = dmalloc(reinterpret_cast<void**>(&b->d_gsum), gsum_total * 24))) return fail(st);
+        if ((st = dmalloc(reinterpret_cast<void**>(&b->d_gseg), b->n_seg * sizeof(GroupSegment)))) return fail(st);
+    }
     if ((st = dmalloc(reinterpret_cast<void**>(&b->d_seg), b->n_seg * 2 * 8))) return fail(st);
     if ((st = dmalloc(reinterpret_cast<void**>(&b->d_red), b->n_seg * 4 * 8))) return fail(st);
     if ((st = dmalloc(reinterpret_cast<void**>(&b->d_queue), 64 * 8))) return fail(st);
@@ -1054,6 +1072,9 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
         r.b = t.b * sm;
         r.n_paths = t.n_samples;
         r.n_chunks = t_chunks[i];
+        r.gsum = by_group ? b->d_gsum + t_gsum_off[i] : nullptr;
+        // a ticket costs about what 16 slices of a group do (pimc_chunks.hpp)
+        r.block = t.N >= 64 ? 1u : 64u / t.N;
         r.stream = t.stream;
         r.s = b->t_s[i];
     }
@@ -1064,8 +1085,9 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
         C.n16 = is_n16(order[pos]);
         C.first = pos;
         while (pos < n_tasks && tasks[order[pos]].p == C.p && is_n16(order[pos]) == C.n16) {
-            dt[pos].item0 = C.n_items;
+            dt[pos].item0 = C.n_work;
             C.n_items += dt[pos].n_chunks;
+            C.n_work += by_group ? ((dt[pos].n_paths + 63) / 64 + dt[pos].block - 1) / dt[pos].block : dt[pos].n_chunks;
             C.smax = std::max(C.smax, dt[pos].s);
             ++C.n_tasks;
             ++pos;
@@ -1078,12 +1100,23 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
     std::vector<uint64_t> seg(b->n_seg * 2);
     std::copy(seg_base.begin(), seg_base.end(), seg.begin());
     std::copy(seg_len.begin(), seg_len.end(), seg.begin() + b->n_seg);
+    std::vector<GroupSegment> gseg;
+    if (by_group)
+        for (size_t pos = 0; pos < n_tasks; ++pos) {
+            const size_t i = order[pos];
+            const uint64_t groups = (tasks[i].n_samples + 63) / 64;
+            for (int k = 0; k < (hier ? b->t_s[i] + 1 : 1); ++k)
+                gseg.push_back(GroupSegment{b->d_gsum + t_gsum_off[i] + uint64_t(k) * groups * 3,
+                                            b->d_partials + seg_base[b->t_seg[i] + size_t(k)], tasks[i].n_samples});
+        }
     HIP_TRY_B(b, hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking));
     HIP_TRY_B(b, hipEventCreate(&b->e0));
     HIP_TRY_B(b, hipEventCreate(&b->e1));
     HIP_TRY_B(b, hipMemcpyAsync(b->d_blob, blob.data(), blob.size() * 8, hipMemcpyHostToDevice, b->stream));
     HIP_TRY_B(b, hipMemcpyAsync(b->d_tasks, dt.data(), dt.size() * sizeof(BatchTask), hipMemcpyHostToDevice, b->stream));
     HIP_TRY_B(b, hipMemcpyAsync(b->d_seg, seg.data(), seg.size() * 8, hipMemcpyHostToDevice, b->stream));
+    if (by_group)
+        HIP_TRY_B(b, hipMemcpyAsync(b->d_gseg, gseg.data(), gseg.size() * sizeof(GroupSegment), hipMemcpyHostToDevice, b->stream));
     HIP_TRY_B(b, hipStreamSynchronize(b->stream));
     if ((st = capture_graph(b))) return fail(st);
     *out = b;
@@ -1273,6 +1306,8 @@ int pimc_batch_destroy(pimc_batch* b) {
     (void)hipFree(b->d_blob);
     (void)hipFree(b->d_tasks);
     (void)hipFree(b->d_partials);
+    (void)hipFree(b->d_gsum);
+    (void)hipFree(b->d_gseg);
     (void)hipFree(b->d_seg);
     (void)hipFree(b->d_red);
     (void)hipFree(b->d_queue);

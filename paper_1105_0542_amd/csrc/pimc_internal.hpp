@@ -175,6 +175,15 @@ hipError_t launch_group_chunks(const PathWork& w, int slots, uint64_t n_paths, d
 hipError_t launch_seg_reduce(const double* partials, const uint64_t* base, const uint64_t* len, uint64_t n_seg,
                              double* out, hipStream_t st);
 
+// A segment whose groups are all fine: its group sums, where its chunk records go, its paths.
+struct GroupSegment {
+    const double* gsum;                // [group][3]
+    double* records;                   // [chunk][4]
+    uint64_t n_paths;
+};
+// Chunk records and canonical reduction of such segments: out[i][4] (all device).
+hipError_t launch_seg_groups(const GroupSegment* segs, uint64_t n_seg, double* out, hipStream_t st);
+
 // One task of a batch, as the persistent kernel reads it (device array, wave-uniform loads).
 struct BatchTask {
     const double* tab;                 // level tables of the task's (system, T, p), quartic layout
@@ -184,7 +193,9 @@ struct BatchTask {
     double a, b;                       // endpoints after the mass rescaling
     uint64_t n_paths;
     uint64_t n_chunks;
-    uint64_t item0;                    // queue index of the task's chunk 0
+    uint64_t item0;                    // queue index of the task's first item
+    double* gsum;                      // [slot][group][3], by group; null: by whole chunk
+    uint32_t block;                    // groups per item (by group)
     uint32_t stream;
     int s;
 };
@@ -201,7 +212,7 @@ struct ShapeDesc {
 int batch_shape_count(int p, bool n16);
 bool batch_shape(int p, bool n16, int idx, ShapeDesc& d);
 hipError_t launch_batch(const BatchTask* tasks, int n_tasks, uint64_t n_items, unsigned long long* queue, uint32_t grab,
-                        const RngKey& key, int hier, int p, bool n16, int shape, int grid, size_t lds, hipStream_t st);
+                        int by_group, const RngKey& key, int hier, int p, bool n16, int shape, int grid, size_t lds, hipStream_t st);
 int batch_resident_blocks(int p, bool n16, int shape, size_t lds_bytes, int device);
 hipError_t launch_fill_u64(unsigned long long* p, int n, unsigned long long v, hipStream_t st);
 

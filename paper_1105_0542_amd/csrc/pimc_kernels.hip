@@ -48,25 +48,20 @@ hipError_t launch_normals(const RngKey& key, uint64_t first_path, uint64_t k_pat
 }
 
 // ---------------------------------------------------------------------------- chunk reduction
-// Group sums into chunk records (pimc_chunks.hpp). Four lanes per (slot, chunk): lane q adds groups
-// q, q + 4, ... of the chunk -- an accumulator slot -- and then the four slots are added in order.
-// Bound by latency: a chunk's 64 x 24 bytes are read with 16 loads in flight per lane.
-__global__ void __launch_bounds__(kBlock) k_group_chunks(const double* __restrict__ gsum, uint64_t first_chunk,
-                                                         uint64_t n_fine, uint64_t n_chunks, uint64_t n_paths,
-                                                         double* __restrict__ partials) {
-    const uint64_t i = uint64_t(blockIdx.x) * kBlock + threadIdx.x;
-    const int q = int(i & 3u);
-    const uint64_t fc = i >> 2;
-    const uint64_t slot = blockIdx.y;
-    const bool live = first_chunk + fc < n_chunks;
+// Group sums into chunk records (pimc_chunks.hpp): component q of the record of the chunk whose first
+// group is g0 (of n_groups), by a quad of lanes: lane q adds groups q, q + 4, ... of the chunk -- an
+// accumulator slot -- and then the four slots are added in order. Bound by latency: a chunk's 64 x 24
+// bytes are read with the 16 groups' loads of a lane in flight.
+__device__ __forceinline__ double chunk_component(const double* __restrict__ gsum, uint64_t g0, uint64_t n_groups,
+                                                  double cnt, bool live) {
+    const int q = int(threadIdx.x & 3u);
     double s[3] = {0.0, 0.0, 0.0};
-    const double* p = gsum + (slot * n_fine + fc * kChunkGroups) * 3;
 #pragma unroll
     for (int k = 0; k < kChunkGroups / kChunkSlots; ++k) {
-        const int g = k * kChunkSlots + q;
-        if (live && fc * kChunkGroups + uint64_t(g) < n_fine) {
+        const uint64_t g = g0 + uint64_t(k * kChunkSlots + q);
+        if (live && g < n_groups) {
 #pragma unroll
-            for (int j = 0; j < 3; ++j) s[j] += p[g * 3 + j];
+            for (int j = 0; j < 3; ++j) s[j] += gsum[g * 3 + j];
         }
     }
     double t[3];
@@ -77,10 +72,23 @@ __global__ void __launch_bounds__(kBlock) k_group_chunks(const double* __restric
 #pragma unroll
         for (int k = 0; k < kChunkSlots; ++k) t[j] += __shfl(s[j], lane0 + k, 64);
     }
-    if (!live) return;
-    const uint64_t rem = n_paths - (first_chunk + fc) * kChunkPaths;
-    const double cnt = double(rem < kChunkPaths ? rem : kChunkPaths);
-    partials[(slot * n_chunks + first_chunk + fc) * 4 + q] = q == 0 ? cnt : (q == 1 ? t[0] : (q == 2 ? t[1] : t[2]));
+    return q == 0 ? cnt : (q == 1 ? t[0] : (q == 2 ? t[1] : t[2]));
+}
+
+__device__ __forceinline__ double chunk_count(uint64_t n_paths, uint64_t c) {
+    const uint64_t rem = n_paths - c * kChunkPaths;
+    return double(rem < kChunkPaths ? rem : kChunkPaths);
+}
+
+__global__ void __launch_bounds__(kBlock) k_group_chunks(const double* __restrict__ gsum, uint64_t first_chunk,
+                                                         uint64_t n_fine, uint64_t n_chunks, uint64_t n_paths,
+                                                         double* __restrict__ partials) {
+    const uint64_t i = uint64_t(blockIdx.x) * kBlock + threadIdx.x;
+    const uint64_t c = first_chunk + (i >> 2);
+    const uint64_t slot = blockIdx.y;
+    const bool live = c < n_chunks;
+    const double v = chunk_component(gsum + slot * n_fine * 3, (i >> 2) * kChunkGroups, n_fine, chunk_count(n_paths, c), live);
+    if (live) partials[(slot * n_chunks + c) * 4 + (i & 3u)] = v;
 }
 
 hipError_t launch_group_chunks(const PathWork& w, int slots, uint64_t n_paths, double* partials, hipStream_t st) {
@@ -97,15 +105,9 @@ hipError_t launch_group_chunks(const PathWork& w, int slots, uint64_t n_paths, d
 // thread t adds chunks t, t + kBlock, ... in order, then a fixed halving tree over the threads.
 // The order depends only on the chunk count, so any run -- single or one task of a batch, any
 // grid -- gives the same bits for the same chunks.
-__global__ void __launch_bounds__(kBlock) k_seg_reduce(const double* __restrict__ partials,
-                                                       const uint64_t* __restrict__ base,
-                                                       const uint64_t* __restrict__ len,
-                                                       double* __restrict__ out) {
+__device__ __forceinline__ void seg_reduce(const double* p, uint64_t n, double* __restrict__ out) {
     __shared__ double red[4][kBlock];
-    const uint64_t seg = blockIdx.x;
     const int tid = threadIdx.x;
-    const double* p = partials + base[seg];
-    const uint64_t n = len[seg];
     double s[4] = {0.0, 0.0, 0.0, 0.0};
     for (uint64_t c = tid; c < n; c += kBlock) {
 #pragma unroll
@@ -121,7 +123,41 @@ __global__ void __launch_bounds__(kBlock) k_seg_reduce(const double* __restrict_
         }
         __syncthreads();
     }
-    if (tid < 4) out[seg * 4 + tid] = red[tid][0];
+    if (tid < 4) out[tid] = red[tid][0];
+}
+
+__global__ void __launch_bounds__(kBlock) k_seg_reduce(const double* __restrict__ partials,
+                                                       const uint64_t* __restrict__ base,
+                                                       const uint64_t* __restrict__ len,
+                                                       double* __restrict__ out) {
+    const uint64_t seg = blockIdx.x;
+    seg_reduce(partials + base[seg], len[seg], out + seg * 4);
+}
+
+// The same from group sums: the workgroup first forms its segment's chunk records (64 quads), then
+// reduces them. One launch instead of two, for segments of few chunks.
+__global__ void __launch_bounds__(kBlock) k_seg_groups(const GroupSegment* __restrict__ segs, double* __restrict__ out) {
+    const const_ptr<GroupSegment> S = as_const(segs) + blockIdx.x;
+    const double* gsum = S->gsum;
+    double* rec = S->records;
+    const uint64_t n_paths = S->n_paths;
+    const uint64_t n_groups = (n_paths + 63) / 64;
+    const uint64_t n_chunks = (n_paths + kChunkPaths - 1) / kChunkPaths;
+    for (uint64_t c0 = 0; c0 < n_chunks; c0 += kBlock / 4) {
+        const uint64_t c = c0 + (threadIdx.x >> 2);
+        const bool live = c < n_chunks;
+        const double v = chunk_component(gsum, c * kChunkGroups, n_groups, chunk_count(n_paths, c), live);
+        if (live) rec[c * 4 + (threadIdx.x & 3u)] = v;
+    }
+    __syncthreads();
+    seg_reduce(rec, n_chunks, out + uint64_t(blockIdx.x) * 4);
+}
+
+hipError_t launch_seg_groups(const GroupSegment* segs, uint64_t n_seg, double* out, hipStream_t st) {
+    if (n_seg == 0) return hipSuccess;
+    if (n_seg > 0x7fffffffull) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_seg_groups, dim3(uint32_t(n_seg)), dim3(kBlock), 0, st, segs, out);
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------- dispatch

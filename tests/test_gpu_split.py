@@ -66,3 +66,21 @@ def test_ragged_runs_agree_with_their_paths(ctx, s, n):
         assert rec[0][0] == k and rec[0][3] == 0
         assert abs(rec[0][1] - d.sum()) <= tol
         assert abs(rec[0][2] - (d * d).sum()) <= 2 * tol * max(1.0, np.abs(d).max())
+
+
+@pytest.mark.parametrize("big,flags", [(200_000_000, 0), (40_000_001, P.FLAG_HIERARCHY), (70_001, 0), (70_001, P.FLAG_HIERARCHY)])
+def test_batch_items_by_chunk_and_by_group_equal_single_calls(ctx, big, flags):
+    """200e6 paths have 3.1e6 groups, beyond the 2.8e6 whose sums a batch keeps (whole chunks); 40e6 with
+    five levels likewise; 70,001 go by group. Ragged and short tasks of other N beside them."""
+    rows = [(0, 1.0, 0.0, 0.7, 0.8, 16, 1, big, 3), (0, 1.0, 0.1, 0.5, 0.8, 32, 1, 4097, 4),
+            (0, 1.0, 0.2, 0.5, 0.8, 128, 1, 65, 5), (0, 1.0, 0.2, 0.4, 0.8, 64, 2, 2, 6), (0, 1.0, 0.2, 0.4, 0.8, 16, 2, 63, 7)]
+    bt = P.Batch(ctx, [P.quartic(1.0, 2.0)], rows, 5, flags)
+    res, _, _ = bt.run()
+    again, _, _ = bt.run()
+    bt.close()
+    assert res.tobytes() == again.tobytes()
+    for i, (_, m, a, b, T, N, p, n, stream) in enumerate(rows):
+        one, _ = ctx.amplitude(P.quartic(1.0, 2.0), m, a, b, T, N, p, n, 5, stream, flags)
+        for level, r in enumerate(one):
+            got = res[i, level]
+            assert (got["amp"], got["err"], got["n"]) == (r.amp, r.err, r.n), (i, level)
