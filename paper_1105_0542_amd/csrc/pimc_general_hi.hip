@@ -24,7 +24,7 @@ static_assert(gen_subtree_levels(PIMC_GEN_P) == 3, "three-level subtrees above t
 
 // U = min(s, 3): subtrees of 1 and 2 levels only for N = 2 and 4
 template <>
-hipError_t gen_hi_launch<PIMC_GEN_P>(const AmpArgs& A, int U, int grid, hipStream_t st) {
+hipError_t gen_hi_launch<PIMC_GEN_P>(const AmpArgs& A, int U, int grid, LaunchOn st) {
     const GenSliceEval<PIMC_GEN_P> ev{A.tab64, A.gen};
     switch (U) {
         case 1: return launch_one<DefaultShape<1>>(A, ev, grid, st);

@@ -12,7 +12,7 @@ namespace pimc {
 namespace {
 
 template <int P>
-hipError_t launch_p(const AmpArgs& A, int p, int U, int grid, hipStream_t st) {
+hipError_t launch_p(const AmpArgs& A, int p, int U, int grid, LaunchOn st) {
     if constexpr (P <= kGenInlineMaxP) {
         if (p != P) return launch_p<P + 1>(A, p, U, grid, st);
         const GenCompiledEval<P> ev{A.tab64, A.gen};
@@ -58,7 +58,7 @@ int nrec_p(int p) {
 
 static_assert(kGenInlineMaxP == 10 && kGenMaxP == 18, "the out-of-line levels 11..18 are declared in pimc_internal.hpp");
 
-hipError_t launch_general_compiled(const AmpArgs& A, int p, int U, int grid, hipStream_t st) {
+hipError_t launch_general_compiled(const AmpArgs& A, int p, int U, int grid, LaunchOn st) {
     switch (p) {
         case 11: return gen_hi_launch<11>(A, U, grid, st);
         case 12: return gen_hi_launch<12>(A, U, grid, st);

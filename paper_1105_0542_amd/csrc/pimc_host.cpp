@@ -64,6 +64,55 @@ int ensure(pimc_ctx* c, void** buf, size_t* have, size_t need) {
     return PIMC_OK;
 }
 
+int pinned_stage(pimc_ctx* c, size_t need, unsigned char** out) {
+    if (c->stage_busy) HIP_TRY(c, hipStreamSynchronize(c->stream));   // an earlier call ended on an error
+    c->stage_busy = false;
+    if (kRedBytes + need > c->stage_bytes) {
+        if (c->h_stage) HIP_TRY(c, hipHostFree(c->h_stage));
+        c->h_stage = nullptr;
+        c->stage_bytes = 0;
+        const size_t alloc = std::max(kRedBytes + need, size_t(1) << 16);
+        const hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&c->h_stage), alloc, 0);
+        if (e != hipSuccess) {
+            c->h_stage = nullptr;
+            return ctx_fail(c, PIMC_ENOMEM, "hipHostMalloc(%zu) failed: %s", alloc, hipGetErrorString(e));
+        }
+        c->stage_bytes = alloc;
+    }
+    *out = c->h_stage + kRedBytes;
+    return PIMC_OK;
+}
+
+// One launch (k_seg_groups) up to this many chunks, all fine: 25 chunks x 5 levels 7 us against 6 + 3.5
+// us and a gap for the two; beyond, its one workgroup per level is slower than k_group_chunks' many.
+static bool short_run(const PathWork& w) { return w.n_coarse == 0 && w.n_chunks <= 128; }
+
+std::vector<unsigned char> run_segments(const PathWork& w, int slots, uint64_t n_paths, double* partials) {
+    std::vector<unsigned char> out;
+    if (short_run(w)) {
+        out.resize(size_t(slots) * sizeof(GroupSegment));
+        for (int k = 0; k < slots; ++k) {
+            const GroupSegment g{w.gsum + size_t(k) * size_t(w.n_groups) * 3, partials + size_t(k) * size_t(w.n_chunks) * 4, n_paths};
+            std::memcpy(out.data() + size_t(k) * sizeof(g), &g, sizeof(g));
+        }
+    } else {
+        std::vector<uint64_t> seg(size_t(slots) * 2, w.n_chunks);
+        for (int k = 0; k < slots; ++k) seg[size_t(k)] = uint64_t(k) * w.n_chunks * 4;
+        out.resize(seg.size() * 8);
+        std::memcpy(out.data(), seg.data(), out.size());
+    }
+    return out;
+}
+
+hipError_t launch_run_sums(const PathWork& w, int slots, uint64_t n_paths, double* partials, const void* segs, double* out,
+                           hipStream_t st) {
+    if (short_run(w)) return launch_seg_groups(static_cast<const GroupSegment*>(segs), uint64_t(slots), out, st);
+    const hipError_t e = launch_group_chunks(w, slots, n_paths, partials, st);
+    if (e != hipSuccess) return e;
+    const uint64_t* seg = static_cast<const uint64_t*>(segs);
+    return launch_seg_reduce(partials, seg, seg + slots, uint64_t(slots), out, st);
+}
+
 bool finite(double v) { return std::isfinite(v); }
 
 int log2_exact(uint32_t N) {
@@ -282,10 +331,11 @@ int check_mpt(const pimc_mpt* V, double m, double a, double b, double T, uint32_
     return check_args(&zero, m, a, b, T, N, p, n_samples);
 }
 
-// Upload tables and per-level constants (into the context's buffer, or into work->prm); fill the
-// kernel arguments except the output pointers.
+// Upload tables, per-level constants and the segments of the run's reduction (into the context's buffer,
+// by way of its pinned one and without waiting, or into the workspace); fill the kernel arguments except
+// the output pointers. *segs_dev: where the segments are.
 int stage_problem(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t stream, AmpArgs& A,
-                  const DeviceWork* work = nullptr) {
+                  const std::vector<unsigned char>& segs, const void** segs_dev, const DeviceWork* work = nullptr) {
     const size_t nlev = size_t(P.s + 1);
     const size_t n_tab = P.tab.size();
     // layout: sig[nlev] shift[nlev] tab64[n_tab] tab32[n_tab] deg[K]
@@ -298,17 +348,25 @@ int stage_problem(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t stream,
     const size_t off_dsech = off_dpoly + P.gen.dpoly.size() * 8;
     // the two work counters of the persistent kernel, zero, on a 256-byte line of their own
     const size_t off_queue = (off_dsech + P.gen.dsech.size() * 8 + 255) & ~size_t(255);
-    const size_t total = off_queue + 256;
-    std::vector<unsigned char> host(total, 0);
-    std::memcpy(host.data(), P.sig.data(), nlev * 8);
-    std::memcpy(host.data() + off_shift, P.shift.data(), nlev * 8);
-    if (n_tab) {
-        std::memcpy(host.data() + off_tab, P.tab_dev.data(), n_tab * 8);
-        std::memcpy(host.data() + off_tab32, P.tab32.data(), n_tab * 4);
+    const size_t off_segs = off_queue + 256;
+    const size_t total = off_segs + (work ? 0 : segs.size());
+    std::vector<unsigned char> heap(work ? total : 0);
+    unsigned char* host = heap.data();
+    if (!work) {
+        const int st = pinned_stage(c, total, &host);
+        if (st) return st;
     }
-    if (!P.deg.empty()) std::memcpy(host.data() + off_deg, P.deg.data(), P.deg.size() * 4);
-    if (!P.gen.dpoly.empty()) std::memcpy(host.data() + off_dpoly, P.gen.dpoly.data(), P.gen.dpoly.size() * 8);
-    if (!P.gen.dsech.empty()) std::memcpy(host.data() + off_dsech, P.gen.dsech.data(), P.gen.dsech.size() * 8);
+    std::memset(host, 0, total);
+    std::memcpy(host, P.sig.data(), nlev * 8);
+    std::memcpy(host + off_shift, P.shift.data(), nlev * 8);
+    if (n_tab) {
+        std::memcpy(host + off_tab, P.tab_dev.data(), n_tab * 8);
+        std::memcpy(host + off_tab32, P.tab32.data(), n_tab * 4);
+    }
+    if (!P.deg.empty()) std::memcpy(host + off_deg, P.deg.data(), P.deg.size() * 4);
+    if (!P.gen.dpoly.empty()) std::memcpy(host + off_dpoly, P.gen.dpoly.data(), P.gen.dpoly.size() * 8);
+    if (!P.gen.dsech.empty()) std::memcpy(host + off_dsech, P.gen.dsech.data(), P.gen.dsech.size() * 8);
+    if (!work && !segs.empty()) std::memcpy(host + off_segs, segs.data(), segs.size());
     void* prm = nullptr;
     if (work) {
         if (total > work->prm_cap)
@@ -319,10 +377,15 @@ int stage_problem(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t stream,
         if (st) return st;
         prm = c->d_prm;
     }
-    HIP_TRY(c, hipMemcpyAsync(prm, host.data(), total, hipMemcpyHostToDevice, c->stream));
-    // the host vector must stay valid until the copy has read it
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    if (!work) c->stage_busy = true;
+    HIP_TRY(c, hipMemcpyAsync(prm, host, total, hipMemcpyHostToDevice, c->stream));
+    if (work) {
+        // the host vectors must stay valid until the copies have read them
+        if (!segs.empty()) HIP_TRY(c, hipMemcpyAsync(work->seg, segs.data(), segs.size(), hipMemcpyHostToDevice, c->stream));
+        HIP_TRY(c, hipStreamSynchronize(c->stream));
+    }
     unsigned char* base = static_cast<unsigned char*>(prm);
+    *segs_dev = work ? static_cast<const void*>(work->seg) : base + off_segs;
     std::memset(&A, 0, sizeof(A));
     A.sig = reinterpret_cast<const double*>(base);
     A.shift = reinterpret_cast<const double*>(base + off_shift);
@@ -408,10 +471,8 @@ int amplitude_core(pimc_ctx* c, const Problem& P, uint64_t n_samples, uint64_t s
     const int resident = resident_blocks(c, P);
     PathWork pw;
     double* partials;
-    double* red_dev;
-    uint64_t* seg;
     if (work) {
-        if (partial_bytes > work->partial_cap || size_t(slots) * 32 > work->red_cap || size_t(slots) * 16 > work->seg_cap)
+        if (partial_bytes > work->partial_cap || size_t(slots) * 32 > work->red_cap || size_t(slots) * sizeof(GroupSegment) > work->seg_cap)
             return ctx_fail(c, PIMC_EINVAL,
                             "%llu samples x %d levels need %zu bytes of chunk sums, the workspace holds %zu",
                             (unsigned long long)n_samples, slots, partial_bytes, work->partial_cap);
@@ -420,48 +481,36 @@ int amplitude_core(pimc_ctx* c, const Problem& P, uint64_t n_samples, uint64_t s
         const size_t left = work->partial_cap - partial_bytes;
         pw = split_paths(n_samples, P.s, slots, std::min(left, kFineBytes), uint64_t(resident) * (kBlock / 64));
         pw.gsum = partials + partial_bytes / 8;
-        red_dev = work->red;
-        seg = work->seg;
     } else {
         st = ensure(c, reinterpret_cast<void**>(&c->d_partials), &c->partial_bytes, partial_bytes);
-        if (st) return st;
-        st = ensure(c, reinterpret_cast<void**>(&c->d_red), &c->red_bytes, size_t(slots) * 4 * 8);
-        if (st) return st;
-        st = ensure(c, reinterpret_cast<void**>(&c->d_seg), &c->seg_bytes, size_t(slots) * 2 * 8);
         if (st) return st;
         pw = split_paths(n_samples, P.s, slots, kFineBytes, uint64_t(resident) * (kBlock / 64));
         st = ensure(c, reinterpret_cast<void**>(&c->d_gsum), &c->gsum_bytes, group_sum_bytes(pw, slots));
         if (st) return st;
         pw.gsum = c->d_gsum;
         partials = c->d_partials;
-        red_dev = c->d_red;
-        seg = c->d_seg;
     }
     AmpArgs A;
-    st = stage_problem(c, P, seed, stream, A, work);
+    const void* segs = nullptr;
+    st = stage_problem(c, P, seed, stream, A, run_segments(pw, slots, n_samples, partials), &segs, work);
     if (st) return st;
+    // the last kernel writes the sums straight into pinned memory (the workspace's are copied)
+    double* const red_out = work ? work->red : reinterpret_cast<double*>(c->h_stage);
     pw.queue = A.work.queue;
     A.work = pw;
-    c->h_seg.assign(size_t(slots) * 2, 0);
-    for (int k = 0; k < slots; ++k) {
-        c->h_seg[size_t(k)] = uint64_t(k) * n_chunks * 4;
-        c->h_seg[size_t(slots + k)] = n_chunks;
-    }
-    HIP_TRY(c, hipMemcpyAsync(seg, c->h_seg.data(), c->h_seg.size() * 8, hipMemcpyHostToDevice, c->stream));
     A.first_path = 0;
     A.n_paths = n_samples;
     A.hier = hier ? 1 : 0;
     A.partials = partials;
     A.dump = nullptr;
     const int grid = work_grid(A.work, kBlock / 64, resident);
-    HIP_TRY(c, hipEventRecord(c->ev0, c->stream));
-    HIP_TRY(c, launch_amplitude(A, P.kind, P.p, P.U, grid, c->stream));
-    HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
-    HIP_TRY(c, launch_group_chunks(A.work, slots, n_samples, partials, c->stream));
-    HIP_TRY(c, launch_seg_reduce(partials, seg, seg + slots, uint64_t(slots), red_dev, c->stream));
-    double red[4 * (PIMC_MAX_S + 1)];
-    HIP_TRY(c, hipMemcpyAsync(red, red_dev, size_t(slots) * 4 * 8, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(c, launch_amplitude(A, P.kind, P.p, P.U, grid, LaunchOn(c->stream, c->ev0, c->ev1)));
+    HIP_TRY(c, launch_run_sums(A.work, slots, n_samples, partials, segs, red_out, c->stream));
+    double red_copy[4 * (PIMC_MAX_S + 1)];
+    if (work) HIP_TRY(c, hipMemcpyAsync(red_copy, red_out, size_t(slots) * 4 * 8, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    c->stage_busy = false;
+    const double* red = work ? red_copy : red_out;
     float ms = 0.f;
     HIP_TRY(c, hipEventElapsedTime(&ms, c->ev0, c->ev1));
     c->last_ms = ms;
@@ -489,7 +538,8 @@ int path_actions_core(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t str
         return PIMC_OK;
     }
     AmpArgs A;
-    st = stage_problem(c, P, seed, stream, A);
+    const void* segs = nullptr;
+    st = stage_problem(c, P, seed, stream, A, {}, &segs);
     if (st) return st;
     st = ensure(c, reinterpret_cast<void**>(&c->d_dump), &c->dump_bytes, size_t(k_paths) * nlev * 8);
     if (st) return st;
@@ -506,6 +556,7 @@ int path_actions_core(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t str
     HIP_TRY(c, launch_amplitude(A, P.kind, P.p, P.U, grid, c->stream));
     HIP_TRY(c, hipMemcpyAsync(S_out, c->d_dump, size_t(k_paths) * nlev * 8, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    c->stage_busy = false;
     // level 0 is the same straight slice for every path: report it for every path
     for (uint64_t i = 0; i < k_paths; ++i)
         if (!(flags & PIMC_HIERARCHY)) S_out[i * nlev] = 0.0;
@@ -607,6 +658,7 @@ int pimc_destroy(pimc_ctx* c) {
     (void)hipFree(c->d_seg);
     (void)hipFree(c->d_dump);
     (void)hipFree(c->d_gsum);
+    if (c->h_stage) (void)hipHostFree(c->h_stage);
     if (c->ev0) (void)hipEventDestroy(c->ev0);
     if (c->ev1) (void)hipEventDestroy(c->ev1);
     if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);

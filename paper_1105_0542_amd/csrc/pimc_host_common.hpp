@@ -22,7 +22,10 @@ struct pimc_ctx {
     double* d_partials = nullptr;   size_t partial_bytes = 0;
     double* d_red = nullptr;        size_t red_bytes = 0;
     uint64_t* d_seg = nullptr;      size_t seg_bytes = 0;
-    std::vector<uint64_t> h_seg;    // segment base/len of the last reduction (kept alive for the async copy)
+    std::vector<uint64_t> h_seg;    // segment base/len of the last proposal reduction (kept alive for the async copy)
+    // pinned: the reduced sums of a run (kRedBytes, written by its last kernel), then what it uploads
+    unsigned char* h_stage = nullptr;  size_t stage_bytes = 0;
+    bool stage_busy = false;        // a copy out of it may still be under way
     double* d_dump = nullptr;       size_t dump_bytes = 0;
     double* d_gsum = nullptr;       size_t gsum_bytes = 0;     // group sums of the fine chunks (at most kFineBytes)
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
@@ -44,6 +47,16 @@ void set_thread_error(const char* fmt, ...);
 int ctx_fail(pimc_ctx* c, int status, const char* fmt, ...);
 // Grow a device buffer to at least need bytes (contents are not kept).
 int ensure(pimc_ctx* c, void** buf, size_t* have, size_t need);
+
+// The context's pinned buffer, with room for the sums of a run and for `need` bytes to upload (at
+// *out); free for writing when this returns.
+constexpr size_t kRedBytes = size_t(PIMC_MAX_S + 1) * 4 * 8;
+int pinned_stage(pimc_ctx* c, size_t need, unsigned char** out);
+// What the reduction of a run reads on the device (GroupSegment per slot for a short run, else base and
+// length per slot), and its launch: chunk records from the fine groups' sums, then out[slot][4].
+std::vector<unsigned char> run_segments(const pimc::PathWork& w, int slots, uint64_t n_paths, double* partials);
+hipError_t launch_run_sums(const pimc::PathWork& w, int slots, uint64_t n_paths, double* partials, const void* segs,
+                           double* out, hipStream_t st);
 
 #define HIP_TRY(ctx, expr)                                                                      \
     do {                                                                                        \

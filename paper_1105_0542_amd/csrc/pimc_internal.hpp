@@ -1,6 +1,7 @@
 // Internal interface between the host library (pimc_host.cpp) and the kernels (pimc_kernels.hip).
 #pragma once
 
+#include <hip/hip_ext.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -119,35 +120,43 @@ inline size_t amp_lds_bytes(int D, int s, int BS) {
            sizeof(double);
 }
 
+// Where an estimation kernel is launched, and the events (or null) that its own dispatch records: a
+// recorded event of its own is another packet and a gap of some us before and after the kernel.
+struct LaunchOn {
+    hipStream_t st;
+    hipEvent_t start, stop;
+    LaunchOn(hipStream_t stream, hipEvent_t e0 = nullptr, hipEvent_t e1 = nullptr) : st(stream), start(e0), stop(e1) {}
+};
+
 // Launch the estimation kernel; p selects the quartic specialization, U = s - D the unrolled
 // subtree depth. Returns hipErrorInvalidValue for an unsupported combination.
-hipError_t launch_amplitude(const AmpArgs& A, EvalKind kind, int p, int U, int grid, hipStream_t st);
+hipError_t launch_amplitude(const AmpArgs& A, EvalKind kind, int p, int U, int grid, LaunchOn st);
 
 // The compile-time shapes of level p with U = 4 (pimc_kernels_q64.hip, pimc_kernels_q32.hip,
 // pimc_kernels_tanh.hip): hipErrorInvalidValue / 256 for p outside 1..kMaxP.
-hipError_t launch_quartic64(const AmpArgs& A, int p, int U, int grid, hipStream_t st);
-hipError_t launch_quartic32(const AmpArgs& A, int p, int U, int grid, hipStream_t st);
-hipError_t launch_tanh_fixed(const AmpArgs& A, int p, int grid, hipStream_t st);
+hipError_t launch_quartic64(const AmpArgs& A, int p, int U, int grid, LaunchOn st);
+hipError_t launch_quartic32(const AmpArgs& A, int p, int U, int grid, LaunchOn st);
+hipError_t launch_tanh_fixed(const AmpArgs& A, int p, int grid, LaunchOn st);
 int resident_quartic64(int p, int U, size_t lds_bytes, int device);
 int resident_quartic32(int p, int U, size_t lds_bytes, int device);
 int resident_tanh_fixed(int p, size_t lds_bytes, int device);
 
 // General-potential mode (pimc_general_kernels.hip): the evaluators generated for level p; the
 // number of monomials of the level-p table (-1 outside 1..kGenMaxP).
-hipError_t launch_general_compiled(const AmpArgs& A, int p, int U, int grid, hipStream_t st);
+hipError_t launch_general_compiled(const AmpArgs& A, int p, int U, int grid, LaunchOn st);
 int general_compiled_resident(int p, int U, size_t lds_bytes, int device);
 int general_compiled_nrec(int p);
 // The levels above kGenInlineMaxP, one translation unit each (pimc_general_hi.hip built with
 // PIMC_GEN_P = p): launch, resident workgroups per CU and monomial count of that level's evaluator.
 template <int P>
-hipError_t gen_hi_launch(const AmpArgs& A, int U, int grid, hipStream_t st);
+hipError_t gen_hi_launch(const AmpArgs& A, int U, int grid, LaunchOn st);
 template <int P>
 int gen_hi_resident(int U, size_t lds_bytes, int device);
 template <int P>
 int gen_hi_nrec();
 #define PIMC_GEN_HI_DECLARE(P)                                                         \
     template <>                                                                         \
-    hipError_t gen_hi_launch<P>(const AmpArgs& A, int U, int grid, hipStream_t st);    \
+    hipError_t gen_hi_launch<P>(const AmpArgs& A, int U, int grid, LaunchOn st);    \
     template <>                                                                         \
     int gen_hi_resident<P>(int U, size_t lds_bytes, int device);                        \
     template <>                                                                         \

@@ -163,7 +163,7 @@ hipError_t launch_seg_groups(const GroupSegment* segs, uint64_t n_seg, double* o
 // ---------------------------------------------------------------------------- dispatch
 
 template <bool EVEN>
-static hipError_t launch_generic(const AmpArgs& A, int U, int grid, hipStream_t st) {
+static hipError_t launch_generic(const AmpArgs& A, int U, int grid, LaunchOn st) {
     GenericEval64<EVEN> ev{A.tab64, A.gdeg, A.gK, A.gstride};
     switch (U) {
         case 1: return launch_one<DefaultShape<1>>(A, ev, grid, st);
@@ -174,7 +174,7 @@ static hipError_t launch_generic(const AmpArgs& A, int U, int grid, hipStream_t 
     }
 }
 
-static hipError_t launch_tanh(const AmpArgs& A, int U, int grid, hipStream_t st) {
+static hipError_t launch_tanh(const AmpArgs& A, int U, int grid, LaunchOn st) {
     TanhEval64 ev{A.tab64, A.gdeg, A.gK, A.gstride, A.alpha};
     switch (U) {
         case 1: return launch_one<DefaultShape<1>>(A, ev, grid, st);
@@ -186,7 +186,7 @@ static hipError_t launch_tanh(const AmpArgs& A, int U, int grid, hipStream_t st)
 }
 
 
-hipError_t launch_amplitude(const AmpArgs& A, EvalKind kind, int p, int U, int grid, hipStream_t st) {
+hipError_t launch_amplitude(const AmpArgs& A, EvalKind kind, int p, int U, int grid, LaunchOn st) {
     switch (kind) {
         case EvalKind::Quartic64: return launch_quartic64(A, p, U, grid, st);
         case EvalKind::Quartic32: return launch_quartic32(A, p, U, grid, st);

@@ -9,7 +9,7 @@ namespace pimc {
 namespace {
 
 template <int P>
-hipError_t launch_p(const AmpArgs& A, int p, int U, int grid, hipStream_t st) {
+hipError_t launch_p(const AmpArgs& A, int p, int U, int grid, LaunchOn st) {
     if constexpr (P <= kMaxP) {
         if (p != P) return launch_p<P + 1>(A, p, U, grid, st);
         const QuarticEval32<P> ev{A.tab32};
@@ -34,7 +34,7 @@ int resident_p(int p, int U, size_t lds, int device) {
 
 }  // namespace
 
-hipError_t launch_quartic32(const AmpArgs& A, int p, int U, int grid, hipStream_t st) {
+hipError_t launch_quartic32(const AmpArgs& A, int p, int U, int grid, LaunchOn st) {
     return launch_p<1>(A, p, U, grid, st);
 }
 

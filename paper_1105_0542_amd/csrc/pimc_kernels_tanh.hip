@@ -9,7 +9,7 @@ namespace pimc {
 namespace {
 
 template <int P>
-hipError_t launch_p(const AmpArgs& A, int p, int grid, hipStream_t st) {
+hipError_t launch_p(const AmpArgs& A, int p, int grid, LaunchOn st) {
     if constexpr (P <= kMaxP) {
         if (p != P) return launch_p<P + 1>(A, p, grid, st);
         const TanhEvalP<P> ev{A.tab64, A.alpha};
@@ -31,7 +31,7 @@ int resident_p(int p, size_t lds, int device) {
 
 }  // namespace
 
-hipError_t launch_tanh_fixed(const AmpArgs& A, int p, int grid, hipStream_t st) { return launch_p<1>(A, p, grid, st); }
+hipError_t launch_tanh_fixed(const AmpArgs& A, int p, int grid, LaunchOn st) { return launch_p<1>(A, p, grid, st); }
 
 int resident_tanh_fixed(int p, size_t lds_bytes, int device) { return resident_p<1>(p, lds_bytes, device); }
 

@@ -19,8 +19,7 @@ namespace {
 // Layout of the workspace: parameter block, segment list (base, length per level), reduced sums
 // (4 doubles per level), then the chunk sums.
 constexpr size_t kPrmBytes = size_t(256) << 10;
-constexpr size_t kSegBytes = size_t(PIMC_MAX_S + 1) * 2 * 8;
-constexpr size_t kRedBytes = size_t(PIMC_MAX_S + 1) * 4 * 8;
+constexpr size_t kSegBytes = size_t(PIMC_MAX_S + 1) * sizeof(pimc::GroupSegment);
 constexpr size_t kSegOff = kPrmBytes;
 constexpr size_t kRedOff = (kSegOff + kSegBytes + 255) & ~size_t(255);
 constexpr size_t kPartOff = (kRedOff + kRedBytes + 255) & ~size_t(255);

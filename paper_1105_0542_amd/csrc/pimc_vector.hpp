@@ -133,25 +133,25 @@ constexpr int kPolyMaxSlots = 1 << 20;  // coefficient slots per level
 // Launch the vector estimation kernel: dim 1..4; U = min(s, kVecU); `specialized` selects the
 // evaluator with the compile-time shape of level p (dim 2 or 3, U = kVecU), else the evaluator
 // that reads the shape array. hipErrorInvalidValue for an unsupported combination.
-hipError_t launch_vector(const VecArgs& A, int dim, int p, int U, bool specialized, int grid, hipStream_t st);
+hipError_t launch_vector(const VecArgs& A, int dim, int p, int U, bool specialized, int grid, LaunchOn st);
 int vector_resident_blocks(int dim, int p, int U, bool specialized, size_t lds_bytes, int device);
 
 // The component evaluator: A.tab = coefficients, A.shape = structure stream.
-hipError_t launch_vector_poly(const VecArgs& A, int dim, int U, int grid, hipStream_t st);
+hipError_t launch_vector_poly(const VecArgs& A, int dim, int U, int grid, LaunchOn st);
 int vector_poly_resident(int dim, int U, size_t lds_bytes, int device);
 
 // Per-dimension halves (one translation unit each).
-hipError_t launch_vector_d1(const VecArgs& A, int p, int U, bool specialized, int grid, hipStream_t st);
-hipError_t launch_vector_d2(const VecArgs& A, int p, int U, bool specialized, int grid, hipStream_t st);
-hipError_t launch_vector_d3(const VecArgs& A, int p, int U, bool specialized, int grid, hipStream_t st);
+hipError_t launch_vector_d1(const VecArgs& A, int p, int U, bool specialized, int grid, LaunchOn st);
+hipError_t launch_vector_d2(const VecArgs& A, int p, int U, bool specialized, int grid, LaunchOn st);
+hipError_t launch_vector_d3(const VecArgs& A, int p, int U, bool specialized, int grid, LaunchOn st);
 int vector_resident_d1(int p, int U, bool specialized, size_t lds, int device);
 int vector_resident_d2(int p, int U, bool specialized, size_t lds, int device);
 int vector_resident_d3(int p, int U, bool specialized, size_t lds, int device);
-hipError_t launch_vector_d4(const VecArgs& A, int p, int U, bool specialized, int grid, hipStream_t st);
+hipError_t launch_vector_d4(const VecArgs& A, int p, int U, bool specialized, int grid, LaunchOn st);
 int vector_resident_d4(int p, int U, bool specialized, size_t lds, int device);
 // The component evaluator's kernels, one translation unit per dimension (pimc_vector_poly.hip).
 template <int DIM>
-hipError_t launch_vector_poly_dim(const VecArgs& A, int U, int grid, hipStream_t st);
+hipError_t launch_vector_poly_dim(const VecArgs& A, int U, int grid, LaunchOn st);
 template <int DIM>
 int vector_poly_resident_dim(int U, size_t lds, int device);
 // Subtrees of kPolySplitU levels or more (the deepest, poly_subtree_levels(DIM)) are compiled in a
@@ -159,7 +159,7 @@ int vector_poly_resident_dim(int U, size_t lds, int device);
 // parallel with the shallower ones; launch_vector_poly_dim forwards to them.
 constexpr int kPolySplitU = 7;
 template <int DIM>
-hipError_t launch_vector_poly_deep(const VecArgs& A, int grid, hipStream_t st);
+hipError_t launch_vector_poly_deep(const VecArgs& A, int grid, LaunchOn st);
 template <int DIM>
 int vector_poly_resident_deep(size_t lds, int device);
 

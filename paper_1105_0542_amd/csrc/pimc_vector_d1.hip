@@ -4,7 +4,7 @@
 
 namespace pimc {
 
-hipError_t launch_vector_d1(const VecArgs& A, int p, int U, bool specialized, int grid, hipStream_t st) {
+hipError_t launch_vector_d1(const VecArgs& A, int p, int U, bool specialized, int grid, LaunchOn st) {
     (void)p;
     if (specialized) return hipErrorInvalidValue;
     return vec::launch_rt<1>(A, U, grid, st);

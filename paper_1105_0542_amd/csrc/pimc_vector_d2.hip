@@ -4,7 +4,7 @@
 
 namespace pimc {
 
-hipError_t launch_vector_d2(const VecArgs& A, int p, int U, bool specialized, int grid, hipStream_t st) {
+hipError_t launch_vector_d2(const VecArgs& A, int p, int U, bool specialized, int grid, LaunchOn st) {
     if (specialized) {
         if (U != kVecU) return hipErrorInvalidValue;
         return vec::launch_spec<2, 1>(A, p, grid, st);

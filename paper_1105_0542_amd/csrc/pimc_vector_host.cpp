@@ -349,7 +349,8 @@ int build_vector_problem(const pimc_radial_potential* V, double m, const double*
     return PIMC_OK;
 }
 
-int stage_vector(pimc_ctx* c, const VecProblem& P, uint64_t seed, uint32_t stream, VecArgs& A) {
+int stage_vector(pimc_ctx* c, const VecProblem& P, uint64_t seed, uint32_t stream, VecArgs& A,
+                 const std::vector<unsigned char>& segs, const void** segs_dev) {
     const size_t nlev = size_t(P.s + 1);
     const size_t n_tab = P.tab_dev.size();
     const size_t off_shift = nlev * 8;
@@ -357,16 +358,22 @@ int stage_vector(pimc_ctx* c, const VecProblem& P, uint64_t seed, uint32_t strea
     const size_t off_shape = off_tab + n_tab * 8;
     // the two work counters of the persistent kernel, zero, on a 256-byte line of their own
     const size_t off_queue = (off_shape + P.shape.size() * 4 + 255) & ~size_t(255);
-    const size_t total = off_queue + 256;
-    std::vector<unsigned char> host(total, 0);
-    std::memcpy(host.data(), P.sig.data(), nlev * 8);
-    std::memcpy(host.data() + off_shift, P.shift.data(), nlev * 8);
-    std::memcpy(host.data() + off_tab, P.tab_dev.data(), n_tab * 8);
-    std::memcpy(host.data() + off_shape, P.shape.data(), P.shape.size() * 4);
-    int st = ensure(c, &c->d_prm, &c->prm_bytes, total);
+    const size_t off_segs = off_queue + 256;
+    const size_t total = off_segs + segs.size();
+    unsigned char* host = nullptr;
+    int st = pinned_stage(c, total, &host);
     if (st) return st;
-    HIP_TRY(c, hipMemcpyAsync(c->d_prm, host.data(), total, hipMemcpyHostToDevice, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));     // the host vector must outlive the copy
+    std::memset(host, 0, total);
+    std::memcpy(host, P.sig.data(), nlev * 8);
+    std::memcpy(host + off_shift, P.shift.data(), nlev * 8);
+    std::memcpy(host + off_tab, P.tab_dev.data(), n_tab * 8);
+    std::memcpy(host + off_shape, P.shape.data(), P.shape.size() * 4);
+    if (!segs.empty()) std::memcpy(host + off_segs, segs.data(), segs.size());
+    st = ensure(c, &c->d_prm, &c->prm_bytes, total);
+    if (st) return st;
+    c->stage_busy = true;
+    HIP_TRY(c, hipMemcpyAsync(c->d_prm, host, total, hipMemcpyHostToDevice, c->stream));
+    *segs_dev = static_cast<unsigned char*>(c->d_prm) + off_segs;
     unsigned char* base = static_cast<unsigned char*>(c->d_prm);
     std::memset(&A, 0, sizeof(A));
     A.sig = reinterpret_cast<const double*>(base);
@@ -419,46 +426,36 @@ int vector_amplitude_core(pimc_ctx* c, const VecProblem& P, uint64_t n_samples, 
     if (P.s == 0) return PIMC_OK;
     int st = check_lds(c, P);
     if (st) return st;
-    VecArgs A;
-    st = stage_vector(c, P, seed, stream, A);
-    if (st) return st;
     const uint64_t chunk_paths = kChunkPaths;
     const uint64_t n_chunks = (n_samples + chunk_paths - 1) / chunk_paths;
     const int slots = hier ? nlev : 1;
     st = ensure(c, reinterpret_cast<void**>(&c->d_partials), &c->partial_bytes, size_t(slots) * n_chunks * 4 * 8);
     if (st) return st;
     const int resident = vector_resident(c, P);
-    unsigned long long* const queue = A.work.queue;
-    A.work = split_paths(n_samples, P.s, slots, kFineBytes, uint64_t(resident) * (kVecBlock / 64));
-    A.work.queue = queue;
-    st = ensure(c, reinterpret_cast<void**>(&c->d_gsum), &c->gsum_bytes, group_sum_bytes(A.work, slots));
+    PathWork pw = split_paths(n_samples, P.s, slots, kFineBytes, uint64_t(resident) * (kVecBlock / 64));
+    st = ensure(c, reinterpret_cast<void**>(&c->d_gsum), &c->gsum_bytes, group_sum_bytes(pw, slots));
     if (st) return st;
-    A.work.gsum = c->d_gsum;
-    st = ensure(c, reinterpret_cast<void**>(&c->d_red), &c->red_bytes, size_t(slots) * 4 * 8);
+    pw.gsum = c->d_gsum;
+    VecArgs A;
+    const void* segs = nullptr;
+    st = stage_vector(c, P, seed, stream, A, run_segments(pw, slots, n_samples, c->d_partials), &segs);
     if (st) return st;
-    st = ensure(c, reinterpret_cast<void**>(&c->d_seg), &c->seg_bytes, size_t(slots) * 2 * 8);
-    if (st) return st;
-    c->h_seg.assign(size_t(slots) * 2, 0);
-    for (int k = 0; k < slots; ++k) {
-        c->h_seg[size_t(k)] = uint64_t(k) * n_chunks * 4;
-        c->h_seg[size_t(slots + k)] = n_chunks;
-    }
-    HIP_TRY(c, hipMemcpyAsync(c->d_seg, c->h_seg.data(), c->h_seg.size() * 8, hipMemcpyHostToDevice, c->stream));
+    pw.queue = A.work.queue;
+    A.work = pw;
     A.first_path = 0;
     A.n_paths = n_samples;
     A.hier = hier ? 1 : 0;
     A.partials = c->d_partials;
     A.dump = nullptr;
     const int grid = work_grid(A.work, kVecBlock / 64, resident);
-    HIP_TRY(c, hipEventRecord(c->ev0, c->stream));
-    HIP_TRY(c, P.poly ? launch_vector_poly(A, P.dim, P.U, grid, c->stream)
-                      : launch_vector(A, P.dim, P.p, P.U, P.specialized, grid, c->stream));
-    HIP_TRY(c, hipEventRecord(c->ev1, c->stream));
-    HIP_TRY(c, launch_group_chunks(A.work, slots, n_samples, c->d_partials, c->stream));
-    HIP_TRY(c, launch_seg_reduce(c->d_partials, c->d_seg, c->d_seg + slots, uint64_t(slots), c->d_red, c->stream));
-    std::vector<double> red(size_t(slots) * 4);
-    HIP_TRY(c, hipMemcpyAsync(red.data(), c->d_red, red.size() * 8, hipMemcpyDeviceToHost, c->stream));
+    const LaunchOn on(c->stream, c->ev0, c->ev1);
+    HIP_TRY(c, P.poly ? launch_vector_poly(A, P.dim, P.U, grid, on)
+                      : launch_vector(A, P.dim, P.p, P.U, P.specialized, grid, on));
+    // the last kernel writes the sums straight into pinned memory
+    double* const red = reinterpret_cast<double*>(c->h_stage);
+    HIP_TRY(c, launch_run_sums(A.work, slots, n_samples, c->d_partials, segs, red, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    c->stage_busy = false;
     float ms = 0.f;
     HIP_TRY(c, hipEventElapsedTime(&ms, c->ev0, c->ev1));
     c->last_ms = ms;
@@ -485,7 +482,8 @@ int vector_path_actions_core(pimc_ctx* c, const VecProblem& P, uint64_t seed, ui
     int st = check_lds(c, P);
     if (st) return st;
     VecArgs A;
-    st = stage_vector(c, P, seed, stream, A);
+    const void* segs = nullptr;
+    st = stage_vector(c, P, seed, stream, A, {}, &segs);
     if (st) return st;
     st = ensure(c, reinterpret_cast<void**>(&c->d_dump), &c->dump_bytes, size_t(k_paths) * nlev * 8);
     if (st) return st;
@@ -882,7 +880,7 @@ int build_poly_problem(const pimc_poly_potential* V, double m, const double* a, 
 
 namespace pimc {
 
-hipError_t launch_vector(const VecArgs& A, int dim, int p, int U, bool specialized, int grid, hipStream_t st) {
+hipError_t launch_vector(const VecArgs& A, int dim, int p, int U, bool specialized, int grid, LaunchOn st) {
     switch (dim) {
         case 1: return launch_vector_d1(A, p, U, specialized, grid, st);
         case 2: return launch_vector_d2(A, p, U, specialized, grid, st);
@@ -892,7 +890,7 @@ hipError_t launch_vector(const VecArgs& A, int dim, int p, int U, bool specializ
     }
 }
 
-hipError_t launch_vector_poly(const VecArgs& A, int dim, int U, int grid, hipStream_t st) {
+hipError_t launch_vector_poly(const VecArgs& A, int dim, int U, int grid, LaunchOn st) {
     switch (dim) {
         case 1: return launch_vector_poly_dim<1>(A, U, grid, st);
         case 2: return launch_vector_poly_dim<2>(A, U, grid, st);

@@ -507,9 +507,9 @@ k_amplitude_vec(VecArgs A, Eval ev) {
 
 // ---------------------------------------------------------------------------- dispatch
 template <int DIM, int U, class Eval>
-inline hipError_t launch_one(const VecArgs& A, const Eval& ev, int grid, hipStream_t st) {
+inline hipError_t launch_one(const VecArgs& A, const Eval& ev, int grid, LaunchOn st) {
     const size_t lds = vec_lds_bytes(DIM, A.D, A.s);
-    hipLaunchKernelGGL((k_amplitude_vec<DIM, U, Eval>), dim3(grid), dim3(kVecBlock), lds, st, A, ev);
+    hipExtLaunchKernelGGL((k_amplitude_vec<DIM, U, Eval>), dim3(grid), dim3(kVecBlock), lds, st.st, st.start, st.stop, 0, A, ev);
     return hipGetLastError();
 }
 
@@ -524,7 +524,7 @@ inline int resident_one(size_t lds, int device) {
 }
 
 template <int DIM>
-inline hipError_t launch_rt(const VecArgs& A, int U, int grid, hipStream_t st) {
+inline hipError_t launch_rt(const VecArgs& A, int U, int grid, LaunchOn st) {
     const RadialEvalRT<DIM> ev{A.tab, A.shape, A.stride};
     switch (U) {
         case 1: return launch_one<DIM, 1>(A, ev, grid, st);
@@ -548,7 +548,7 @@ inline int resident_rt(int U, size_t lds, int device) {
 // UMAX: the deepest subtree instantiated by the caller's translation unit (the deepest of all may be
 // compiled in a unit of its own).
 template <int DIM, int UMAX = poly_subtree_levels(DIM)>
-inline hipError_t launch_poly(const VecArgs& A, int U, int grid, hipStream_t st) {
+inline hipError_t launch_poly(const VecArgs& A, int U, int grid, LaunchOn st) {
     const PolyEvalRT<DIM> ev{A.tab, A.shape, A.stride};
     switch (U) {
         case 1: return launch_one<DIM, 1>(A, ev, grid, st);
@@ -578,7 +578,7 @@ inline int resident_poly(int U, size_t lds, int device) {
 }
 
 template <int DIM, int P>
-inline hipError_t launch_spec(const VecArgs& A, int p, int grid, hipStream_t st) {
+inline hipError_t launch_spec(const VecArgs& A, int p, int grid, LaunchOn st) {
     if constexpr (P <= kMaxP) {
         if (p != P) return launch_spec<DIM, P + 1>(A, p, grid, st);
         const RadialEval<P, DIM> ev{A.tab};

@@ -20,7 +20,7 @@ constexpr bool kSplit = kUDeep >= kPolySplitU;
 #if PIMC_POLY_DEEP
 
 template <>
-hipError_t launch_vector_poly_deep<PIMC_POLY_DIM>(const VecArgs& A, int grid, hipStream_t st) {
+hipError_t launch_vector_poly_deep<PIMC_POLY_DIM>(const VecArgs& A, int grid, LaunchOn st) {
     if constexpr (kSplit) {
         const vec::PolyEvalRT<PIMC_POLY_DIM> ev{A.tab, A.shape, A.stride};
         return vec::launch_one<PIMC_POLY_DIM, kUDeep>(A, ev, grid, st);
@@ -40,7 +40,7 @@ int vector_poly_resident_deep<PIMC_POLY_DIM>(size_t lds, int device) {
 constexpr int kUShallow = kSplit ? kPolySplitU - 1 : kUDeep;
 
 template <>
-hipError_t launch_vector_poly_dim<PIMC_POLY_DIM>(const VecArgs& A, int U, int grid, hipStream_t st) {
+hipError_t launch_vector_poly_dim<PIMC_POLY_DIM>(const VecArgs& A, int U, int grid, LaunchOn st) {
     if constexpr (kSplit)
         if (U == kUDeep) return launch_vector_poly_deep<PIMC_POLY_DIM>(A, grid, st);
     return vec::launch_poly<PIMC_POLY_DIM, kUShallow>(A, U, grid, st);

@@ -198,9 +198,9 @@ k_amplitude(AmpArgs A, Eval ev) {
 }
 
 template <class S, class Eval>
-inline hipError_t launch_one(const AmpArgs& A, const Eval& ev, int grid, hipStream_t st) {
+inline hipError_t launch_one(const AmpArgs& A, const Eval& ev, int grid, LaunchOn st) {
     const size_t lds = amp_lds_bytes(A.D, A.s, S::BS);
-    hipLaunchKernelGGL((k_amplitude<S, Eval>), dim3(grid), dim3(S::BS), lds, st, A, ev);
+    hipExtLaunchKernelGGL((k_amplitude<S, Eval>), dim3(grid), dim3(S::BS), lds, st.st, st.start, st.stop, 0, A, ev);
     return hipGetLastError();
 }
 
