@@ -151,4 +151,29 @@ __device__ __forceinline__ void run_groups(const PathWork& w, int nlev, int hier
     }
 }
 
+// Reference actions on the device, for the evaluators whose slice costs too much on the host (24,196
+// monomials at p = 18 of the general mode: 14 ms of host time at N = 64, 230 ms at N = 1024). Level n
+// (blockIdx.x + 1) of the straight line from a to b: block y takes the y-th part of its 2^n slices, and
+// the parts are added by k_line_sum. slice(level, k, N) is one slice's action. Parts and orders depend
+// on n alone, so level n of an s-run has the reference of the n-run.
+__host__ __device__ inline int line_parts(int n) { return n <= 8 ? 1 : (n >= 14 ? kLineParts : 1 << (n - 8)); }
+
+template <class Slice>
+__device__ __forceinline__ void line_part(double* __restrict__ parts, Slice slice) {
+    const int n = int(blockIdx.x) + 1;
+    const int np = line_parts(n);
+    if (int(blockIdx.y) >= np) return;
+    const int N = 1 << n, per = N / np;
+    double S = 0.0;
+    for (int i = threadIdx.x; i < per; i += kBlock) S += slice(n, int(blockIdx.y) * per + i, N);
+    __shared__ double red[kBlock];
+    red[threadIdx.x] = S;
+    __syncthreads();
+    for (int w = kBlock / 2; w >= 1; w >>= 1) {
+        if (int(threadIdx.x) < w) red[threadIdx.x] += red[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) parts[n * kLineParts + int(blockIdx.y)] = red[0];
+}
+
 }  // namespace pimc

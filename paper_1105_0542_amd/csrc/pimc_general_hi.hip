@@ -44,6 +44,11 @@ int gen_hi_resident<PIMC_GEN_P>(int U, size_t lds_bytes, int device) {
 }
 
 template <>
+hipError_t gen_hi_line<PIMC_GEN_P>(const AmpArgs& A, double* parts, hipStream_t st) {
+    return launch_line(A, GenSliceEval<PIMC_GEN_P>{A.tab64, A.gen}, parts, st);
+}
+
+template <>
 int gen_hi_nrec<PIMC_GEN_P>() {
     return GenCompiled<PIMC_GEN_P>::NREC;
 }

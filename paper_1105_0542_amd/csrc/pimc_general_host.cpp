@@ -44,18 +44,6 @@ const LevelMonomials& cached_monomials(int p) {
     return *it->second;
 }
 
-double straight_line_general(const GenPotential& G, const std::vector<GenMono>& M, const double* scales, double a,
-                             double b, int n) {
-    const int N = 1 << n;
-    double acc = 0.0;
-    for (int k = 0; k < N; ++k) {
-        const double q0 = a + (b - a) * double(k) / double(N);
-        const double q1 = a + (b - a) * double(k + 1) / double(N);
-        acc += gen_eval_slice(G, M, scales, q0, q1);
-    }
-    return acc;
-}
-
 }  // namespace
 
 namespace pimc_host {
@@ -151,9 +139,8 @@ int build_problem_general(const pimc_general_potential* V, double m, double a, d
     P.sig.assign(size_t(P.s + 1), 0.0);
     for (int n = 1; n <= P.s; ++n) P.sig[size_t(n)] = std::sqrt(T / std::ldexp(1.0, n + 1));
     P.shift.assign(size_t(P.s + 1), 0.0);
-    for (int n = 0; n <= P.s; ++n)
-        P.shift[size_t(n)] =
-            straight_line_general(G, L.M, P.tab.data() + size_t(n) * size_t(stride), P.a, P.b, n);
+    // level 0 here, the references of the other levels on the device (launch_line_general)
+    P.shift[0] = gen_eval_slice(G, L.M, P.tab.data(), P.a, P.b);
     P.level0_action = P.shift[0];
     return PIMC_OK;
 }

@@ -54,7 +54,31 @@ int nrec_p(int p) {
     }
 }
 
+template <int P>
+hipError_t line_p(const AmpArgs& A, int p, double* parts, hipStream_t st) {
+    if constexpr (P <= kGenInlineMaxP) {
+        if (p != P) return line_p<P + 1>(A, p, parts, st);
+        return launch_line(A, GenCompiledEval<P>{A.tab64, A.gen}, parts, st);
+    } else {
+        return hipErrorInvalidValue;
+    }
+}
+
 }  // namespace
+
+hipError_t launch_line_general(const AmpArgs& A, int p, double* parts, hipStream_t st) {
+    switch (p) {
+        case 11: return gen_hi_line<11>(A, parts, st);
+        case 12: return gen_hi_line<12>(A, parts, st);
+        case 13: return gen_hi_line<13>(A, parts, st);
+        case 14: return gen_hi_line<14>(A, parts, st);
+        case 15: return gen_hi_line<15>(A, parts, st);
+        case 16: return gen_hi_line<16>(A, parts, st);
+        case 17: return gen_hi_line<17>(A, parts, st);
+        case 18: return gen_hi_line<18>(A, parts, st);
+        default: return line_p<1>(A, p, parts, st);
+    }
+}
 
 static_assert(kGenInlineMaxP == 10 && kGenMaxP == 18, "the out-of-line levels 11..18 are declared in pimc_internal.hpp");
 

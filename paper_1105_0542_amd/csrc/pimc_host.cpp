@@ -154,18 +154,6 @@ double free_kernel(double a, double b, double T) {
     return std::exp(-(b - a) * (b - a) / (2.0 * T)) / std::sqrt(2.0 * M_PI * T);
 }
 
-// Potential part of eq.(SNp) on the straight line from a to b at level n (2^n slices).
-double straight_line_action(const LevelTable& lt, double a, double b, int n) {
-    const int M = 1 << n;
-    double acc = 0.0;
-    for (int k = 0; k < M; ++k) {
-        const double q0 = a + (b - a) * double(k) / double(M);
-        const double q1 = a + (b - a) * double(k + 1) / double(M);
-        acc += eval_level(lt, q0, q1);
-    }
-    return acc;
-}
-
 // Amplitude, error and diagnostics of one level from its canonical sums red = (n, sum d, sum d^2,
 // non-finite count), with log of the prefactor K_0 sqrt(m) e^{-S_ref}. Returns true when the
 // result is not finite.
@@ -335,7 +323,8 @@ int check_mpt(const pimc_mpt* V, double m, double a, double b, double T, uint32_
 // by way of its pinned one and without waiting, or into the workspace); fill the kernel arguments except
 // the output pointers. *segs_dev: where the segments are.
 int stage_problem(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t stream, AmpArgs& A,
-                  const std::vector<unsigned char>& segs, const void** segs_dev, const DeviceWork* work = nullptr) {
+                  const std::vector<unsigned char>& segs, const void** segs_dev, double** line_dev,
+                  const DeviceWork* work = nullptr) {
     const size_t nlev = size_t(P.s + 1);
     const size_t n_tab = P.tab.size();
     // layout: sig[nlev] shift[nlev] tab64[n_tab] tab32[n_tab] deg[K]
@@ -350,6 +339,9 @@ int stage_problem(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t stream,
     const size_t off_queue = (off_dsech + P.gen.dsech.size() * 8 + 255) & ~size_t(255);
     const size_t off_segs = off_queue + 256;
     const size_t total = off_segs + (work ? 0 : segs.size());
+    // general-potential mode: the partial sums of the reference actions, on the device only
+    const size_t off_line = (total + 15) & ~size_t(15);
+    const size_t need = off_line + (P.kind == EvalKind::General64 ? nlev * kLineParts * 8 : 0);
     std::vector<unsigned char> heap(work ? total : 0);
     unsigned char* host = heap.data();
     if (!work) {
@@ -373,7 +365,7 @@ int stage_problem(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t stream,
             return ctx_fail(c, PIMC_EINVAL, "tables need %zu bytes, the workspace holds %zu", total, work->prm_cap);
         prm = work->prm;
     } else {
-        const int st = ensure(c, &c->d_prm, &c->prm_bytes, total);
+        const int st = ensure(c, &c->d_prm, &c->prm_bytes, need);
         if (st) return st;
         prm = c->d_prm;
     }
@@ -386,6 +378,7 @@ int stage_problem(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t stream,
     }
     unsigned char* base = static_cast<unsigned char*>(prm);
     *segs_dev = work ? static_cast<const void*>(work->seg) : base + off_segs;
+    *line_dev = reinterpret_cast<double*>(base + off_line);
     std::memset(&A, 0, sizeof(A));
     A.sig = reinterpret_cast<const double*>(base);
     A.shift = reinterpret_cast<const double*>(base + off_shift);
@@ -492,7 +485,8 @@ int amplitude_core(pimc_ctx* c, const Problem& P, uint64_t n_samples, uint64_t s
     }
     AmpArgs A;
     const void* segs = nullptr;
-    st = stage_problem(c, P, seed, stream, A, run_segments(pw, slots, n_samples, partials), &segs, work);
+    double* line = nullptr;
+    st = stage_problem(c, P, seed, stream, A, run_segments(pw, slots, n_samples, partials), &segs, &line, work);
     if (st) return st;
     // the last kernel writes the sums straight into pinned memory (the workspace's are copied)
     double* const red_out = work ? work->red : reinterpret_cast<double*>(c->h_stage);
@@ -504,6 +498,12 @@ int amplitude_core(pimc_ctx* c, const Problem& P, uint64_t n_samples, uint64_t s
     A.partials = partials;
     A.dump = nullptr;
     const int grid = work_grid(A.work, kBlock / 64, resident);
+    const bool line_on_device = P.kind == EvalKind::General64;      // never with `work`: that entry point takes polynomials
+    double* const line_host = line_on_device ? red_out + size_t(PIMC_MAX_S + 1) * 4 : nullptr;
+    if (line_on_device) {
+        HIP_TRY(c, launch_line_general(A, P.p, line, c->stream));
+        HIP_TRY(c, launch_line_sum(line, P.s, const_cast<double*>(A.shift), line_host, c->stream));
+    }
     HIP_TRY(c, launch_amplitude(A, P.kind, P.p, P.U, grid, LaunchOn(c->stream, c->ev0, c->ev1)));
     HIP_TRY(c, launch_run_sums(A.work, slots, n_samples, partials, segs, red_out, c->stream));
     double red_copy[4 * (PIMC_MAX_S + 1)];
@@ -511,6 +511,7 @@ int amplitude_core(pimc_ctx* c, const Problem& P, uint64_t n_samples, uint64_t s
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     c->stage_busy = false;
     const double* red = work ? red_copy : red_out;
+    if (line_on_device) std::copy(line_host + 1, line_host + nlev, c->last_shift.begin() + 1);
     float ms = 0.f;
     HIP_TRY(c, hipEventElapsedTime(&ms, c->ev0, c->ev1));
     c->last_ms = ms;
@@ -522,7 +523,7 @@ int amplitude_core(pimc_ctx* c, const Problem& P, uint64_t n_samples, uint64_t s
     for (int n = 1; n < nlev; ++n) {
         if (!hier && n != P.s) continue;
         const size_t k = size_t(hier ? n : 0);
-        if (assemble_level(&red[k * 4], std::log(P.pref * P.K0) - P.shift[size_t(n)], out[n])) nonfinite = true;
+        if (assemble_level(&red[k * 4], std::log(P.pref * P.K0) - c->last_shift[size_t(n)], out[n])) nonfinite = true;
     }
     return nonfinite ? PIMC_WNONFINITE : PIMC_OK;
 }
@@ -539,7 +540,8 @@ int path_actions_core(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t str
     }
     AmpArgs A;
     const void* segs = nullptr;
-    st = stage_problem(c, P, seed, stream, A, {}, &segs);
+    double* line = nullptr;
+    st = stage_problem(c, P, seed, stream, A, {}, &segs, &line);
     if (st) return st;
     st = ensure(c, reinterpret_cast<void**>(&c->d_dump), &c->dump_bytes, size_t(k_paths) * nlev * 8);
     if (st) return st;

@@ -23,7 +23,7 @@ struct pimc_ctx {
     double* d_red = nullptr;        size_t red_bytes = 0;
     uint64_t* d_seg = nullptr;      size_t seg_bytes = 0;
     std::vector<uint64_t> h_seg;    // segment base/len of the last proposal reduction (kept alive for the async copy)
-    // pinned: the reduced sums of a run (kRedBytes, written by its last kernel), then what it uploads
+    // pinned: the reduced sums and reference actions of a run (kRedBytes, written by its kernels), then what it uploads
     unsigned char* h_stage = nullptr;  size_t stage_bytes = 0;
     bool stage_busy = false;        // a copy out of it may still be under way
     double* d_dump = nullptr;       size_t dump_bytes = 0;
@@ -48,9 +48,9 @@ int ctx_fail(pimc_ctx* c, int status, const char* fmt, ...);
 // Grow a device buffer to at least need bytes (contents are not kept).
 int ensure(pimc_ctx* c, void** buf, size_t* have, size_t need);
 
-// The context's pinned buffer, with room for the sums of a run and for `need` bytes to upload (at
+// The context's pinned buffer, with room for the sums of a run and its reference actions and for `need` bytes to upload (at
 // *out); free for writing when this returns.
-constexpr size_t kRedBytes = size_t(PIMC_MAX_S + 1) * 4 * 8;
+constexpr size_t kRedBytes = size_t(PIMC_MAX_S + 1) * 5 * 8;   // four sums and the reference action per level
 int pinned_stage(pimc_ctx* c, size_t need, unsigned char** out);
 // What the reduction of a run reads on the device (GroupSegment per slot for a short run, else base and
 // length per slot), and its launch: chunk records from the fine groups' sums, then out[slot][4].

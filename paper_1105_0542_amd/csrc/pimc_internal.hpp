@@ -154,13 +154,17 @@ template <int P>
 int gen_hi_resident(int U, size_t lds_bytes, int device);
 template <int P>
 int gen_hi_nrec();
+template <int P>
+hipError_t gen_hi_line(const AmpArgs& A, double* parts, hipStream_t st);
 #define PIMC_GEN_HI_DECLARE(P)                                                         \
     template <>                                                                         \
     hipError_t gen_hi_launch<P>(const AmpArgs& A, int U, int grid, LaunchOn st);    \
     template <>                                                                         \
     int gen_hi_resident<P>(int U, size_t lds_bytes, int device);                        \
     template <>                                                                         \
-    int gen_hi_nrec<P>();
+    int gen_hi_nrec<P>();                                                               \
+    template <>                                                                         \
+    hipError_t gen_hi_line<P>(const AmpArgs& A, double* parts, hipStream_t st);
 PIMC_GEN_HI_DECLARE(11)
 PIMC_GEN_HI_DECLARE(12)
 PIMC_GEN_HI_DECLARE(13)
@@ -174,6 +178,12 @@ PIMC_GEN_HI_DECLARE(18)
 // Raw standard normals of heap nodes 1..n_nodes for k_paths paths: out[path][node-1] (device).
 hipError_t launch_normals(const RngKey& key, uint64_t first_path, uint64_t k_paths, uint32_t n_nodes, double* out,
                           hipStream_t st);
+
+// Straight-line reference actions formed on the device (pimc_chunks.hpp): at most kLineParts partial sums
+// per level, `parts` [s+1][kLineParts]; then level n's action, n = 1..s, into shift[n] and shift_host[n].
+constexpr int kLineParts = 64;
+hipError_t launch_line_sum(const double* parts, int s, double* shift, double* shift_host, hipStream_t st);
+hipError_t launch_line_general(const AmpArgs& A, int p, double* parts, hipStream_t st);
 
 // Adds the group sums of a run's fine chunks into their chunk records, each chunk in the canonical
 // order (group g to slot g mod kChunkSlots in increasing g, then the slots in order).

@@ -209,6 +209,23 @@ hipError_t launch_seg_reduce(const double* partials, const uint64_t* base, const
     return hipGetLastError();
 }
 
+// Level n = blockIdx.x + 1: its parts added by a wave butterfly.
+__global__ void __launch_bounds__(64) k_line_sum(const double* __restrict__ parts, double* shift, double* shift_host) {
+    const int n = int(blockIdx.x) + 1;
+    const double S = wave_sum(int(threadIdx.x) < line_parts(n) ? parts[n * kLineParts + int(threadIdx.x)] : 0.0);
+    if (threadIdx.x == 0) {
+        shift[n] = S;
+        shift_host[n] = S;
+    }
+}
+
+hipError_t launch_line_sum(const double* parts, int s, double* shift, double* shift_host, hipStream_t st) {
+    static_assert(kLineParts == 64, "one lane per part");
+    if (s < 1) return hipSuccess;
+    hipLaunchKernelGGL(k_line_sum, dim3(s), dim3(64), 0, st, parts, shift, shift_host);
+    return hipGetLastError();
+}
+
 hipError_t launch_fill_u64(unsigned long long* p, int n, unsigned long long v, hipStream_t st) {
     hipLaunchKernelGGL(k_fill_u64, dim3((n + 63) / 64), dim3(64), 0, st, p, n, v);
     return hipGetLastError();

@@ -21,8 +21,9 @@ namespace {
 constexpr size_t kPrmBytes = size_t(256) << 10;
 constexpr size_t kSegBytes = size_t(PIMC_MAX_S + 1) * sizeof(pimc::GroupSegment);
 constexpr size_t kSegOff = kPrmBytes;
+constexpr size_t kSumBytes = size_t(PIMC_MAX_S + 1) * 4 * 8;
 constexpr size_t kRedOff = (kSegOff + kSegBytes + 255) & ~size_t(255);
-constexpr size_t kPartOff = (kRedOff + kRedBytes + 255) & ~size_t(255);
+constexpr size_t kPartOff = (kRedOff + kSumBytes + 255) & ~size_t(255);
 static_assert(kPartOff < PIMC_NOALLOC_BYTES, "workspace layout");
 
 static __device__ __align__(256) unsigned char scratch[PIMC_NOALLOC_BYTES];
@@ -85,7 +86,7 @@ int pimc_amplitude_noalloc(pimc_ctx* c, const pimc_potential* V, double m, doubl
     work.seg = reinterpret_cast<uint64_t*>(w + kSegOff);
     work.seg_cap = kSegBytes;
     work.red = reinterpret_cast<double*>(w + kRedOff);
-    work.red_cap = kRedBytes;
+    work.red_cap = kSumBytes;
     work.partials = reinterpret_cast<double*>(w + kPartOff);
     work.partial_cap = PIMC_NOALLOC_BYTES - kPartOff;
     return amplitude_core(c, P, n_samples, seed, stream, flags, out, &work);

@@ -206,26 +206,39 @@ inline std::vector<int> table_xdegrees(const Coefficients& C) {
     return xdeg;
 }
 
-// Horner evaluation of one folded table on the host (used for the straight-line reference action
-// and the analytic level-0 amplitude).
-inline double eval_level(const LevelTable& t, double qa, double qb) {
-    const double mid = 0.5 * (qa + qb);
-    const double dl = qb - qa;
-    double u;
-    if (t.tanh_alpha > 0.0) {
-        const double y = std::tanh(t.tanh_alpha * mid);
-        u = y * y;
-    } else {
-        u = t.even ? mid * mid : mid;
-    }
+// Potential part of eq.(SNp) on the straight line from a to b at this level (2^n slices): the reference
+// action, and at n = 0 the analytic level-0 exponent. The deviation is the same in every slice, so the
+// P_k are first added up with their powers of dlt^2; a slice is then one polynomial.
+inline double straight_line_action(const LevelTable& t, double a, double b, int n) {
+    const int N = 1 << n;
+    const double dl = (b - a) / double(N);
     const double z = dl * dl;
-    double acc = 0.0;
+    std::vector<double> R;                     // sum_k z^k P_k, by power of u
+    for (int d : t.deg) R.resize(std::max(R.size(), size_t(d) + 1), 0.0);
     size_t off = t.coef.size();
     for (int k = int(t.deg.size()) - 1; k >= 0; --k) {
         off -= size_t(t.deg[k]) + 1;
-        double v = t.coef[off];
-        for (int e = 1; e <= t.deg[k]; ++e) v = v * u + t.coef[off + e];
-        acc = (k == int(t.deg.size()) - 1) ? v : acc * z + v;
+        for (size_t e = 0; e < R.size(); ++e)
+            R[e] = R[e] * z + (e <= size_t(t.deg[k]) ? t.coef[off + size_t(t.deg[k]) - e] : 0.0);
+    }
+    constexpr int W = 8;                       // slices side by side: independent chains
+    double acc = 0.0;
+    for (int k0 = 0; k0 < N; k0 += W) {
+        double u[W], v[W];
+        for (int i = 0; i < W; ++i) {
+            const double q0 = a + (b - a) * double(k0 + i) / double(N);
+            const double q1 = a + (b - a) * double(k0 + i + 1) / double(N);
+            const double mid = 0.5 * (q0 + q1);
+            u[i] = t.even ? mid * mid : mid;
+            if (t.tanh_alpha > 0.0) {
+                const double y = k0 + i < N ? std::tanh(t.tanh_alpha * mid) : 0.0;
+                u[i] = y * y;
+            }
+            v[i] = 0.0;
+        }
+        for (size_t e = R.size(); e-- > 0;)
+            for (int i = 0; i < W; ++i) v[i] = v[i] * u[i] + R[e];
+        for (int i = 0; i < W && k0 + i < N; ++i) acc += v[i];
     }
     return acc;
 }

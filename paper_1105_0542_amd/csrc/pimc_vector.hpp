@@ -149,6 +149,10 @@ int vector_resident_d2(int p, int U, bool specialized, size_t lds, int device);
 int vector_resident_d3(int p, int U, bool specialized, size_t lds, int device);
 hipError_t launch_vector_d4(const VecArgs& A, int p, int U, bool specialized, int grid, LaunchOn st);
 int vector_resident_d4(int p, int U, bool specialized, size_t lds, int device);
+// Straight-line reference actions of the component evaluator (pimc_chunks.hpp).
+hipError_t launch_line_poly(const VecArgs& A, int dim, double* parts, hipStream_t st);
+template <int DIM>
+hipError_t launch_line_poly_dim(const VecArgs& A, double* parts, hipStream_t st);
 // The component evaluator's kernels, one translation unit per dimension (pimc_vector_poly.hip).
 template <int DIM>
 hipError_t launch_vector_poly_dim(const VecArgs& A, int U, int grid, LaunchOn st);

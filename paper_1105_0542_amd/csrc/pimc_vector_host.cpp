@@ -40,125 +40,165 @@ namespace {
 
 constexpr double kPi = 3.14159265358979323846;
 
-using IKey = std::array<int, 3>;                 // exponents of u, w, z
-using IPoly = std::map<IKey, double>;
-
-void axpy(IPoly& y, double a, const IPoly& x) {
-    for (const auto& kv : x) y[kv.first] += a * kv.second;
-}
-
-IPoly der(const IPoly& f, int var) {
-    IPoly out;
-    for (const auto& kv : f)
-        if (kv.first[size_t(var)]) {
-            IKey k = kv.first;
-            k[size_t(var)] -= 1;
-            out[k] += kv.second * double(kv.first[size_t(var)]);
-        }
-    return out;
-}
-
-IPoly times(const IPoly& f, int var, double s) {
-    IPoly out;
-    for (const auto& kv : f) {
-        IKey k = kv.first;
-        k[size_t(var)] += 1;
-        out[k] = kv.second * s;
+// A contraction W_{m,k} or a derivative of one: homogeneous of degree `deg` in xbar, so a polynomial in
+// u, w, z whose terms are u^i w^(deg - 2b) z^b. Stored densely by (b, i): rows b = 0..nb-1 of nu
+// coefficients (an empty polynomial has nb = 0).
+struct IPoly {
+    int deg = 0, nb = 0, nu = 0;
+    std::vector<double> c;
+    IPoly() = default;
+    IPoly(int d, int rows, int cols) : deg(d), nb(std::max(0, std::min(rows, d / 2 + 1))), nu(cols) {
+        if (nb <= 0 || nu <= 0 || d < 0) nb = nu = 0;
+        c.assign(size_t(nb) * size_t(nu), 0.0);
     }
+    double* row(int b) { return c.data() + size_t(b) * size_t(nu); }
+    const double* row(int b) const { return c.data() + size_t(b) * size_t(nu); }
+    // room for rows x cols coefficients, the present ones kept
+    void grow(int rows, int cols) {
+        if (rows <= nb && cols <= nu) return;
+        IPoly g(deg, std::max(rows, nb), std::max(cols, nu));
+        for (int b = 0; b < nb; ++b) std::copy(row(b), row(b) + nu, g.row(b));
+        *this = std::move(g);
+    }
+};
+
+// y += s u^pu z^pz f; the caller sees to the degrees: f.deg + (2 pz) and the powers of w that come
+// with it add up to y.deg.
+void axpy(IPoly& y, double s, const IPoly& f, int pu = 0, int pz = 0) {
+    if (!f.nb) return;
+    y.grow(f.nb + pz, f.nu + pu);
+    for (int b = 0; b < f.nb; ++b) {
+        const double* src = f.row(b);
+        double* dst = y.row(b + pz) + pu;
+        for (int i = 0; i < f.nu; ++i) dst[i] += s * src[i];
+    }
+}
+
+IPoly der_u(const IPoly& f) {
+    IPoly out(f.deg, f.nb, f.nu - 1);
+    for (int b = 0; b < out.nb; ++b)
+        for (int i = 0; i < out.nu; ++i) out.row(b)[i] = double(i + 1) * f.row(b)[i + 1];
     return out;
 }
 
-IPoly mul(const IPoly& a, const IPoly& b) {
-    IPoly out;
-    for (const auto& ka : a)
-        for (const auto& kb : b)
-            out[IKey{ka.first[0] + kb.first[0], ka.first[1] + kb.first[1], ka.first[2] + kb.first[2]}] +=
-                ka.second * kb.second;
+IPoly der_w(const IPoly& f) {                 // the power of w is deg - 2 b
+    IPoly out(f.deg - 1, f.nb, f.nu);
+    for (int b = 0; b < out.nb; ++b)
+        for (int i = 0; i < out.nu; ++i) out.row(b)[i] = double(f.deg - 2 * b) * f.row(b)[i];
     return out;
 }
 
-constexpr int U_ = 0, W_ = 1, Z_ = 2;
-
-IPoly lap(const IPoly& f, int d) {
-    const IPoly fu = der(f, U_), fw = der(f, W_);
-    IPoly out;
-    axpy(out, 2.0 * d, fu);
-    axpy(out, 1.0, times(der(fu, U_), U_, 4.0));
-    axpy(out, 1.0, times(der(fu, W_), W_, 4.0));
-    axpy(out, 1.0, times(der(fw, W_), Z_, 1.0));
+IPoly der_z(const IPoly& f) {
+    IPoly out(f.deg - 2, f.nb - 1, f.nu);
+    for (int b = 0; b < out.nb; ++b)
+        for (int i = 0; i < out.nu; ++i) out.row(b)[i] = double(b + 1) * f.row(b + 1)[i];
     return out;
 }
 
-IPoly lapbar(const IPoly& f, int d) {
-    const IPoly fz = der(f, Z_), fw = der(f, W_);
-    IPoly out;
-    axpy(out, 2.0 * d, fz);
-    axpy(out, 1.0, times(der(fz, Z_), Z_, 4.0));
-    axpy(out, 1.0, times(der(fz, W_), W_, 4.0));
-    axpy(out, 1.0, times(der(fw, W_), U_, 1.0));
-    return out;
+// y += s u^pu z^pz f g
+void mul_acc(IPoly& y, double s, const IPoly& f, const IPoly& g, int pu = 0, int pz = 0) {
+    if (!f.nb || !g.nb) return;
+    y.grow(f.nb + g.nb - 1 + pz, f.nu + g.nu - 1 + pu);
+    for (int b = 0; b < f.nb; ++b)
+        for (int i = 0; i < f.nu; ++i) {
+            const double v = s * f.row(b)[i];
+            if (v == 0.0) continue;
+            for (int e = 0; e < g.nb && b + e + pz < y.nb; ++e) {
+                const double* src = g.row(e);
+                double* dst = y.row(b + e + pz) + i + pu;
+                for (int j = 0; j < g.nu; ++j) dst[j] += v * src[j];
+            }
+        }
 }
 
-IPoly gdot(const IPoly& f, const IPoly& g) {
-    const IPoly fu = der(f, U_), fw = der(f, W_), gu = der(g, U_), gw = der(g, W_);
-    IPoly out = times(mul(fu, gu), U_, 4.0);
-    IPoly cross = mul(fu, gw);
-    axpy(cross, 1.0, mul(fw, gu));
-    axpy(out, 1.0, times(cross, W_, 2.0));
-    axpy(out, 1.0, times(mul(fw, gw), Z_, 1.0));
-    return out;
+// First derivatives of a contraction, kept for the products of the recursion.
+struct Grad {
+    IPoly u, w, z;
+};
+
+Grad gradient(const IPoly& f) { return Grad{der_u(f), der_w(f), der_z(f)}; }
+
+// y += the Laplacian in x (in xbar) of f, from its gradient g.
+void lap_acc(IPoly& y, const Grad& g, int d) {
+    axpy(y, 2.0 * d, g.u);
+    axpy(y, 4.0, der_u(g.u), 1);
+    axpy(y, 4.0, der_w(g.u));                 // times w: the same row
+    axpy(y, 1.0, der_w(g.w), 0, 1);
 }
 
-IPoly gbdot(const IPoly& f, const IPoly& g) {
-    const IPoly fz = der(f, Z_), fw = der(f, W_), gz = der(g, Z_), gw = der(g, W_);
-    IPoly out = times(mul(fw, gw), U_, 1.0);
-    IPoly cross = mul(fw, gz);
-    axpy(cross, 1.0, mul(fz, gw));
-    axpy(out, 1.0, times(cross, W_, 2.0));
-    axpy(out, 1.0, times(mul(fz, gz), Z_, 4.0));
-    return out;
+void lapbar_acc(IPoly& y, const Grad& g, int d) {
+    axpy(y, 2.0 * d, g.z);
+    axpy(y, 4.0, der_z(g.z), 0, 1);
+    axpy(y, 4.0, der_w(g.z));                 // times w
+    axpy(y, 1.0, der_w(g.w), 1);
 }
 
-IPoly xbar_grad(const IPoly& f) {
-    IPoly out = times(der(f, U_), W_, 2.0);
-    axpy(out, 1.0, times(der(f, W_), Z_, 1.0));
-    return out;
+// y += s grad f . grad g (gradbar f . gradbar g).
+void gdot_acc(IPoly& y, double s, const Grad& f, const Grad& g) {
+    mul_acc(y, 4.0 * s, f.u, g.u, 1);
+    mul_acc(y, 2.0 * s, f.u, g.w);            // times w
+    mul_acc(y, 2.0 * s, f.w, g.u);
+    mul_acc(y, s, f.w, g.w, 0, 1);
 }
 
-void prune(IPoly& f) {
-    for (auto it = f.begin(); it != f.end();)
-        it = (it->second == 0.0) ? f.erase(it) : std::next(it);
+void gbdot_acc(IPoly& y, double s, const Grad& f, const Grad& g) {
+    mul_acc(y, s, f.w, g.w, 1);
+    mul_acc(y, 2.0 * s, f.w, g.z);            // times w
+    mul_acc(y, 2.0 * s, f.z, g.w);
+    mul_acc(y, 4.0 * s, f.z, g.z, 0, 1);
+}
+
+// The products of eq.(MBrec) for (m, k) -- first sum, x-gradients of (l, r) and (m - l - 2, k - r);
+// second sum, xbar-gradients of (l, r) and (m - l - 1, k - r + 1), whose r = 0 terms vanish -- are symmetric in their two
+// factors: each unordered pair once, with factor f = 2 where the factors differ.
+template <class First, class Second>
+inline void for_product_pairs(int m, int k, First first, Second second) {
+    for (int l = 0; l <= m - 2; ++l)
+        for (int r = std::max(0, k - m + l + 2); r <= std::min(k, l); ++r) {
+            const int l2 = m - l - 2, r2 = k - r;
+            if (l < l2 || (l == l2 && r <= r2)) first(l, r, l2, r2, l == l2 && r == r2 ? 1.0 : 2.0);
+        }
+    for (int l = 1; l <= m - 2; ++l)
+        for (int r = std::max(1, k - m + l + 2); r <= std::min(k, l); ++r) {
+            const int l2 = m - l - 1, r2 = k - r + 1;
+            if (l < l2 || (l == l2 && r <= r2)) second(l, r, l2, r2, l == l2 && r == r2 ? 1.0 : 2.0);
+        }
 }
 
 // W[m][k], 0 <= k <= m <= p-1: eq.(DIA) on the diagonal, then eq.(MBrec) for k = m-1..0 (Fig. 1).
 std::vector<std::vector<IPoly>> radial_coefficients(const std::vector<double>& a, int d, int p) {
     std::vector<std::vector<IPoly>> W(static_cast<size_t>(p), std::vector<IPoly>(static_cast<size_t>(p)));
-    IPoly V;
-    for (size_t n = 0; n < a.size(); ++n)
-        if (a[n] != 0.0) V[IKey{int(n), 0, 0}] = a[n];
+    std::vector<std::vector<Grad>> G(static_cast<size_t>(p), std::vector<Grad>(static_cast<size_t>(p)));
+    IPoly V(0, 1, int(a.size()));
+    for (size_t n = 0; n < a.size(); ++n) V.c[n] = a[n];
     W[0][0] = V;
+    G[0][0] = gradient(V);
     double fact = 1.0;
+    IPoly t = V;                              // (xbar . grad)^(2m) V
     for (int m = 1; m < p; ++m) {
         fact *= double(2 * m) * double(2 * m + 1);
-        IPoly t = V;
-        for (int i = 0; i < 2 * m; ++i) t = xbar_grad(t);
-        IPoly diag;
+        for (int i = 0; i < 2; ++i) {         // xbar . grad f = 2w f_u + z f_w
+            IPoly next(t.deg + 1, 0, 0);
+            axpy(next, 2.0, der_u(t));
+            axpy(next, 1.0, der_w(t), 0, 1);
+            t = std::move(next);
+        }
+        IPoly diag(2 * m, 0, 0);
         axpy(diag, 1.0 / fact, t);
-        prune(diag);
-        W[size_t(m)][size_t(m)] = diag;
+        W[size_t(m)][size_t(m)] = std::move(diag);
+        G[size_t(m)][size_t(m)] = gradient(W[size_t(m)][size_t(m)]);
         for (int k = m - 1; k >= 0; --k) {
-            IPoly rhs = lap(W[size_t(m - 1)][size_t(k)], d);
-            axpy(rhs, 1.0, lapbar(W[size_t(m)][size_t(k + 1)], d));
-            for (int l = 0; l <= m - 2; ++l)
-                for (int r = std::max(0, k - m + l + 2); r <= std::min(k, l); ++r)
-                    axpy(rhs, -1.0, gdot(W[size_t(l)][size_t(r)], W[size_t(m - l - 2)][size_t(k - r)]));
-            for (int l = 1; l <= m - 2; ++l)
-                for (int r = std::max(0, k - m + l + 2); r <= std::min(k, l); ++r)
-                    axpy(rhs, -1.0, gbdot(W[size_t(l)][size_t(r)], W[size_t(m - l - 1)][size_t(k - r + 1)]));
-            IPoly out;
-            axpy(out, 1.0 / double(8 * (m + k + 1)), rhs);
-            prune(out);
-            W[size_t(m)][size_t(k)] = out;
+            IPoly rhs(2 * k, k + 1, std::max(0, kQuarticDegrees.d[m][k]) / 2 + 2);
+            lap_acc(rhs, G[size_t(m - 1)][size_t(k)], d);
+            lapbar_acc(rhs, G[size_t(m)][size_t(k + 1)], d);
+            for_product_pairs(m, k, [&](int l, int r, int l2, int r2, double f) {
+                gdot_acc(rhs, -f, G[size_t(l)][size_t(r)], G[size_t(l2)][size_t(r2)]);
+            }, [&](int l, int r, int l2, int r2, double f) {
+                gbdot_acc(rhs, -f, G[size_t(l)][size_t(r)], G[size_t(l2)][size_t(r2)]);
+            });
+            for (double& v : rhs.c) v *= 1.0 / double(8 * (m + k + 1));
+            W[size_t(m)][size_t(k)] = std::move(rhs);
+            G[size_t(m)][size_t(k)] = gradient(W[size_t(m)][size_t(k)]);
         }
     }
     return W;
@@ -183,54 +223,71 @@ std::vector<Group> layout_groups(int p) {
 
 // The level table at eps (unscaled, consumption order, highest power of u first); false if a
 // coefficient falls outside the shape bound.
-bool fold_radial(const std::vector<std::vector<IPoly>>& W, int p, double eps, std::vector<double>& tab) {
-    const std::vector<Group> groups = layout_groups(p);
+bool fold_radial(const std::vector<std::vector<IPoly>>& W, const std::vector<Group>& groups, int p, double eps,
+                 std::vector<double>& tab) {
     tab.assign(size_t(radial_size(p)), 0.0);
-    std::map<std::pair<int, int>, const Group*> where;
-    for (const Group& g : groups) where[{g.j + g.l, g.j}] = &g;
+    std::vector<std::vector<const Group*>> where(static_cast<size_t>(p), std::vector<const Group*>(static_cast<size_t>(p)));
+    for (const Group& g : groups) where[size_t(g.j + g.l)][size_t(g.j)] = &g;
     for (int m = 0; m < p; ++m)
         for (int k = 0; k <= m; ++k) {
+            const IPoly& w = W[size_t(m)][size_t(k)];
             const double f = std::pow(eps, double(m - k + 1));
-            for (const auto& kv : W[size_t(m)][size_t(k)]) {
-                const int i = kv.first[0], jw = kv.first[1], lz = kv.first[2];
-                if (jw % 2 != 0 || jw / 2 + lz != k) return false;
-                auto it = where.find({k, jw / 2});
-                if (it == where.end() || i >= it->second->len) return false;
-                const Group& g = *it->second;
-                tab[size_t(g.off + g.len - 1 - i)] += kv.second * f;
+            for (int b = 0; b < w.nb; ++b) {                        // u^i w^(2 (k - b)) z^b
+                const int j = k - b;
+                const Group* g = where[size_t(k)][size_t(j)];
+                for (int i = 0; i < w.nu; ++i) {
+                    if (w.row(b)[i] == 0.0) continue;
+                    if (!g || i >= g->len) return false;
+                    tab[size_t(g->off + g->len - 1 - i)] += w.row(b)[i] * f;
+                }
             }
         }
     return true;
 }
 
-// eps W_p of one slice from an unscaled table (the kernels' order: Horner in u, z, w^2).
-double eval_slice(const std::vector<double>& tab, int p, const double* x, const double* xb, int d) {
-    double u = 0.0, w = 0.0, z = 0.0;
+// Level action of the straight line from a to b (2^n slices) from an unscaled table. The deviation is the
+// same in every slice: the Q_{k,j} of one j are first added up with their powers of z = xbar.xbar.
+double radial_line_action(const std::vector<double>& tab, const std::vector<Group>& groups, int p, const double* a,
+                          const double* b, int d, int n) {
+    const int N = 1 << n, nj = radial_nj(p);
+    double xb[kVecMaxDim], z = 0.0;
     for (int c = 0; c < d; ++c) {
-        u = std::fma(x[c], x[c], u);
-        w = std::fma(x[c], xb[c], w);
-        z = std::fma(xb[c], xb[c], z);
+        xb[c] = 0.5 * (b[c] - a[c]) / double(N);
+        z += xb[c] * xb[c];
     }
-    const double w2 = w * w;
-    const int nj = radial_nj(p);
-    size_t off = 0;
-    double acc = 0.0;
-    for (int j = nj - 1; j >= 0; --j) {
-        const int nl = radial_nl(p, j);
-        double zs = 0.0;
-        for (int l = nl - 1; l >= 0; --l) {
-            const int len = radial_len(p, j + l, j);
-            double v = 0.0;
-            if (len > 0) {
-                v = tab[off];
-                for (int e = 1; e < len; ++e) v = std::fma(v, u, tab[off + size_t(e)]);
+    std::vector<std::vector<double>> R(static_cast<size_t>(nj));    // per j: sum_l z^l Q_{j+l,j}, by power of u
+    for (const Group& g : groups) {                                 // l from high to low within a j
+        std::vector<double>& r = R[size_t(g.j)];
+        r.resize(std::max(r.size(), size_t(g.len)), 0.0);
+        for (size_t e = 0; e < r.size(); ++e)
+            r[e] = r[e] * z + (e < size_t(g.len) ? tab[size_t(g.off + g.len - 1) - e] : 0.0);
+    }
+    constexpr int L = 8;                                            // slices side by side
+    double S = 0.0;
+    for (int k0 = 0; k0 < N; k0 += L) {
+        double u[L], w2[L], acc[L];
+        for (int i = 0; i < L; ++i) {
+            double su = 0.0, sw = 0.0;
+            for (int c = 0; c < d; ++c) {
+                const double q0 = a[c] + (b[c] - a[c]) * double(k0 + i) / double(N);
+                const double q1 = a[c] + (b[c] - a[c]) * double(k0 + i + 1) / double(N);
+                const double x = 0.5 * (q0 + q1);
+                su += x * x;
+                sw += x * xb[c];
             }
-            off += size_t(len);
-            zs = (l == nl - 1) ? v : std::fma(zs, z, v);
+            u[i] = su;
+            w2[i] = sw * sw;
+            acc[i] = 0.0;
         }
-        acc = (j == nj - 1) ? zs : std::fma(acc, w2, zs);
+        for (int j = nj - 1; j >= 0; --j) {
+            double v[L] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+            for (size_t e = R[size_t(j)].size(); e-- > 0;)
+                for (int i = 0; i < L; ++i) v[i] = v[i] * u[i] + R[size_t(j)][e];
+            for (int i = 0; i < L; ++i) acc[i] = acc[i] * w2[i] + v[i];
+        }
+        for (int i = 0; i < L && k0 + i < N; ++i) S += acc[i];
     }
-    return acc;
+    return S;
 }
 
 // Device copy: coefficient of u^i (w^2)^j z^l times 4^-(i + 2j + l).
@@ -319,28 +376,16 @@ int build_vector_problem(const pimc_radial_potential* V, double m, const double*
     P.tab_dev.assign(P.tab.size(), 0.0);
     P.shift.assign(size_t(P.s + 1), 0.0);
     std::vector<double> lt;
+    const std::vector<Group> groups = layout_groups(p);
     for (int n = 0; n <= P.s; ++n) {
-        if (!fold_radial(W, p, std::ldexp(T, -n), lt)) {
+        if (!fold_radial(W, groups, p, std::ldexp(T, -n), lt)) {
             std::snprintf(why, whylen, "internal: a coefficient falls outside the radial table shape");
             return PIMC_EUNSUPPORTED;
         }
         std::copy(lt.begin(), lt.end(), P.tab.begin() + size_t(n) * size_t(P.stride));
         const std::vector<double> sc = scale_for_sums(lt, p);
         std::copy(sc.begin(), sc.end(), P.tab_dev.begin() + size_t(n) * size_t(P.stride));
-        // straight line q_k = a + (b - a) k / 2^n
-        const int M = 1 << n;
-        double S = 0.0;
-        for (int k = 0; k < M; ++k) {
-            double x[kVecMaxDim], xb[kVecMaxDim];
-            for (int c = 0; c < P.dim; ++c) {
-                const double q0 = P.a[c] + (P.b[c] - P.a[c]) * double(k) / double(M);
-                const double q1 = P.a[c] + (P.b[c] - P.a[c]) * double(k + 1) / double(M);
-                x[c] = 0.5 * (q0 + q1);
-                xb[c] = 0.5 * (q1 - q0);
-            }
-            S += eval_slice(lt, p, x, xb, P.dim);
-        }
-        P.shift[size_t(n)] = S;
+        P.shift[size_t(n)] = radial_line_action(lt, groups, p, P.a, P.b, P.dim, n);
     }
     P.level0_action = P.shift[0];
     P.shape = shape_array(p);
@@ -350,7 +395,7 @@ int build_vector_problem(const pimc_radial_potential* V, double m, const double*
 }
 
 int stage_vector(pimc_ctx* c, const VecProblem& P, uint64_t seed, uint32_t stream, VecArgs& A,
-                 const std::vector<unsigned char>& segs, const void** segs_dev) {
+                 const std::vector<unsigned char>& segs, const void** segs_dev, double** line_dev) {
     const size_t nlev = size_t(P.s + 1);
     const size_t n_tab = P.tab_dev.size();
     const size_t off_shift = nlev * 8;
@@ -360,6 +405,9 @@ int stage_vector(pimc_ctx* c, const VecProblem& P, uint64_t seed, uint32_t strea
     const size_t off_queue = (off_shape + P.shape.size() * 4 + 255) & ~size_t(255);
     const size_t off_segs = off_queue + 256;
     const size_t total = off_segs + segs.size();
+    // component route: the partial sums of the reference actions, on the device only
+    const size_t off_line = (total + 15) & ~size_t(15);
+    const size_t need = off_line + (P.poly ? nlev * kLineParts * 8 : 0);
     unsigned char* host = nullptr;
     int st = pinned_stage(c, total, &host);
     if (st) return st;
@@ -369,11 +417,12 @@ int stage_vector(pimc_ctx* c, const VecProblem& P, uint64_t seed, uint32_t strea
     std::memcpy(host + off_tab, P.tab_dev.data(), n_tab * 8);
     std::memcpy(host + off_shape, P.shape.data(), P.shape.size() * 4);
     if (!segs.empty()) std::memcpy(host + off_segs, segs.data(), segs.size());
-    st = ensure(c, &c->d_prm, &c->prm_bytes, total);
+    st = ensure(c, &c->d_prm, &c->prm_bytes, need);
     if (st) return st;
     c->stage_busy = true;
     HIP_TRY(c, hipMemcpyAsync(c->d_prm, host, total, hipMemcpyHostToDevice, c->stream));
     *segs_dev = static_cast<unsigned char*>(c->d_prm) + off_segs;
+    *line_dev = reinterpret_cast<double*>(static_cast<unsigned char*>(c->d_prm) + off_line);
     unsigned char* base = static_cast<unsigned char*>(c->d_prm);
     std::memset(&A, 0, sizeof(A));
     A.sig = reinterpret_cast<const double*>(base);
@@ -438,7 +487,8 @@ int vector_amplitude_core(pimc_ctx* c, const VecProblem& P, uint64_t n_samples, 
     pw.gsum = c->d_gsum;
     VecArgs A;
     const void* segs = nullptr;
-    st = stage_vector(c, P, seed, stream, A, run_segments(pw, slots, n_samples, c->d_partials), &segs);
+    double* line = nullptr;
+    st = stage_vector(c, P, seed, stream, A, run_segments(pw, slots, n_samples, c->d_partials), &segs, &line);
     if (st) return st;
     pw.queue = A.work.queue;
     A.work = pw;
@@ -448,14 +498,20 @@ int vector_amplitude_core(pimc_ctx* c, const VecProblem& P, uint64_t n_samples, 
     A.partials = c->d_partials;
     A.dump = nullptr;
     const int grid = work_grid(A.work, kVecBlock / 64, resident);
+    double* const red = reinterpret_cast<double*>(c->h_stage);
+    double* const line_host = red + size_t(PIMC_MAX_S + 1) * 4;
+    if (P.poly) {
+        HIP_TRY(c, launch_line_poly(A, P.dim, line, c->stream));
+        HIP_TRY(c, launch_line_sum(line, P.s, const_cast<double*>(A.shift), line_host, c->stream));
+    }
     const LaunchOn on(c->stream, c->ev0, c->ev1);
     HIP_TRY(c, P.poly ? launch_vector_poly(A, P.dim, P.U, grid, on)
                       : launch_vector(A, P.dim, P.p, P.U, P.specialized, grid, on));
     // the last kernel writes the sums straight into pinned memory
-    double* const red = reinterpret_cast<double*>(c->h_stage);
     HIP_TRY(c, launch_run_sums(A.work, slots, n_samples, c->d_partials, segs, red, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     c->stage_busy = false;
+    if (P.poly) std::copy(line_host + 1, line_host + nlev, c->last_shift.begin() + 1);
     float ms = 0.f;
     HIP_TRY(c, hipEventElapsedTime(&ms, c->ev0, c->ev1));
     c->last_ms = ms;
@@ -467,7 +523,7 @@ int vector_amplitude_core(pimc_ctx* c, const VecProblem& P, uint64_t n_samples, 
     for (int n = 1; n < nlev; ++n) {
         if (!hier && n != P.s) continue;
         const size_t k = size_t(hier ? n : 0);
-        if (assemble_level(&red[k * 4], std::log(P.pref * P.K0) - P.shift[size_t(n)], out[n])) nonfinite = true;
+        if (assemble_level(&red[k * 4], std::log(P.pref * P.K0) - c->last_shift[size_t(n)], out[n])) nonfinite = true;
     }
     return nonfinite ? PIMC_WNONFINITE : PIMC_OK;
 }
@@ -483,7 +539,8 @@ int vector_path_actions_core(pimc_ctx* c, const VecProblem& P, uint64_t seed, ui
     if (st) return st;
     VecArgs A;
     const void* segs = nullptr;
-    st = stage_vector(c, P, seed, stream, A, {}, &segs);
+    double* line = nullptr;
+    st = stage_vector(c, P, seed, stream, A, {}, &segs, &line);
     if (st) return st;
     st = ensure(c, reinterpret_cast<void**>(&c->d_dump), &c->dump_bytes, size_t(k_paths) * nlev * 8);
     if (st) return st;
@@ -675,7 +732,7 @@ bool build_poly_code(const std::vector<MKey>& keys, int d, PolyCode& P) {
     return ok;
 }
 
-// The same arithmetic as PolyEvalRT on one slice (y as defined above), for the reference actions.
+// The same arithmetic as PolyEvalRT on one slice (y as defined above), for the level-0 action.
 double eval_poly_node(const std::vector<int>& code, size_t& s, const double* coef, size_t& c, const double* y, int v,
                       int nv) {
     if (v == nv - 1) {
@@ -854,19 +911,13 @@ int build_poly_problem(const pimc_poly_potential* V, double m, const double* a, 
             for (int c = 0; c < 2 * kVecMaxDim; ++c) deg += k[size_t(c)];
             coef[o] = std::ldexp(f[size_t(R.slot[o])], -deg);   // y = 2 x, 2 xbar
         }
-        const int M = 1 << n;
-        double S = 0.0;
-        for (int k = 0; k < M; ++k) {
-            double y[2 * kVecMaxDim] = {0, 0, 0, 0, 0, 0};
-            for (int c = 0; c < P.dim; ++c) {
-                const double q0 = P.a[c] + (P.b[c] - P.a[c]) * double(k) / double(M);
-                const double q1 = P.a[c] + (P.b[c] - P.a[c]) * double(k + 1) / double(M);
-                y[c] = q1 - q0;
-                y[P.dim + c] = q0 + q1;
-            }
-            S += eval_poly_code(R.code, coef, y, nv);
+        if (n > 0) continue;                     // the references of the other levels are formed on the device
+        double y[2 * kVecMaxDim] = {};
+        for (int c = 0; c < P.dim; ++c) {
+            y[c] = P.b[c] - P.a[c];
+            y[P.dim + c] = P.a[c] + P.b[c];
         }
-        P.shift[size_t(n)] = S;
+        P.shift[0] = eval_poly_code(R.code, coef, y, nv);
     }
     P.tab_dev = P.tab;
     P.level0_action = P.shift[0];
@@ -896,6 +947,16 @@ hipError_t launch_vector_poly(const VecArgs& A, int dim, int U, int grid, Launch
         case 2: return launch_vector_poly_dim<2>(A, U, grid, st);
         case 3: return launch_vector_poly_dim<3>(A, U, grid, st);
         case 4: return launch_vector_poly_dim<4>(A, U, grid, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_line_poly(const VecArgs& A, int dim, double* parts, hipStream_t st) {
+    switch (dim) {
+        case 1: return launch_line_poly_dim<1>(A, parts, st);
+        case 2: return launch_line_poly_dim<2>(A, parts, st);
+        case 3: return launch_line_poly_dim<3>(A, parts, st);
+        case 4: return launch_line_poly_dim<4>(A, parts, st);
         default: return hipErrorInvalidValue;
     }
 }
@@ -966,11 +1027,11 @@ int pimc_level_table_radial(const pimc_radial_potential* V, double m, double T, 
     if (level > PIMC_MAX_S) { set_thread_error("level > %d", PIMC_MAX_S); return PIMC_EINVAL; }
     const auto W = radial_coefficients(rescaled(V, m), V->dim, p);
     std::vector<double> tab;
-    if (!fold_radial(W, p, std::ldexp(T, -int(level)), tab)) {
+    const std::vector<Group> groups = layout_groups(p);
+    if (!fold_radial(W, groups, p, std::ldexp(T, -int(level)), tab)) {
         set_thread_error("internal: a coefficient falls outside the radial table shape");
         return PIMC_EUNSUPPORTED;
     }
-    const std::vector<Group> groups = layout_groups(p);
     if (n_out) *n_out = tab.size();
     if (n_groups) *n_groups = int(groups.size());
     if (!out || cap < tab.size()) {

@@ -513,6 +513,22 @@ inline hipError_t launch_one(const VecArgs& A, const Eval& ev, int grid, LaunchO
     return hipGetLastError();
 }
 
+// Reference actions of the straight line from A.a to A.b (pimc_chunks.hpp).
+template <int DIM, class Eval>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) k_line_vec(VecArgs A, Eval ev, double* parts) {
+    line_part(parts, [&](int level, int k, int N) __attribute__((always_inline)) {
+        double qa[1][DIM], qb[1][DIM];
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) {
+            qa[0][c] = A.a[c] + (A.b[c] - A.a[c]) * double(k) / double(N);
+            qb[0][c] = A.a[c] + (A.b[c] - A.a[c]) * double(k + 1) / double(N);
+        }
+        double S = 0.0;
+        ev.template eval<1>(level, qa, qb, S);
+        return S;
+    });
+}
+
 template <int DIM, int U, class Eval>
 inline int resident_one(size_t lds, int device) {
     int per_cu = 0;

@@ -47,6 +47,15 @@ hipError_t launch_vector_poly_dim<PIMC_POLY_DIM>(const VecArgs& A, int U, int gr
 }
 
 template <>
+hipError_t launch_line_poly_dim<PIMC_POLY_DIM>(const VecArgs& A, double* parts, hipStream_t st) {
+    if (A.s < 1) return hipSuccess;
+    const vec::PolyEvalRT<PIMC_POLY_DIM> ev{A.tab, A.shape, A.stride};
+    hipLaunchKernelGGL((vec::k_line_vec<PIMC_POLY_DIM, vec::PolyEvalRT<PIMC_POLY_DIM>>), dim3(A.s, line_parts(A.s)),
+                       dim3(kBlock), 0, st, A, ev, parts);
+    return hipGetLastError();
+}
+
+template <>
 int vector_poly_resident_dim<PIMC_POLY_DIM>(int U, size_t lds, int device) {
     if constexpr (kSplit)
         if (U == kUDeep) return vector_poly_resident_deep<PIMC_POLY_DIM>(lds, device);

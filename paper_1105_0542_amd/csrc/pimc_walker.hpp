@@ -204,6 +204,25 @@ inline hipError_t launch_one(const AmpArgs& A, const Eval& ev, int grid, LaunchO
     return hipGetLastError();
 }
 
+// Reference actions of the straight line from A.a to A.b (pimc_chunks.hpp).
+template <class Eval>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(2))) k_line(AmpArgs A, Eval ev, double* parts) {
+    line_part(parts, [&](int level, int k, int N) __attribute__((always_inline)) {
+        const double qa[1] = {A.a + (A.b - A.a) * double(k) / double(N)};
+        const double qb[1] = {A.a + (A.b - A.a) * double(k + 1) / double(N)};
+        double S = 0.0;
+        ev.template eval<1>(level, qa, qb, S);
+        return S;
+    });
+}
+
+template <class Eval>
+inline hipError_t launch_line(const AmpArgs& A, const Eval& ev, double* parts, hipStream_t st) {
+    if (A.s < 1) return hipSuccess;
+    hipLaunchKernelGGL((k_line<Eval>), dim3(A.s, line_parts(A.s)), dim3(kBlock), 0, st, A, ev, parts);
+    return hipGetLastError();
+}
+
 template <class S, class Eval>
 inline int resident_one(size_t lds, int device) {
     int per_cu = 0;
