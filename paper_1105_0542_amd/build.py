@@ -29,12 +29,17 @@ HEADERS = ["pimc_tables.hpp", "pimc_device.hpp", "pimc_internal.hpp", "pimc_math
 # object directory.
 CODEGEN = "pimc_gen_codegen.cpp"
 GENERATED = "pimc_general_gen.hpp"
-# One translation unit per out-of-line general-mode level: (source, defines, object name).
+# Compiler flag of units whose literal constants the machine-level loop-invariant code motion would hoist
+# into registers that then spill (pimc_general_inline.hip, pimc_vector_poly.hip state what it costs).
+NO_LICM = ["-mllvm", "-disable-machine-licm"]
+# One translation unit per out-of-line general-mode level: (source, defines and flags, object name).
 GEN_HI_LEVELS = range(11, 19)
 VARIANTS = [("pimc_general_hi.hip", [f"-DPIMC_GEN_P={p}"], f"pimc_general_hi_p{p}") for p in GEN_HI_LEVELS]
+VARIANTS += [("pimc_general_inline.hip", ["-DPIMC_GEN_LO=1", "-DPIMC_GEN_HI=4"], "pimc_general_inline_1"),
+             ("pimc_general_inline.hip", ["-DPIMC_GEN_LO=5", "-DPIMC_GEN_HI=10"] + NO_LICM, "pimc_general_inline_5")]
 # One translation unit per dimension for the component evaluator's kernels, and one more for the
 # deepest subtree of d = 3 and 4 (empty where that depth is below the split).
-VARIANTS += [("pimc_vector_poly.hip", [f"-DPIMC_POLY_DIM={d}"], f"pimc_vector_poly_d{d}") for d in (1, 2, 3, 4)]
+VARIANTS += [("pimc_vector_poly.hip", [f"-DPIMC_POLY_DIM={d}"] + (NO_LICM if d < 3 else []), f"pimc_vector_poly_d{d}") for d in (1, 2, 3, 4)]
 VARIANTS += [("pimc_vector_poly.hip", [f"-DPIMC_POLY_DIM={d}", "-DPIMC_POLY_DEEP=1"], f"pimc_vector_poly_d{d}_deep")
              for d in (3, 4)]
 

@@ -21,6 +21,20 @@ struct GenCompiled;
 
 namespace pimc {
 
+// a b + k with k in scalar registers. From p = 5 on (SGPR_ADDEND) as the three-operand instruction: written
+// as fma(), the compiler takes the two-operand one, which accumulates into k's registers, and copies k
+// there first, two moves for each of the 44 steps of a slice's polynomial part. 1e6 paths, N = 256, p = 8:
+// 8.57 -> 8.28 ms, p = 10 20.9 -> 20.0; below (p = 4, four slices at once) 3.38 -> 3.59, so not there.
+template <bool SGPR_ADDEND>
+__device__ __forceinline__ double fma_row(double a, double b, double k) {
+    if constexpr (SGPR_ADDEND) {
+        asm("v_fma_f64 %0, %0, %1, %2" : "+v"(a) : "v"(b), "s"(k));
+        return a;
+    } else {
+        return fma(a, b, k);
+    }
+}
+
 template <int J>
 __device__ __forceinline__ void gen_derivatives_dev(const GenTables& g, double x, double (&v)[J + 1]) {
     // V^(j) of the polynomial part (degree <= 8, zero-padded rows: a leading zero coefficient leaves
@@ -32,7 +46,7 @@ __device__ __forceinline__ void gen_derivatives_dev(const GenTables& g, double x
     for (int j = 0; j <= JP; ++j) {
         double acc = dp[j * 9 + 8 - j];
 #pragma unroll
-        for (int n = 7 - j; n >= 0; --n) acc = fma(acc, x, dp[j * 9 + n]);
+        for (int n = 7 - j; n >= 0; --n) acc = fma_row<(J >= 8)>(acc, x, dp[j * 9 + n]);
         v[j] = acc;
     }
 #pragma unroll
@@ -58,11 +72,12 @@ __device__ __forceinline__ void gen_derivatives_dev(const GenTables& g, double x
         // d^j/dx^j B e^{-b x^2} = B (-sqrt b)^j H_j(sqrt(b) x) e^{-b x^2}, H_{j+1} = 2y H_j - 2j H_{j-1}
         const double y = g.gsb[t] * x;
         double e = g.gB[t] * exp_fp64(-g.gb[t] * x * x);
+        const double y2 = y + y;
         double hm = 0.0, h = 1.0;
 #pragma unroll
         for (int j = 0; j <= J; ++j) {
-            v[j] += e * h;
-            const double hn = 2.0 * y * h - 2.0 * double(j) * hm;
+            v[j] = fma(e, h, v[j]);
+            const double hn = fma(y2, h, -2.0 * double(j) * hm);
             hm = h;
             h = hn;
             e *= -g.gsb[t];

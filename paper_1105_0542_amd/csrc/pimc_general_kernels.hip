@@ -1,70 +1,11 @@
-// Estimation kernels of the general-potential mode: the walker (pimc_walker.hpp) instantiated with
-// the evaluators generated for p = 1..kGenInlineMaxP (pimc_general_device.hpp), subtrees of
-// U = 1..gen_subtree_levels(p) levels; the levels above are dispatched to their own translation units
-// (pimc_general_hi.hip).
+// Estimation kernels of the general-potential mode: dispatch by level to the translation units of the
+// inlined evaluators (pimc_general_inline.hip, p = 1..4 and 5..kGenInlineMaxP) and of the out-of-line
+// ones (pimc_general_hi.hip, one per level).
 #include <hip/hip_runtime.h>
 
-#include "pimc_general_device.hpp"
-#include "pimc_walker.hpp"
+#include "pimc_internal.hpp"
 
 namespace pimc {
-
-namespace {
-
-template <int P>
-hipError_t launch_p(const AmpArgs& A, int p, int U, int grid, LaunchOn st) {
-    if constexpr (P <= kGenInlineMaxP) {
-        if (p != P) return launch_p<P + 1>(A, p, U, grid, st);
-        const GenCompiledEval<P> ev{A.tab64, A.gen};
-        switch (U) {
-            case 1: return launch_one<DefaultShape<1>>(A, ev, grid, st);
-            case 2: if constexpr (gen_subtree_levels(P) >= 2) return launch_one<DefaultShape<2>>(A, ev, grid, st); else break;
-            case 3: if constexpr (gen_subtree_levels(P) >= 3) return launch_one<DefaultShape<3>>(A, ev, grid, st); else break;
-            case 4: if constexpr (gen_subtree_levels(P) >= 4) return launch_one<DefaultShape<4>>(A, ev, grid, st); else break;
-            default: break;
-        }
-        return hipErrorInvalidValue;
-    } else {
-        return hipErrorInvalidValue;
-    }
-}
-
-template <int P>
-int resident_p(int p, int U, size_t lds, int device) {
-    if constexpr (P <= kGenInlineMaxP) {
-        if (p != P) return resident_p<P + 1>(p, U, lds, device);
-        switch (U) {
-            case 2: if constexpr (gen_subtree_levels(P) >= 2) return resident_one<DefaultShape<2>, GenCompiledEval<P>>(lds, device); else break;
-            case 3: if constexpr (gen_subtree_levels(P) >= 3) return resident_one<DefaultShape<3>, GenCompiledEval<P>>(lds, device); else break;
-            case 4: if constexpr (gen_subtree_levels(P) >= 4) return resident_one<DefaultShape<4>, GenCompiledEval<P>>(lds, device); else break;
-            default: break;
-        }
-        return resident_one<DefaultShape<1>, GenCompiledEval<P>>(lds, device);
-    } else {
-        return 256;
-    }
-}
-
-template <int P>
-int nrec_p(int p) {
-    if constexpr (P <= kGenInlineMaxP) {
-        return p == P ? GenCompiled<P>::NREC : nrec_p<P + 1>(p);
-    } else {
-        return -1;
-    }
-}
-
-template <int P>
-hipError_t line_p(const AmpArgs& A, int p, double* parts, hipStream_t st) {
-    if constexpr (P <= kGenInlineMaxP) {
-        if (p != P) return line_p<P + 1>(A, p, parts, st);
-        return launch_line(A, GenCompiledEval<P>{A.tab64, A.gen}, parts, st);
-    } else {
-        return hipErrorInvalidValue;
-    }
-}
-
-}  // namespace
 
 hipError_t launch_line_general(const AmpArgs& A, int p, double* parts, hipStream_t st) {
     switch (p) {
@@ -76,9 +17,10 @@ hipError_t launch_line_general(const AmpArgs& A, int p, double* parts, hipStream
         case 16: return gen_hi_line<16>(A, parts, st);
         case 17: return gen_hi_line<17>(A, parts, st);
         case 18: return gen_hi_line<18>(A, parts, st);
-        default: return line_p<1>(A, p, parts, st);
+        default: return p <= 4 ? gen_inline_line<1>(A, p, parts, st) : gen_inline_line<5>(A, p, parts, st);
     }
 }
+
 
 static_assert(kGenInlineMaxP == 10 && kGenMaxP == 18, "the out-of-line levels 11..18 are declared in pimc_internal.hpp");
 
@@ -92,7 +34,7 @@ hipError_t launch_general_compiled(const AmpArgs& A, int p, int U, int grid, Lau
         case 16: return gen_hi_launch<16>(A, U, grid, st);
         case 17: return gen_hi_launch<17>(A, U, grid, st);
         case 18: return gen_hi_launch<18>(A, U, grid, st);
-        default: return launch_p<1>(A, p, U, grid, st);
+        default: return p <= 4 ? gen_inline_launch<1>(A, p, U, grid, st) : gen_inline_launch<5>(A, p, U, grid, st);
     }
 }
 
@@ -106,7 +48,7 @@ int general_compiled_resident(int p, int U, size_t lds_bytes, int device) {
         case 16: return gen_hi_resident<16>(U, lds_bytes, device);
         case 17: return gen_hi_resident<17>(U, lds_bytes, device);
         case 18: return gen_hi_resident<18>(U, lds_bytes, device);
-        default: return resident_p<1>(p, U, lds_bytes, device);
+        default: return p <= 4 ? gen_inline_resident<1>(p, U, lds_bytes, device) : gen_inline_resident<5>(p, U, lds_bytes, device);
     }
 }
 
@@ -120,7 +62,7 @@ int general_compiled_nrec(int p) {
         case 16: return gen_hi_nrec<16>();
         case 17: return gen_hi_nrec<17>();
         case 18: return gen_hi_nrec<18>();
-        default: return nrec_p<1>(p);
+        default: return p <= 4 ? gen_inline_nrec<1>(p) : gen_inline_nrec<5>(p);
     }
 }
 

@@ -146,6 +146,28 @@ int resident_tanh_fixed(int p, size_t lds_bytes, int device);
 hipError_t launch_general_compiled(const AmpArgs& A, int p, int U, int grid, LaunchOn st);
 int general_compiled_resident(int p, int U, size_t lds_bytes, int device);
 int general_compiled_nrec(int p);
+// The levels up to kGenInlineMaxP in two translation units (pimc_general_inline.hip), LO = 1 and 5 their
+// first levels.
+template <int LO>
+hipError_t gen_inline_launch(const AmpArgs& A, int p, int U, int grid, LaunchOn st);
+template <int LO>
+int gen_inline_resident(int p, int U, size_t lds_bytes, int device);
+template <int LO>
+int gen_inline_nrec(int p);
+template <int LO>
+hipError_t gen_inline_line(const AmpArgs& A, int p, double* parts, hipStream_t st);
+#define PIMC_GEN_INLINE_DECLARE(LO)                                                          \
+    template <>                                                                               \
+    hipError_t gen_inline_launch<LO>(const AmpArgs& A, int p, int U, int grid, LaunchOn st); \
+    template <>                                                                               \
+    int gen_inline_resident<LO>(int p, int U, size_t lds_bytes, int device);                 \
+    template <>                                                                               \
+    int gen_inline_nrec<LO>(int p);                                                          \
+    template <>                                                                               \
+    hipError_t gen_inline_line<LO>(const AmpArgs& A, int p, double* parts, hipStream_t st);
+PIMC_GEN_INLINE_DECLARE(1)
+PIMC_GEN_INLINE_DECLARE(5)
+#undef PIMC_GEN_INLINE_DECLARE
 // The levels above kGenInlineMaxP, one translation unit each (pimc_general_hi.hip built with
 // PIMC_GEN_P = p): launch, resident workgroups per CU and monomial count of that level's evaluator.
 template <int P>
