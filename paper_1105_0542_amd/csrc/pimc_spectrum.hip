@@ -303,6 +303,139 @@ __global__ void k_scale_by_norm(const double* __restrict__ w, uint32_t n, const 
     qnext[i] = w[i] * inv;
 }
 
+// ---------------------------------------------------------------------------- fused Lanczos step
+// A step is a chain of short dependent kernels, 4 to 7 us each beside a product of 28 us (n = 16384): row
+// sums, dots, correction, dots, correction, norm, scaling. Here they are four, a workgroup of 8 waves per
+// row block of kTile rows, each doing what the block can do with the rows that it has just formed:
+//   k_step_rows:    w = M q_j from the tile partials, and the block's part of every dot <Q_c, w>;
+//   k_step_correct: the dots from all blocks' parts, w -= sum_c h_c Q_c, and the parts of the second
+//                   pass's dots; with LAST the part of |w|^2 instead;
+//   k_step_scale:   |w| from the parts, q_{j+1} = w / |w|.
+// Every block adds the parts for itself (lane = column, whole lines from L2). 8 bytes per column and pair
+// of blocks: 25 MB for 48 columns of n = 16384, 100 MB for n = 32768, and four times that per doubling,
+// so the fused form ends at kFuseBlocks row blocks and kFuseCols columns. GPU time of the chain without
+// the product, separate and fused, at 48 columns: n = 16384 35 and 21 us, n = 32768 57 and 43 us;
+// n = 300..8000, whole call: 1111 -> 850 us (300), 1200 -> 900 (1000), 1930 -> 1500 (8000),
+// 4550 -> 3700 (16384, 48 steps).
+constexpr int kStepWaves = 8;
+constexpr int kStepBlock = kStepWaves * 64;
+constexpr uint32_t kFuseCols = 128;
+constexpr uint32_t kFuseBlocks = 512;
+
+__device__ __forceinline__ double wave_total(double v) {
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+// parts[block * kFuseCols + c]: sum over the block's rows of Q_c w (wr: this lane's row of w, lane = row).
+__device__ __forceinline__ void dot_parts(const double* __restrict__ Q, uint64_t ldq, uint32_t row, bool live, double wr,
+                                          uint32_t ncols, double* __restrict__ parts) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll 4
+    for (uint32_t c = threadIdx.x >> 6; c < ncols; c += kStepWaves) {
+        const double v = wave_total(live ? Q[uint64_t(c) * ldq + row] * wr : 0.0);
+        if (lane == 0) parts[uint64_t(blockIdx.x) * kFuseCols + c] = v;
+    }
+}
+
+__global__ void __launch_bounds__(kStepBlock) k_step_rows(const double* __restrict__ prow, const double* __restrict__ pcol,
+                                                          uint32_t n, TileBand band, const double* __restrict__ Q,
+                                                          uint64_t ldq, uint32_t ncols, double* __restrict__ w,
+                                                          double* __restrict__ parts) {
+    __shared__ double part[kStepWaves][kTile];
+    const uint32_t I = blockIdx.x;
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const uint32_t row = I * kTile + uint32_t(lane);
+    const bool live = row < n;
+    const uint32_t lo = I > band.bw ? I - band.bw : 0u;
+    const uint32_t end = I + band.bw + 1 < band.nb ? I + band.bw + 1 : band.nb;
+    double s = 0.0;
+#pragma unroll 4
+    for (uint32_t q = lo + uint32_t(wave); q < end; q += kStepWaves) {
+        const uint32_t a = q < I ? q : I, b = q < I ? I : q;       // tile (a, b), a <= b
+        const uint64_t t = band.first(a) + (b - a);
+        s += q < I ? pcol[t * kTile + uint32_t(lane)] : prow[t * kTile + uint32_t(lane)];
+    }
+    part[wave][lane] = s;
+    __syncthreads();
+    double wr = 0.0;
+#pragma unroll
+    for (int k = 0; k < kStepWaves; ++k) wr += part[k][lane];
+    if (wave == 0 && live) w[row] = wr;
+    dot_parts(Q, ldq, row, live, wr, ncols, parts);
+}
+
+// in: the parts of this pass's dots; out: the parts of the next pass's (LAST: of |w|^2, one per block);
+// with alpha, *alpha = the dot with column ncols - 1.
+template <bool LAST>
+__global__ void __launch_bounds__(kStepBlock) k_step_correct(const double* __restrict__ Q, uint64_t ldq, uint32_t n, uint32_t nb,
+                                                             uint32_t ncols, const double* __restrict__ in,
+                                                             double* __restrict__ w, double* __restrict__ out,
+                                                             double* __restrict__ alpha) {
+    __shared__ double h[kFuseCols];
+    __shared__ double part[kStepWaves][kTile];
+    const int lane = threadIdx.x & 63;
+    const int wave = threadIdx.x >> 6;
+    const uint32_t row = blockIdx.x * kTile + uint32_t(lane);
+    const bool live = row < n;
+    for (uint32_t c0 = 0; c0 < ncols; c0 += 64) {                 // lane = column, wave w adds blocks w, w + 8, ...
+        const uint32_t c = c0 + uint32_t(lane);
+        double v = 0.0;
+        if (c < ncols) {
+#pragma unroll 8
+            for (uint32_t i = uint32_t(wave); i < nb; i += kStepWaves) v += in[uint64_t(i) * kFuseCols + c];
+        }
+        part[wave][lane] = v;
+        __syncthreads();
+        if (wave == 0 && c < ncols) {
+            v = 0.0;
+#pragma unroll
+            for (int k = 0; k < kStepWaves; ++k) v += part[k][lane];
+            h[c] = v;
+        }
+        __syncthreads();
+    }
+    double s = 0.0;
+#pragma unroll 4
+    for (uint32_t c = uint32_t(wave); c < ncols; c += kStepWaves)
+        s = fma(live ? Q[uint64_t(c) * ldq + row] : 0.0, h[c], s);
+    part[wave][lane] = s;
+    __syncthreads();
+    double sum = 0.0;
+#pragma unroll
+    for (int k = 0; k < kStepWaves; ++k) sum += part[k][lane];
+    const double wr = live ? w[row] - sum : 0.0;
+    __syncthreads();                                               // every wave has read w before wave 0 replaces it
+    if (wave == 0 && live) w[row] = wr;
+    if (alpha && blockIdx.x == 0 && threadIdx.x == 0) *alpha = h[ncols - 1];
+    if constexpr (LAST) {
+        const double v = wave_total(wr * wr);
+        if (threadIdx.x == 0) out[blockIdx.x] = v;
+    } else {
+        dot_parts(Q, ldq, row, live, wr, ncols, out);
+    }
+}
+
+// beta[j] = |w| from the blocks' parts, qnext = w / |w| (zero vector if |w| = 0): 256 rows per workgroup.
+__global__ void __launch_bounds__(256) k_step_scale(const double* __restrict__ w, uint32_t n, uint32_t nb,
+                                                    const double* __restrict__ parts, double* __restrict__ beta, uint32_t j,
+                                                    double* __restrict__ qnext) {
+    __shared__ double red[4];
+    const int lane = threadIdx.x & 63;
+    double v = 0.0;
+    for (uint32_t i = threadIdx.x; i < nb; i += 256) v += parts[i];
+    v = wave_total(v);
+    if (lane == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    const double nrm = sqrt((red[0] + red[1]) + (red[2] + red[3]));
+    if (blockIdx.x == 0 && threadIdx.x == 0) beta[j] = nrm;
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i >= n) return;
+    qnext[i] = w[i] * (nrm > 0.0 ? 1.0 / nrm : 0.0);
+}
+
 static inline uint32_t cdiv(uint64_t a, uint64_t b) { return uint32_t((a + b - 1) / b); }
 
 hipError_t launch_evolution_matrix(const SpecTable& tb, double L, double D, double sm, double t, double pref,
@@ -335,16 +468,43 @@ TileBand tile_band(uint32_t n, double dy, double t) {
     return TileBand{nb, bw};
 }
 
-hipError_t launch_symv_tiles(const double* M, const uint32_t* map, const TileBand& band, uint32_t n,
-                             const double* x, double* prow, double* pcol, double* y, hipStream_t st) {
-    if (n == 0 || band.nb != (n + kTile - 1) / kTile || band.bw >= band.nb) return hipErrorInvalidValue;
+static void enqueue_tiles(const double* M, const uint32_t* map, const TileBand& band, uint32_t n, const double* x,
+                          double* prow, double* pcol, hipStream_t st) {
     int ncu = 0, dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
         ncu = 256;
     const uint32_t ntiles = uint32_t(band.tiles());
     const uint32_t grid = std::min<uint32_t>(ntiles, uint32_t(kSymvBlocksPerCU * ncu));
     hipLaunchKernelGGL(k_symv_tiles, dim3(grid), dim3(256), 0, st, M, map, ntiles, n, x, prow, pcol);
-    hipLaunchKernelGGL(k_symv_reduce, dim3(band.nb), dim3(256), 0, st, prow, pcol, n, band, y);
+}
+
+size_t lanczos_scratch(uint32_t nb) { return nb <= kFuseBlocks ? size_t(nb) * (2 * kFuseCols + 1) : 0; }
+
+hipError_t launch_lanczos_step(const double* M, const uint32_t* map, const TileBand& band, uint32_t n, double* Q, uint64_t ldq,
+                               uint32_t j, double* prow, double* pcol, double* w, double* h, double* scratch, double* alpha,
+                               double* beta, hipStream_t st) {
+    if (n == 0 || band.nb != (n + kTile - 1) / kTile || band.bw >= band.nb) return hipErrorInvalidValue;
+    const uint32_t nb = band.nb, ncols = j + 1;
+    double* qnext = Q + uint64_t(j + 1) * ldq;
+    enqueue_tiles(M, map, band, n, Q + uint64_t(j) * ldq, prow, pcol, st);
+    if (ncols <= kFuseCols && nb <= kFuseBlocks) {
+        double* p1 = scratch;
+        double* p2 = p1 + size_t(nb) * kFuseCols;
+        double* pn = p2 + size_t(nb) * kFuseCols;
+        hipLaunchKernelGGL(k_step_rows, dim3(nb), dim3(kStepBlock), 0, st, prow, pcol, n, band, Q, ldq, ncols, w, p1);
+        hipLaunchKernelGGL(k_step_correct<false>, dim3(nb), dim3(kStepBlock), 0, st, Q, ldq, n, nb, ncols, p1, w, p2, alpha + j);
+        hipLaunchKernelGGL(k_step_correct<true>, dim3(nb), dim3(kStepBlock), 0, st, Q, ldq, n, nb, ncols, p2, w, pn,
+                           static_cast<double*>(nullptr));
+        hipLaunchKernelGGL(k_step_scale, dim3(cdiv(n, 256)), dim3(256), 0, st, w, n, nb, pn, beta, j, qnext);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(k_symv_reduce, dim3(nb), dim3(256), 0, st, prow, pcol, n, band, w);
+    for (int pass = 0; pass < 2; ++pass) {
+        hipLaunchKernelGGL(k_col_dots, dim3(ncols), dim3(256), 0, st, Q, ldq, n, w, h, pass == 0 ? alpha + j : nullptr, j);
+        hipLaunchKernelGGL(k_combine_cols, dim3(cdiv(n, 256)), dim3(256), 0, st, Q, ldq, n, ncols, h, w, 1);
+    }
+    hipLaunchKernelGGL(k_norm, dim3(1), dim3(256), 0, st, w, n, beta, j);
+    hipLaunchKernelGGL(k_scale_by_norm, dim3(cdiv(n, 256)), dim3(256), 0, st, w, n, beta, j, qnext);
     return hipGetLastError();
 }
 
@@ -355,21 +515,9 @@ hipError_t launch_gemv(const double* M, uint64_t ld, uint32_t n, const double* x
     return hipGetLastError();
 }
 
-hipError_t launch_col_dots(const double* Q, uint64_t ldq, uint32_t n, uint32_t ncols, const double* w, double* out,
-                           hipStream_t st, double* diag, uint32_t diag_col) {
-    hipLaunchKernelGGL(k_col_dots, dim3(ncols), dim3(256), 0, st, Q, ldq, n, w, out, diag, diag_col);
-    return hipGetLastError();
-}
-
 hipError_t launch_combine_cols(const double* Q, uint64_t ldq, uint32_t n, uint32_t ncols, const double* h, double* y,
                                int subtract, hipStream_t st) {
     hipLaunchKernelGGL(k_combine_cols, dim3(cdiv(n, 256)), dim3(256), 0, st, Q, ldq, n, ncols, h, y, subtract);
-    return hipGetLastError();
-}
-
-hipError_t launch_normalize(const double* w, uint32_t n, double* beta, uint32_t j, double* qnext, hipStream_t st) {
-    hipLaunchKernelGGL(k_norm, dim3(1), dim3(256), 0, st, w, n, beta, j);
-    hipLaunchKernelGGL(k_scale_by_norm, dim3(cdiv(n, 256)), dim3(256), 0, st, w, n, beta, j, qnext);
     return hipGetLastError();
 }
 

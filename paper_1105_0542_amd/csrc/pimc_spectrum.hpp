@@ -40,19 +40,19 @@ struct TileBand {
 TileBand tile_band(uint32_t n, double dy, double t);
 hipError_t launch_evolution_tiles(const SpecTable& tb, double L, double D, double sm, double t, double pref,
                                   uint32_t n, const uint32_t* map, uint32_t ntiles, double* M, hipStream_t st);
-// y = M x from the packed tiles: partial products per tile (prow, pcol: tiles * kTile doubles each)
-// then a fixed-order reduction per row block; x is read for indices < n only.
-hipError_t launch_symv_tiles(const double* M, const uint32_t* map, const TileBand& band, uint32_t n,
-                             const double* x, double* prow, double* pcol, double* y, hipStream_t st);
+// Step j of the Lanczos iteration: w = (1 - Q Q^T) M q_j with q_j = column j of Q (leading dimension ldq),
+// by classical Gram-Schmidt against columns 0..j, twice: in exact arithmetic the first pass removes
+// alpha_j q_j + beta_{j-1} q_{j-1} (the three-term recurrence) and nothing else, so alpha[j] = <q_j, M q_j>
+// is its coefficient of q_j; beta[j] = |w|, column j + 1 = w / beta[j]. The product goes by partial
+// products per tile (prow, pcol: tiles * kTile doubles each) added per row block; every sum has a fixed
+// order. w: n, h: j + 1, scratch: lanczos_scratch(nb) doubles.
+size_t lanczos_scratch(uint32_t nb);
+hipError_t launch_lanczos_step(const double* M, const uint32_t* map, const TileBand& band, uint32_t n, double* Q, uint64_t ldq,
+                               uint32_t j, double* prow, double* pcol, double* w, double* h, double* scratch, double* alpha,
+                               double* beta, hipStream_t st);
 // y = M x (ld even; M and x 16-byte aligned).
 hipError_t launch_gemv(const double* M, uint64_t ld, uint32_t n, const double* x, double* y, hipStream_t st);
-// out[c] = <Q_c, w>, c < ncols (Q_c = Q + c*ldq); with diag non-null also *diag = out[diag_col].
-hipError_t launch_col_dots(const double* Q, uint64_t ldq, uint32_t n, uint32_t ncols, const double* w, double* out,
-                           hipStream_t st, double* diag = nullptr, uint32_t diag_col = 0);
 // y = sum_c h[c] Q_c (subtract = 0) or y -= sum_c h[c] Q_c (subtract = 1).
 hipError_t launch_combine_cols(const double* Q, uint64_t ldq, uint32_t n, uint32_t ncols, const double* h, double* y,
                                int subtract, hipStream_t st);
-// beta[j] = |w|, qnext = w / beta[j].
-hipError_t launch_normalize(const double* w, uint32_t n, double* beta, uint32_t j, double* qnext, hipStream_t st);
-
 }  // namespace pimc

@@ -259,7 +259,7 @@ int pimc_spectrum(pimc_ctx* c, const pimc_potential* V, double m, double t, int 
     if ((st = dev_alloc(c, prb, size_t(ntiles) * kTile * 8))) return st;
     if ((st = dev_alloc(c, pcb, size_t(ntiles) * kTile * 8))) return st;
     if ((st = dev_alloc(c, Qb, size_t(ld) * (max_iter + 1) * 8))) return st;
-    if ((st = dev_alloc(c, wb, size_t(ld) * 8))) return st;
+    if ((st = dev_alloc(c, wb, (ld + lanczos_scratch(band.nb)) * 8))) return st;
     if ((st = dev_alloc(c, ab, size_t(max_iter) * 8))) return st;
     if ((st = dev_alloc(c, bb, size_t(max_iter) * 8))) return st;
     if ((st = dev_alloc(c, hb, size_t(max_iter + 1) * 8))) return st;
@@ -272,6 +272,7 @@ int pimc_spectrum(pimc_ctx* c, const pimc_potential* V, double m, double t, int 
     const uint32_t* dmap = static_cast<const uint32_t*>(mapb.p);
     double* prow = static_cast<double*>(prb.p);
     double* pcol = static_cast<double*>(pcb.p);
+    double* scratch = w + ld;
     HIP_TRY(c, hipMemcpyAsync(mapb.p, map.data(), map.size() * 4, hipMemcpyHostToDevice, c->stream));
     HIP_TRY(c, hipEventRecord(c->ev0, c->stream));
     if ((st = build_matrix(c, V, m, t, p, L, n, M, ld, tab, dmap, ntiles))) return st;
@@ -297,16 +298,7 @@ int pimc_spectrum(pimc_ctx* c, const pimc_potential* V, double m, double t, int 
     bool converged = false;
     const uint32_t check_every = 16;
     for (uint32_t j = 0; j < max_iter; ++j) {
-        double* qj = Q + uint64_t(j) * ld;
-        HIP_TRY(c, launch_symv_tiles(M, dmap, band, n, qj, prow, pcol, w, c->stream));
-        // w = (1 - Q Q^T) M q_j by classical Gram-Schmidt, twice: in exact arithmetic the first pass
-        // removes alpha_j q_j + beta_{j-1} q_{j-1} (the three-term recurrence) and nothing else, so
-        // alpha_j = <q_j, M q_j> is its coefficient of q_j, and beta_j = |w| afterwards
-        for (int pass = 0; pass < 2; ++pass) {
-            HIP_TRY(c, launch_col_dots(Q, ld, n, j + 1, w, h, c->stream, pass == 0 ? alpha + j : nullptr, j));
-            HIP_TRY(c, launch_combine_cols(Q, ld, n, j + 1, h, w, 1, c->stream));
-        }
-        HIP_TRY(c, launch_normalize(w, n, beta, j, Q + uint64_t(j + 1) * ld, c->stream));
+        HIP_TRY(c, launch_lanczos_step(M, dmap, band, n, Q, ld, j, prow, pcol, w, h, scratch, alpha, beta, c->stream));
         const uint32_t mm = j + 1;
         if (mm >= k + 1 && (mm % check_every == 0 || mm == max_iter)) {
             ha.resize(mm);

@@ -33,3 +33,41 @@ def test_energies_from_the_band_match_the_dense_matrix(n, m, t, L):
     ref = -np.log(lam[:k]) / t
     tol = (1e-10 + n * 2.0 ** -52) * lam[0] / (lam[:k] * t)
     assert np.all(np.abs(E - ref) <= tol), (E - ref, tol)
+
+
+# The steps of the iteration are fused up to 128 columns and 512 row blocks of 64: an iteration that runs
+# past 128 columns, and one with 514 row blocks. Same tolerance; for the second the residual itself, from
+# the full matrix: 1e-10 lambda_0 by construction plus n eps for the products on both sides.
+@pytest.mark.parametrize("n", [200, 333])
+def test_energies_after_more_columns_than_the_fused_steps_take(n):
+    import torch
+    k, t, L = 3, 0.0003, 2.0
+    coefs = [0.0, 0.2, 0.5, 0.0, 0.4]
+    with P.Context() as ctx:
+        M = torch.zeros(n, n, dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        ctx.evolution_matrix(coefs, 1.0, t, 6, L, n, M.data_ptr(), n)
+        lam = np.linalg.eigvalsh(M.cpu().numpy())[::-1]
+        E, _, info, _ = ctx.spectrum(coefs, 1.0, t, 6, L, n, k, max_iter=n)
+    assert info.converged == 1
+    assert info.iterations > 128
+    tol = (1e-10 + n * 2.0 ** -52) * lam[0] / (lam[:k] * t)
+    assert np.all(np.abs(E + np.log(lam[:k]) / t) <= tol)
+
+
+@pytest.mark.parametrize("n", [32768, 32833])
+def test_residual_at_the_largest_fused_size_and_beyond(n):
+    import torch
+    k, t = 2, 0.02
+    with P.Context() as ctx:
+        M = torch.zeros(n, n, dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        ctx.evolution_matrix(P.quartic(1.0, 48.0), 1.0, t, 8, 8.0, n, M.data_ptr(), n)
+        E, psi, info, _ = ctx.spectrum(P.quartic(1.0, 48.0), 1.0, t, 8, 8.0, n, k, want_psi=True)
+        assert info.converged == 1
+        y = torch.from_numpy(np.ascontiguousarray(psi)).cuda().reshape(k, n)
+        y = y / y.norm(dim=1, keepdim=True)
+        lam = np.exp(-t * np.asarray(E))
+        for i in range(k):
+            res = float((M @ y[i] - lam[i] * y[i]).norm())
+            assert res <= (1e-10 + n * 2.0 ** -52) * lam[0], (i, res)
