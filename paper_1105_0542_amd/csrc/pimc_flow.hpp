@@ -70,12 +70,14 @@ uint64_t flow_plane_ld(uint64_t batch);
 hipError_t launch_train_fwd(const FlowNet& net, const RngKey& key, const int* step, uint64_t n, int D, double* Xg,
                             uint64_t ld, uint64_t plane, double* hu2, double* logdet, hipStream_t st);
 // Training backward, last layer first, from G (d l / d z of the output, [h-1][path]; read only) and
-// alpha (per-path loss weights); writes the gradient planes for launch_flow_wgrad.
+// alpha (per-path loss weights); writes the gradient planes for launch_flow_wgrad_part.
 hipError_t launch_train_bwd(const FlowNet& net, const double* Xg, const double* G, uint64_t ld, uint64_t plane,
                             uint64_t n, int D, const double* alpha, const TrainPlanes& planes, hipStream_t st);
-// Parameter gradients [layer][kFlowNP] (FP32) from the planes, in a fixed order; part: scratch of
-// flow_wgrad_part_floats(layers) floats (per-slice partial sums).
-hipError_t launch_flow_wgrad(const TrainPlanes& planes, int layers, float* part, float* grad, hipStream_t st);
+// Parameter gradients [layer][kFlowNP] (FP32) from the planes, as partial sums over batch slices; part:
+// scratch of flow_wgrad_part_floats(layers) floats. With step, *step += 1. launch_flow_wgrad_sum adds
+// the slices of planes of leading dimension ld, in a fixed order.
+hipError_t launch_flow_wgrad_part(const TrainPlanes& planes, int layers, float* part, int* step, hipStream_t st);
+hipError_t launch_flow_wgrad_sum(const float* part, uint64_t ld, int layers, float* grad, hipStream_t st);
 size_t flow_wgrad_part_floats(int layers);
 // Level-s action of the paths in X (N <= 128), log weights ell and G = d ell / dz.
 hipError_t launch_flow_action_grad(const double* tab, const int* deg, int K, int even, const double* sig, double shift,
@@ -88,10 +90,10 @@ hipError_t launch_flow_partials(const double* ell, uint64_t ell_first_path, uint
                                 uint64_t n_chunks, double* partials, hipStream_t st);
 hipError_t launch_flow_alpha(const double* ell, uint64_t n, double beta, double* alpha, double* loss_out,
                              const int* step, hipStream_t st);
-hipError_t launch_adam(float* theta, float* m, float* v, const float* grad, int layers, const int* step, float lr,
+// One update from the slices' gradients, step *step (1, 2, ...).
+hipError_t launch_adam(float* theta, float* m, float* v, const float* part, uint64_t ld, int layers, const int* step, float lr,
                        __bf16* W1, __bf16* W2, __bf16* W1T, __bf16* W2T, hipStream_t st);
 hipError_t launch_params_to_bf16(const float* theta, int layers, __bf16* W1, __bf16* W2, __bf16* W1T, __bf16* W2T,
                                  hipStream_t st);
-hipError_t launch_step_inc(int* step, hipStream_t st);
 
 }  // namespace pimc

@@ -127,10 +127,10 @@ FlowLayerDev layer_dev(const pimc_flow* f, int c) {
     return L;
 }
 
-// Forward of every layer, the action, the loss weights, the backward and the parameter gradients
-// into d_grad. With step != null (training) the base stream and the loss slot follow the device
-// step counter.
-hipError_t enqueue_grad(pimc_flow* f, const RngKey& key, const int* step, double* loss) {
+// Forward of every layer, the action, the loss weights, the backward and the slices of the parameter
+// gradients into d_wpart. With step != null (training) the base stream and the loss slot follow the
+// device step counter, which counts the step in the last of these kernels.
+hipError_t enqueue_grad(pimc_flow* f, const RngKey& key, int* step, double* loss) {
     const Problem& P = f->P;
     const uint64_t B = f->B;
     const size_t plane = size_t(f->D) * B;
@@ -142,7 +142,7 @@ hipError_t enqueue_grad(pimc_flow* f, const RngKey& key, const int* step, double
                                     f->d_hu2, f->d_logdet, f->d_ell, f->d_G, st);
     if (e == hipSuccess) e = launch_flow_alpha(f->d_ell, B, f->beta, f->d_alpha, loss, step, st);
     if (e == hipSuccess) e = launch_train_bwd(f->net, f->d_X, f->d_G, B, plane, B, f->D, f->d_alpha, f->planes, st);
-    if (e == hipSuccess) e = launch_flow_wgrad(f->planes, f->L, f->d_wpart, f->d_grad, st);
+    if (e == hipSuccess) e = launch_flow_wgrad_part(f->planes, f->L, f->d_wpart, step, st);
     return e;
 }
 
@@ -161,9 +161,8 @@ int capture_step(pimc_flow* f, uint64_t seed, uint32_t stream_base) {
     HIP_TRY(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
     hipError_t e = enqueue_grad(f, key, f->d_step, f->d_loss);
     if (e == hipSuccess)
-        e = launch_adam(f->d_theta, f->d_m, f->d_v, f->d_grad, f->L, f->d_step, f->lr, f->d_W1, f->d_W2, f->d_W1T,
+        e = launch_adam(f->d_theta, f->d_m, f->d_v, f->d_wpart, f->planes.ld, f->L, f->d_step, f->lr, f->d_W1, f->d_W2, f->d_W1T,
                         f->d_W2T, c->stream);
-    if (e == hipSuccess) e = launch_step_inc(f->d_step, c->stream);
     hipGraph_t g = nullptr;
     const hipError_t e2 = hipStreamEndCapture(c->stream, &g);
     if (e != hipSuccess) {
@@ -442,6 +441,7 @@ int pimc_flow_grad(pimc_flow* f, uint64_t seed, uint32_t stream, double* loss, d
     HIP_TRY(c, hipSetDevice(c->device));
     const RngKey key{uint32_t(seed), uint32_t(seed >> 32), stream};
     HIP_TRY(c, enqueue_grad(f, key, nullptr, f->d_gloss));
+    HIP_TRY(c, launch_flow_wgrad_sum(f->d_wpart, f->planes.ld, f->L, f->d_grad, c->stream));
     HIP_TRY(c, hipMemcpyAsync(loss, f->d_gloss, 8, hipMemcpyDeviceToHost, c->stream));
     if (ell) HIP_TRY(c, hipMemcpyAsync(ell, f->d_ell, size_t(f->B) * 8, hipMemcpyDeviceToHost, c->stream));
     if (grad)
