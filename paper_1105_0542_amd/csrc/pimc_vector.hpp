@@ -113,21 +113,27 @@ inline size_t vec_lds_bytes(int dim, int D, int s) {
             size_t(kChunkSlots * (s + 1) * 3)) * sizeof(double);
 }
 
+// Bytes past the coefficients and past the structure stream that a kernel may read (not use).
+constexpr int kPolyPadBytes = 64;
 // Component evaluator (any polynomial V): a level-independent structure stream (A.shape, ints) and
 // per-level coefficient arrays (A.tab, A.stride doubles per level); layout in pimc_vector_impl.hpp,
 // PolyEvalRT.
 #ifndef PIMC_POLY_U
-#define PIMC_POLY_U 5
+#define PIMC_POLY_U 6
+#endif
+#ifndef PIMC_POLY_U1
+#define PIMC_POLY_U1 5
 #endif
 #ifndef PIMC_POLY_U3
 #define PIMC_POLY_U3 7
 #endif
-// Subtree levels of the component evaluator (1..7) in d = 1, 2 and in d = 3, 4: deeper than the radial
+// Subtree levels of the component evaluator (1..7) in d = 1, in d = 2 and in d = 3, 4: deeper than the radial
 // kernels' 3, because its cost is a pass over the structure per slice batch, and deeper subtrees give
 // fewer, wider batches (the points that do not fit the registers live in scratch).
 constexpr int kPolyU = PIMC_POLY_U;
+constexpr int kPolyU1 = PIMC_POLY_U1;
 constexpr int kPolyU3 = PIMC_POLY_U3;
-constexpr int poly_subtree_levels(int dim) { return dim >= 3 ? kPolyU3 : kPolyU; }
+constexpr int poly_subtree_levels(int dim) { return dim >= 3 ? kPolyU3 : (dim == 2 ? kPolyU : kPolyU1); }
 constexpr int kPolyMaxSlots = 1 << 20;  // coefficient slots per level
 
 // Launch the vector estimation kernel: dim 1..4; U = min(s, kVecU); `specialized` selects the

@@ -401,7 +401,9 @@ int stage_vector(pimc_ctx* c, const VecProblem& P, uint64_t seed, uint32_t strea
     const size_t off_shift = nlev * 8;
     const size_t off_tab = 2 * nlev * 8;
     const size_t off_shape = off_tab + n_tab * 8;
-    // the two work counters of the persistent kernel, zero, on a 256-byte line of their own
+    // the two work counters of the persistent kernel, zero, on a 256-byte line of their own (it also holds
+    // what the component evaluator reads past the end of the two arrays before it)
+    static_assert(kPolyPadBytes <= 256, "reads past the arrays end in the counters' line");
     const size_t off_queue = (off_shape + P.shape.size() * 4 + 255) & ~size_t(255);
     const size_t off_segs = off_queue + 256;
     const size_t total = off_segs + segs.size();

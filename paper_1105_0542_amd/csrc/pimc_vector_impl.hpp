@@ -188,14 +188,22 @@ struct RadialEvalRT {
 // Every count and exponent is wave-uniform (scalar loads through the constant address space), so the
 // depth-nested loops are scalar branches around B-wide vector FMAs; a_v and the running pointers have
 // one register home per depth (no interpreter dispatch, no copies between depths).
-#ifndef PIMC_POLY_UNROLL
-#define PIMC_POLY_UNROLL 4
-#endif
-constexpr int kPolyUnroll = PIMC_POLY_UNROLL;   // coefficients per scalar load group of a chain
+//
+// What bounds it is the latency of those scalar loads, not the FMAs (a chain has a few coefficients and
+// B = 8 slices). So the walk reads ahead: the next int of the stream is in a register when its node begins,
+// and the first kPolyAhead coefficients of the next chain are loaded while a chain is computed, a longer
+// chain's next group while its last one is. That reads up to kPolyAhead coefficients and one int past the
+// end of the arrays, within the buffer that holds both (kPolyPadBytes).
+// d = 2, p = 10, N = 256, 5e5 paths: 14.7 -> 13.6 ms (with two entries a word or indexes for pointers the
+// additional scalar work cost more than it hid: 16.1 and 18.5). One coordinate has few nodes and long chains
+// and reads as it goes (p = 9, N = 256: 566 us, 588 reading ahead).
+constexpr int kPolyAhead = 4;                   // coefficients per scalar load group of a chain
+static_assert(kPolyAhead * sizeof(double) <= kPolyPadBytes, "reads past the arrays stay in their buffer");
 
 template <int DIM>
 struct PolyEvalRT {
     static constexpr int NV = 2 * DIM;
+    static constexpr bool kAhead = DIM > 1;
     const double* __restrict__ tab;      // coefficients, level-major, stride doubles per level
     const int* __restrict__ code;        // structure stream
     int stride;
@@ -218,58 +226,105 @@ struct PolyEvalRT {
         }
     }
 
+    struct Walk {
+        const_ptr<int> s;          // next int to load
+        const_ptr<double> c;       // next chain's coefficients
+        int nx;                    // the int before s
+        double cq[kPolyAhead];     // the next chain's first coefficients
+        __device__ __forceinline__ int take() {
+            if constexpr (!kAhead) {
+                s += 1;
+                return s[-1];
+            }
+            const int v = nx;
+            nx = s[0];
+            s += 1;
+            return v;
+        }
+        __device__ __forceinline__ void ahead() {
+            if constexpr (kAhead) {
+#pragma unroll
+                for (int q = 0; q < kPolyAhead; ++q) cq[q] = c[q];
+            }
+        }
+    };
+
+    // out = out y + k[q], q = FIRST .. n - 1 (n <= kPolyAhead, wave-uniform).
+    template <int FIRST, int B>
+    __device__ __forceinline__ static void chain_group(const double (&k)[kPolyAhead], int n, const double (&y)[B],
+                                                       double (&out)[B]) {
+        if constexpr (FIRST < kPolyAhead) {
+            if (n <= FIRST) return;
+#pragma unroll
+            for (int i = 0; i < B; ++i) out[i] = fma(out[i], y[i], k[FIRST]);
+            chain_group<FIRST + 1, B>(k, n, y, out);
+        }
+    }
+
     // The node's value into out. A chain starts from its first coefficient and a node of the two
     // deepest internal levels from its first child's value (the same bits as starting from 0:
     // fma(0, y, t) = t); every node has at least one child and every chain at least one coefficient.
     template <int V, int B>
-    __device__ __forceinline__ static void node(const_ptr<int>& s, const_ptr<double>& c, const double (&y)[NV][B],
-                                                double (&out)[B]) {
+    __device__ __forceinline__ static void node(Walk& w, const double (&y)[NV][B], double (&out)[B]) {
         if constexpr (V == NV - 1) {
-            const int L = s[0];
-            s += 1;
-            const double c0 = c[0];
+            const int L = w.take();
+            if constexpr (!kAhead) {
+                const const_ptr<double> c = w.c;
+                w.c += L;
+                const double c0 = c[0];
 #pragma unroll
-            for (int i = 0; i < B; ++i) out[i] = c0;
-            int j = 1;
-            for (; j + kPolyUnroll <= L; j += kPolyUnroll) {
-                double cq[kPolyUnroll];
+                for (int i = 0; i < B; ++i) out[i] = c0;
+                int j = 1;
+                for (; j + kPolyAhead <= L; j += kPolyAhead) {
+                    double k[kPolyAhead];
 #pragma unroll
-                for (int q = 0; q < kPolyUnroll; ++q) cq[q] = c[j + q];
+                    for (int q = 0; q < kPolyAhead; ++q) k[q] = c[j + q];
 #pragma unroll
-                for (int q = 0; q < kPolyUnroll; ++q) {
+                    for (int q = 0; q < kPolyAhead; ++q)
 #pragma unroll
-                    for (int i = 0; i < B; ++i) out[i] = fma(out[i], y[V][i], cq[q]);
+                        for (int i = 0; i < B; ++i) out[i] = fma(out[i], y[V][i], k[q]);
                 }
-            }
-            for (; j < L; ++j) {
-                const double c1 = c[j];
+                for (; j < L; ++j) {
+                    const double c1 = c[j];
 #pragma unroll
-                for (int i = 0; i < B; ++i) out[i] = fma(out[i], y[V][i], c1);
+                    for (int i = 0; i < B; ++i) out[i] = fma(out[i], y[V][i], c1);
+                }
+                return;
             }
-            c += L;
+            double k[kPolyAhead];
+#pragma unroll
+            for (int q = 0; q < kPolyAhead; ++q) k[q] = w.cq[q];
+            const const_ptr<double> c = w.c;
+            w.c += L;
+            w.ahead();
+#pragma unroll
+            for (int i = 0; i < B; ++i) out[i] = k[0];
+            chain_group<1, B>(k, L, y[V], out);
+            for (int j = kPolyAhead; j < L; j += kPolyAhead) {
+#pragma unroll
+                for (int q = 0; q < kPolyAhead; ++q) k[q] = c[j + q];
+                chain_group<0, B>(k, L - j, y[V], out);
+            }
         } else {
-            const int n = s[0];
+            const int n = w.take();
             int k = 0;
             if constexpr (V >= NV - 3) {
                 // the two deepest internal levels (most of the nodes) let the first child write the
                 // accumulator; above them it is zeroed, which keeps one copy of a child's code per
                 // level instead of two (2^(2 DIM - 1) copies of the chain loop when peeled throughout)
-                const int h0 = s[1];
-                s += 2;
-                node<V + 1, B>(s, c, y, out);
+                const int h0 = w.take();
+                node<V + 1, B>(w, y, out);
                 times_pow<B>(out, y[V + 1], h0 >> 8);
                 k = 1;
             } else {
-                s += 1;
 #pragma unroll
                 for (int i = 0; i < B; ++i) out[i] = 0.0;
             }
             for (; k < n; ++k) {
-                const int h = s[0];
-                s += 1;
+                const int h = w.take();
                 times_pow<B>(out, y[V], (h & 255) - 1);
                 double t[B];
-                node<V + 1, B>(s, c, y, t);
+                node<V + 1, B>(w, y, t);
                 times_pow<B>(t, y[V + 1], h >> 8);
 #pragma unroll
                 for (int i = 0; i < B; ++i) fma_into(out[i], y[V][i], t[i]);
@@ -281,8 +336,11 @@ struct PolyEvalRT {
     __device__ __forceinline__ void eval(int level, const double (&qa)[B][DIM], const double (&qb)[B][DIM],
                                          double& S) const {
         const int lv = __builtin_amdgcn_readfirstlane(level);
-        const_ptr<double> c = as_const(tab) + lv * stride;
-        const_ptr<int> s = as_const(code);
+        Walk w;
+        w.c = as_const(tab) + lv * stride;
+        w.s = as_const(code) + (kAhead ? 1 : 0);
+        w.nx = kAhead ? as_const(code)[0] : 0;
+        w.ahead();
         double y[NV][B];
 #pragma unroll
         for (int i = 0; i < B; ++i) {
@@ -292,10 +350,9 @@ struct PolyEvalRT {
                 y[DIM + k][i] = qa[i][k] + qb[i][k];
             }
         }
-        const int tail = s[0];
-        s += 1;
+        const int tail = w.take();
         double v[B];
-        node<0, B>(s, c, y, v);
+        node<0, B>(w, y, v);
         times_pow<B>(v, y[0], tail);
 #pragma unroll
         for (int i = 0; i < B; ++i) S += v[i];
@@ -356,6 +413,70 @@ __device__ __forceinline__ void hier_levels(const Eval& ev, int D, const double 
     }
 }
 
+// The component evaluator is a long instruction sequence, and a copy of it (and of the normals) per batch of
+// a subtree is far more than the instruction cache holds: its subtrees are loops over the levels, with one
+// copy per batch width and the points in scratch memory. d = 2, p = 10, N = 256, 5e5 paths: 13.6 -> 12.1 ms (with
+// subtrees of six levels; of five 13.7, and of five without the loops 13.6), p = 8 2.11 -> 1.83; d = 3, p = 5,
+// N = 128, 5e4 paths 1.23 -> 1.12 ms. One coordinate is faster unrolled (N = 128, p = 9, level s alone 362 us,
+// 465 in loops), and four (N = 128, p = 4: 0.76 ms, 1.14).
+template <class Eval> constexpr bool kRolled = false;
+template <int DIM> constexpr bool kRolled<PolyEvalRT<DIM>> = DIM == 2 || DIM == 3;
+
+template <int DIM, int U, int B, class Eval>
+__device__ __forceinline__ void rolled_batch(const Eval& ev, int level, int sh, int b0,
+                                             const double (&q)[(1 << U) + 1][DIM], double& S) {
+    double qa[B][DIM], qb[B][DIM];
+#pragma unroll
+    for (int i = 0; i < B; ++i)
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) {
+            qa[i][c] = i == 0 ? q[b0 << sh][c] : qb[i - 1][c];
+            qb[i][c] = q[(b0 + i + 1) << sh][c];
+        }
+    ev.template eval<B>(level, qa, qb, S);
+}
+
+template <int DIM, int U, class Eval>
+__device__ __forceinline__ void rolled_levels(const Eval& ev, const VecArgs& A, const VecSource<DIM>& src, uint32_t root,
+                                              int D, double (&q)[(1 << U) + 1][DIM], double (&Ssub)[U + 1]) {
+#pragma unroll 1
+    for (int L = 2; L <= U; ++L) {
+        const int step = 1 << (U - L);
+        const double sg = as_const(A.sig)[D + L];
+#pragma unroll 1
+        for (int i2 = 0; i2 < (1 << (L - 2)); ++i2) {
+            double ze[DIM], zo[DIM];
+            src.pair((root << (L - 2)) + uint32_t(i2), ze, zo);
+            const int jl = (4 * i2 + 1) * step;
+            const int jr = (4 * i2 + 3) * step;
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) {
+                q[jl][c] = sg * ze[c] + 0.5 * (q[jl - step][c] + q[jl + step][c]);
+                q[jr][c] = sg * zo[c] + 0.5 * (q[jr - step][c] + q[jr + step][c]);
+            }
+        }
+    }
+    static_assert(kVecBatch == 8, "widths below");
+#pragma unroll 1
+    for (int L = A.hier ? 0 : U; L <= U; ++L) {
+        double S = Ssub[L];
+        if (L == 0) {
+            rolled_batch<DIM, U, 1>(ev, D, U, 0, q, S);
+        } else if (L == 1) {
+            rolled_batch<DIM, U, 2>(ev, D + 1, U - 1, 0, q, S);
+        } else if (L == 2) {
+            if constexpr (U >= 2) rolled_batch<DIM, U, 4>(ev, D + 2, U - 2, 0, q, S);
+        } else {
+            if constexpr (U >= 3) {
+#pragma unroll 1
+                for (int b0 = 0; b0 < (1 << L); b0 += kVecBatch)
+                    rolled_batch<DIM, U, kVecBatch>(ev, D + L, U - L, b0, q, S);
+            }
+        }
+        Ssub[L] = S;
+    }
+}
+
 // Subtree rooted at heap node `root` (level D+1) over the level-D slice (qL, qR) with root normal z.
 template <int DIM, int U, class Eval>
 __device__ __forceinline__ void run_subtree(const Eval& ev_in, const VecArgs& A, const VecSource<DIM>& src,
@@ -370,6 +491,10 @@ __device__ __forceinline__ void run_subtree(const Eval& ev_in, const VecArgs& A,
         q[0][c] = qL[c];
         q[1 << U][c] = qR[c];
         q[1 << (U - 1)][c] = sg * zroot[c] + 0.5 * (qL[c] + qR[c]);
+    }
+    if constexpr (kRolled<Eval>) {
+        rolled_levels<DIM, U, Eval>(ev, A, src, root, D, q, Ssub);
+        return;
     }
     gen_level<DIM, U, 2>(A, src, root, D, q);
     if (A.hier) hier_levels<DIM, U, 0, Eval>(ev, D, q, Ssub);
@@ -395,13 +520,15 @@ __device__ __forceinline__ void walk_path(const Eval& ev, const VecArgs& A, cons
         double unused[DIM];
         src.pair(0u, unused, z1);                    // node 1 = sine output of call 0
     }
-    if (D == 0) {
-        run_subtree<DIM, U, Eval>(ev, A, src, 1u, 0, a, b, z1, Ssub);
-        return;
+    if constexpr (!kRolled<Eval>) {
+        if (D == 0) {
+            run_subtree<DIM, U, Eval>(ev, A, src, 1u, 0, a, b, z1, Ssub);
+            return;
+        }
     }
     for (int n = 0; n < D; ++n) top[n * kVecBlock] = 0.0;
     double* R = top + D * kVecBlock;
-    const uint32_t nTop = 1u << (D - 1);             // level-D nodes nTop .. 2 nTop - 1
+    const uint32_t nTop = D > 0 ? 1u << (D - 1) : 1u;    // level-D nodes nTop .. 2 nTop - 1
     double qlast[DIM];
 #pragma unroll
     for (int c = 0; c < DIM; ++c) qlast[c] = a[c];
@@ -428,7 +555,7 @@ __device__ __forceinline__ void walk_path(const Eval& ev, const VecArgs& A, cons
             src.node(node, z);
         }
         double qm[DIM], zl[DIM], zr[DIM];
-        while (true) {
+        while (!kRolled<Eval> || D > 0) {
             if (A.hier) {
                 double qa1[1][DIM], qb1[1][DIM];
 #pragma unroll
@@ -454,8 +581,23 @@ __device__ __forceinline__ void walk_path(const Eval& ev, const VecArgs& A, cons
             node = 2u * node;
             ++L;
         }
-        run_subtree<DIM, U, Eval>(ev, A, src, 2u * node, D, qL, qm, zl, Ssub);
-        run_subtree<DIM, U, Eval>(ev, A, src, 2u * node + 1u, D, qm, qR, zr, Ssub);
+        if constexpr (kRolled<Eval>) {               // one copy: both sides, or the whole tree (D = 0)
+            const int sides = D > 0 ? 2 : 1;
+#pragma unroll 1
+            for (int side = 0; side < sides; ++side) {
+                double l[DIM], r[DIM], zs[DIM];
+#pragma unroll
+                for (int c = 0; c < DIM; ++c) {
+                    l[c] = side == 0 ? qL[c] : qm[c];
+                    r[c] = side == 0 && D > 0 ? qm[c] : qR[c];
+                    zs[c] = D == 0 ? z[c] : (side == 0 ? zl[c] : zr[c]);
+                }
+                run_subtree<DIM, U, Eval>(ev, A, src, D > 0 ? 2u * node + uint32_t(side) : 1u, D, l, r, zs, Ssub);
+            }
+        } else {
+            run_subtree<DIM, U, Eval>(ev, A, src, 2u * node, D, qL, qm, zl, Ssub);
+            run_subtree<DIM, U, Eval>(ev, A, src, 2u * node + 1u, D, qm, qR, zr, Ssub);
+        }
 #pragma unroll
         for (int c = 0; c < DIM; ++c) qlast[c] = qR[c];
     }

@@ -1,10 +1,10 @@
 // Vector estimation kernels of the component evaluator (any polynomial V) for one dimension,
 // chosen at build time by PIMC_POLY_DIM (this file is compiled once per dimension, in parallel:
-// subtrees of up to kPolyU levels make these the largest kernels of the vector mode). With
+// subtrees of up to kPolyU1 (kPolyU, kPolyU3) levels make these the largest kernels of the vector mode). With
 // PIMC_POLY_DEEP it holds only the deepest subtree of that dimension, when that is kPolySplitU
 // levels or more, so that the deepest and the shallower kernels compile in parallel.
 // One and two coordinates are built without loop-invariant code motion on machine code (as
-// pimc_general_inline.hip): 6e5 paths, N = 256, d = 1, p = 8 1.10 -> 1.00 ms; d = 2, p = 10 14.9 -> 14.6; three
+// pimc_general_inline.hip): 6e5 paths, N = 256, d = 1, p = 8 1.10 -> 1.00 ms; d = 2, p = 10 14.9 -> 14.6 (before its levels were loops); three
 // and four coordinates the same with and without.
 #include "pimc_vector_impl.hpp"
 
