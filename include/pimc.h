@@ -338,7 +338,8 @@ int pimc_batch_run(pimc_batch *batch, pimc_level_result *out, double *ms);
 int pimc_batch_run_to(pimc_batch *batch, pimc_level_result *out, int out_on_device, double *ms);
 
 /* Scheduling of the persistent kernels: grid = resident workgroups * grid_mult_x2 / 2
- * (grid_mult_x2 in 1..8), each queue grab takes `grab` consecutive chunks (1..64). Changes only
+ * (grid_mult_x2 in 1..8), each queue grab takes `grab` consecutive items (1..64): canonical chunks, or
+ * a few groups of 64 paths where those sums of the batch are small. Changes only
  * scheduling: results are bitwise identical for every setting. Re-captures the graph. */
 int pimc_batch_set_tuning(pimc_batch *batch, int grid_mult_x2, uint32_t grab);
 
