@@ -85,7 +85,7 @@ HBM_PEAK_GBS = 8000.0
 # Modified Poeschl-Teller potential (the paper's Fig. 2): V = -lambda/cosh^2(alpha q), lambda = alpha = 1,
 # A_N^(p)(-0.5, 0.5; 1) for p in {1, 2, 10} from one s = 10 run each (every N = 2^0..2^10).
 MPT = dict(lam=1.0, alpha=1.0, a=-0.5, b=0.5, T=1.0, s=10, ps=(1, 2, 10), samples=100_000_000)
-KERNEL_SOURCES = ["pimc_device.hpp", "pimc_kernels_q64.hip", "pimc_walker.hpp", "pimc_internal.hpp", "pimc_tables.hpp",
+KERNEL_SOURCES = ["pimc_device.hpp", "pimc_kernels_q64.hip", "pimc_walker.hpp", "pimc_chunks.hpp", "pimc_internal.hpp", "pimc_tables.hpp",
                   "pimc_math.hpp"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_k_amplitude_quartic64_p18_s10.json")
 COUNTERS_FILE = os.path.join(ROOT, "profiles", "counters_k_amplitude_quartic64_p18_s10.json")
@@ -468,6 +468,15 @@ def component_rows(P, ctx, base=None):
     return rows
 
 
+def spectrum_elements(n, dy, t):
+    """Distinct elements in the tiles that the eigenvalue iteration keeps (pimc_spectrum.hip, tile_band)."""
+    nb, bw = -(-n // 64), -(-n // 64) - 1
+    reach = math.sqrt(2.0 * t * 40.0 * (1.0 + 1e-6)) / dy
+    if reach < n:
+        bw = min(bw, int((max(reach, 1.0) - 1.0) / 64) + 1)
+    return sum(min(bw + 1, nb - i) for i in range(nb)) * 64 * 64 - nb * 64 * 63 // 2
+
+
 def spectrum_section(P, ctx, dvr, base=None):
     """Matrix build (ALU: level-p Horner + exp per element) and Lanczos (HBM: one pass over the
     matrix per step) for the spectrum workloads; levels against the DVR reference when given."""
@@ -479,8 +488,9 @@ def spectrum_section(P, ctx, dvr, base=None):
                                       tol=1e-10)
         tab, deg, _ = P.level_table(coefs, 1.0, case["t"], SPEC_P, 0)
         flop_el = 2 * (tab.size - 1) + 10          # Horner over the table, mid/dlt/squares, Gaussian term
-        # the matrix is exactly symmetric: n(n+1)/2 distinct elements are built and streamed per step
-        n2 = float(SPEC_N) * (SPEC_N + 1) / 2.0
+        # the matrix is exactly symmetric and zero beyond the cut: the distinct elements of the upper 64x64
+        # tiles that the cut leaves are built and streamed per step
+        n2 = float(spectrum_elements(SPEC_N, 2.0 * case["L"] / SPEC_N, case["t"]))
         mat_tflops = n2 * flop_el / (info.matrix_ms / 1e3) / 1e12
         bytes_iter = n2 * 8.0
         row = {"workload": f"{case['name']}, t={case['t']:g}, L={case['L']:g}, n={SPEC_N}, p={SPEC_P}",
@@ -494,8 +504,8 @@ def spectrum_section(P, ctx, dvr, base=None):
                "lanczos_stream_GBs": bytes_iter * info.iterations / (info.solve_ms / 1e3) / 1e9,
                "lanczos_ms_per_step": info.solve_ms / max(info.iterations, 1),
                "lanczos_note": "solve time includes the reorthogonalization and host checks every 16 steps; "
-                               "the matrix pass alone is bound by HBM (the upper 64x64 tiles, 1.08 GB per "
-                               "step at n = 16384); rates count the n(n+1)/2 distinct elements"}
+                               "the matrix pass alone is bound by memory (the upper 64x64 tiles within the cut); "
+                               "rates count their distinct elements", "matrix_bytes_per_step": bytes_iter}
         if dvr is not None:
             ref = np.asarray(dvr[ci])
             row["max_abs_diff_vs_dvr"] = float(np.max(np.abs(np.asarray(E) - ref)))
