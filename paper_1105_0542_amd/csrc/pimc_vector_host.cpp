@@ -95,7 +95,8 @@ IPoly der_z(const IPoly& f) {
     return out;
 }
 
-// y += s u^pu z^pz f g
+// y += s u^pu z^pz f g. The products of terms only: an entry that is zero is no term, also beside one
+// that left the FP64 range (its product with zero is not a number, and might lie outside the table's shape).
 void mul_acc(IPoly& y, double s, const IPoly& f, const IPoly& g, int pu = 0, int pz = 0) {
     if (!f.nb || !g.nb) return;
     y.grow(f.nb + g.nb - 1 + pz, f.nu + g.nu - 1 + pu);
@@ -106,7 +107,7 @@ void mul_acc(IPoly& y, double s, const IPoly& f, const IPoly& g, int pu = 0, int
             for (int e = 0; e < g.nb && b + e + pz < y.nb; ++e) {
                 const double* src = g.row(e);
                 double* dst = y.row(b + e + pz) + i + pu;
-                for (int j = 0; j < g.nu; ++j) dst[j] += v * src[j];
+                for (int j = 0; j < g.nu; ++j) dst[j] += src[j] == 0.0 ? 0.0 : v * src[j];
             }
         }
 }
