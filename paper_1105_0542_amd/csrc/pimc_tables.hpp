@@ -206,9 +206,31 @@ inline std::vector<int> table_xdegrees(const Coefficients& C) {
     return xdeg;
 }
 
+// Action of one slice from a folded table, in the order of the kernels (Horner in u, then in dlt^2).
+inline double slice_action(const LevelTable& t, double qa, double qb) {
+    const double mid = 0.5 * (qa + qb);
+    const double z = (qb - qa) * (qb - qa);
+    double u = t.even ? mid * mid : mid;
+    if (t.tanh_alpha > 0.0) {
+        const double y = std::tanh(t.tanh_alpha * mid);
+        u = y * y;
+    }
+    double acc = 0.0;
+    size_t off = t.coef.size();
+    for (size_t k = t.deg.size(); k-- > 0;) {
+        off -= size_t(t.deg[k]) + 1;
+        double v = t.coef[off];
+        for (int e = 1; e <= t.deg[k]; ++e) v = v * u + t.coef[off + size_t(e)];
+        acc = k + 1 == t.deg.size() ? v : acc * z + v;
+    }
+    return acc;
+}
+
 // Potential part of eq.(SNp) on the straight line from a to b at this level (2^n slices): the reference
 // action, and at n = 0 the analytic level-0 exponent. The deviation is the same in every slice, so the
-// P_k are first added up with their powers of dlt^2; a slice is then one polynomial.
+// P_k are first added up with their powers of dlt^2; a slice is then one polynomial. Where that leaves the
+// FP64 range the slices are taken as the kernels take them: the sum is nan where they are (an infinity
+// would be a level-0 amplitude of 0), and finite where only the added-up coefficients are not.
 inline double straight_line_action(const LevelTable& t, double a, double b, int n) {
     const int N = 1 << n;
     const double dl = (b - a) / double(N);
@@ -240,6 +262,10 @@ inline double straight_line_action(const LevelTable& t, double a, double b, int 
             for (int i = 0; i < W; ++i) v[i] = v[i] * u[i] + R[e];
         for (int i = 0; i < W && k0 + i < N; ++i) acc += v[i];
     }
+    if (std::isfinite(acc)) return acc;
+    acc = 0.0;
+    for (int k = 0; k < N; ++k)
+        acc += slice_action(t, a + (b - a) * double(k) / double(N), a + (b - a) * double(k + 1) / double(N));
     return acc;
 }
 

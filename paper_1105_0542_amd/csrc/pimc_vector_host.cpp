@@ -246,8 +246,36 @@ bool fold_radial(const std::vector<std::vector<IPoly>>& W, const std::vector<Gro
     return true;
 }
 
+// Action of one slice (midpoint x, half deviation xb) from an unscaled table, in the order of the kernels:
+// Horner in u, z, w^2.
+double radial_slice(const std::vector<double>& tab, const std::vector<Group>& groups, const double* x, const double* xb,
+                    int d) {
+    double u = 0.0, w = 0.0, z = 0.0;
+    for (int c = 0; c < d; ++c) {
+        u = std::fma(x[c], x[c], u);
+        w = std::fma(x[c], xb[c], w);
+        z = std::fma(xb[c], xb[c], z);
+    }
+    double acc = 0.0;
+    size_t g = 0;
+    for (int j = groups.empty() ? -1 : groups[0].j; j >= 0; --j) {
+        double zs = 0.0;
+        for (bool first = true; g < groups.size() && groups[g].j == j; ++g, first = false) {     // l from high to low
+            double v = 0.0;
+            for (int e = 0; e < groups[g].len; ++e) {
+                const double c = tab[size_t(groups[g].off + e)];
+                v = e ? std::fma(v, u, c) : c;
+            }
+            zs = first ? v : std::fma(zs, z, v);
+        }
+        acc = j == groups[0].j ? zs : std::fma(acc, w * w, zs);
+    }
+    return acc;
+}
+
 // Level action of the straight line from a to b (2^n slices) from an unscaled table. The deviation is the
-// same in every slice: the Q_{k,j} of one j are first added up with their powers of z = xbar.xbar.
+// same in every slice: the Q_{k,j} of one j are first added up with their powers of z = xbar.xbar. Where that
+// leaves the FP64 range, slice by slice (as straight_line_action).
 double radial_line_action(const std::vector<double>& tab, const std::vector<Group>& groups, int p, const double* a,
                           const double* b, int d, int n) {
     const int N = 1 << n, nj = radial_nj(p);
@@ -287,6 +315,18 @@ double radial_line_action(const std::vector<double>& tab, const std::vector<Grou
             for (int i = 0; i < L; ++i) acc[i] = acc[i] * w2[i] + v[i];
         }
         for (int i = 0; i < L && k0 + i < N; ++i) S += acc[i];
+    }
+    if (std::isfinite(S)) return S;
+    S = 0.0;
+    for (int k = 0; k < N; ++k) {
+        double x[kVecMaxDim], h[kVecMaxDim];
+        for (int c = 0; c < d; ++c) {
+            const double q0 = a[c] + (b[c] - a[c]) * double(k) / double(N);
+            const double q1 = a[c] + (b[c] - a[c]) * double(k + 1) / double(N);
+            x[c] = 0.5 * (q0 + q1);
+            h[c] = 0.5 * (q1 - q0);
+        }
+        S += radial_slice(tab, groups, x, h, d);
     }
     return S;
 }
