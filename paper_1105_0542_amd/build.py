@@ -21,7 +21,7 @@ SOURCES = ["pimc_batch_p18.hip", "pimc_batch_p12.hip", "pimc_batch_p8.hip",
            "pimc_vector_d2.hip", "pimc_vector_d3.hip", "pimc_vector_d4.hip", "pimc_general_kernels.hip",
            "pimc_kernels.hip", "pimc_flow.hip", "pimc_spectrum.hip", "pimc_vector_d1.hip", "pimc_host.cpp", "pimc_flow_host.cpp", "pimc_spectrum_host.cpp",
            "pimc_general_host.cpp", "pimc_vector_host.cpp", "pimc_noalloc.cpp"]
-HEADERS = ["pimc_tables.hpp", "pimc_device.hpp", "pimc_internal.hpp", "pimc_math.hpp", "pimc_walker.hpp", "pimc_chunks.hpp",
+HEADERS = ["pimc_tables.hpp", "pimc_device.hpp", "pimc_internal.hpp", "pimc_math.hpp", "pimc_walker.hpp", "pimc_chunks.hpp", "pimc_split.hpp",
            "pimc_flow.hpp", "pimc_host_common.hpp", "pimc_spectrum.hpp", "pimc_general.hpp",
            "pimc_general_device.hpp", "pimc_vector.hpp", "pimc_vector_impl.hpp", "pimc_batch.hpp"]
 # Build-time generator of the general-potential evaluators: host C++ (the recursion of pimc_general.hpp)
@@ -46,9 +46,12 @@ VARIANTS += [("pimc_vector_poly.hip", [f"-DPIMC_POLY_DIM={d}", "-DPIMC_POLY_DEEP
 # -ffp-contract=off: every fused multiply-add in the kernels is written as fma(); no other
 # expression is contracted, so the arithmetic is exactly what the source states.
 # -packed-fp32-ops: packed FP32 instructions are not generated.
+# Atomic optimizer off: it brings the result of every atomic into scalar registers at once, and so waits for a
+# work ticket where it is asked for instead of where it is used, a walk later (pimc_chunks.hpp).
 HIP_FLAGS = [
     "-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-ffp-contract=off",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+    "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
     "-Wall", "-Wno-unused-function",
 ]
 

@@ -27,47 +27,56 @@ using BatchDefaultN16 = ShapeList<DefaultShape<4>>;
 // Persistent kernel over the items of one class (level p, launch shape), numbered task by task (task t
 // owns items item0[t] .. item0[t+1] - 1), so an item maps to its task by binary search over the
 // wave-uniform task records. An item is
-//   * by group (small batches): `block` consecutive groups, taken by one wave, whose sums are stored and
-//     added into the chunk records afterwards (pimc_chunks.hpp: the same sums as any other split). A
+//   * by group (classes of few chunks): `block` consecutive groups, taken by one wave, whose sums are stored
+//     and added into the chunk records afterwards (pimc_chunks.hpp: the same sums as any other split). A
 //     task of 20,000 paths has 5 chunks, a class of 85 such tasks 425 of them for 512 resident
-//     workgroups, those with N = 512 16 times as long as those with N = 32;
-//   * a whole chunk (large batches, whose group sums would not fit), taken by a workgroup.
-// Items are taken `grab` at a time from an atomic counter until it passes n_items; every wave (by
+//     workgroups, those with N = 512 16 times as long as those with N = 32. The first n_static items are
+//     dealt to the waves in turn;
+//   * a whole chunk (every other class), taken by a workgroup.
+// The other items are taken `grab` at a time from an atomic counter until it passes n_items; every wave (by
 // group) or workgroup (by chunk) reaches the exit test with one value.
-template <class S, class Eval>
+// Two kernels: in one the branches cost the chunks 3 % (4 tasks of 2e7 paths, N = 16, p = 4: 2.77 and 2.86 ms).
+template <class S, class Eval, bool BY_GROUP>
 __global__ void __launch_bounds__(S::BS) __attribute__((amdgpu_waves_per_eu(S::WPE)))
-k_batch(const BatchTask* __restrict__ tasks, int n_tasks, uint64_t n_items, unsigned long long* queue,
-        uint32_t grab, int by_group, RngKey key, int hier, Eval ev0) {
+k_batch(BatchArgs B, Eval ev0) {
     extern __shared__ double smem[];
     __shared__ unsigned long long s_item;
     constexpr int WAVES = S::BS / 64;
-    const const_ptr<BatchTask> T = as_const(tasks);
+    const const_ptr<BatchTask> T = as_const(B.tasks);
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     load_bm_table(smem, S::BS);
     __syncthreads();
     auto take = [&]() -> unsigned long long {
         unsigned long long t = 0;
-        if ((tid & 63) == 0) t = atomicAdd(queue, (unsigned long long)grab);
+        if ((tid & 63) == 0) t = atomicAdd(B.queue, (unsigned long long)B.grab);
         return t;
     };
-    unsigned long long ticket = by_group ? take() : 0ull;
+    uint64_t deal = uint64_t(blockIdx.x) * WAVES + uint64_t(wave);
+    unsigned long long ticket = 0;
+    if (BY_GROUP && B.n_static < B.n_items) ticket = take();
     while (true) {
-        uint64_t first;
-        if (by_group) {
-            first = uniform_u64(ticket);
-            if (first >= n_items) break;
-            ticket = take();
+        uint64_t first, end;
+        if (BY_GROUP && deal < B.n_static) {
+            first = deal;
+            end = deal + 1;
+            deal += uint64_t(gridDim.x) * WAVES;
         } else {
-            __syncthreads();
-            if (tid == 0) s_item = atomicAdd(queue, (unsigned long long)grab);
-            __syncthreads();
-            first = uniform_u64(s_item);
-            if (first >= n_items) break;
+            if (BY_GROUP) {
+                first = B.n_static + uniform_u64(ticket);
+                if (first >= B.n_items) break;
+                ticket = take();
+            } else {
+                __syncthreads();
+                if (tid == 0) s_item = atomicAdd(B.queue, (unsigned long long)B.grab);
+                __syncthreads();
+                first = uniform_u64(s_item);
+                if (first >= B.n_items) break;
+            }
+            end = first + B.grab < B.n_items ? first + B.grab : B.n_items;
         }
-        const uint64_t end = first + grab < n_items ? first + grab : n_items;
         for (uint64_t item = first; item < end; ++item) {
-            int lo = 0, hi = n_tasks - 1;                  // last task with item0 <= item
+            int lo = 0, hi = B.n_tasks - 1;                  // last task with item0 <= item
             while (lo < hi) {
                 const int mid = (lo + hi + 1) >> 1;
                 if (T[mid].item0 <= item) lo = mid; else hi = mid - 1;
@@ -82,23 +91,24 @@ k_batch(const BatchTask* __restrict__ tasks, int n_tasks, uint64_t n_items, unsi
             A.b = T[lo].b;
             A.sig = T[lo].sig;
             A.shift = T[lo].shift;
-            A.key = key;
+            A.key = B.key;
             A.key.stream = T[lo].stream;
             A.first_path = 0;
             A.n_paths = T[lo].n_paths;
             A.work = PathWork{};
             A.s = T[lo].s;
             A.D = T[lo].s - S::U;
-            A.hier = hier;
+            A.hier = B.hier;
             A.partials = T[lo].partials;
             A.dump = nullptr;
             Eval ev = ev0;
             ev.tab = T[lo].tab;
             const int nlev = A.s + 1;
             const uint64_t n_groups = (A.n_paths + 63) / 64;
-            double* acc = smem + kBoxMullerTable + size_t(3 * A.D + 2) * S::BS;
+            // behind the deepest stack of the class: the waves of a workgroup may be in tasks of different N
+            double* acc = smem + kBoxMullerTable + size_t(3 * (B.smax - S::U) + 2) * S::BS;
             uint64_t g = item - T[lo].item0, last, step = 1;
-            if (by_group) {
+            if (BY_GROUP) {
                 g *= T[lo].block;
                 last = g + T[lo].block;
             } else {
@@ -110,15 +120,15 @@ k_batch(const BatchTask* __restrict__ tasks, int n_tasks, uint64_t n_items, unsi
             }
             if (last > n_groups) last = n_groups;
             for (; g < last; g += step) {
-                GroupSink k;
-                k.acc = by_group ? nullptr : acc + int(g % kChunkSlots) * nlev * 3;
-                k.out = T[lo].gsum + g * 3;
-                k.stride = n_groups * 3;
-                process_group<S, Eval>(ev, A, g, k, smem, smem + kBoxMullerTable + tid);
+                // by group the sums are formed in the slot of this wave's number
+                double* a = acc + (BY_GROUP ? wave * (B.smax + 1) : int(g % kChunkSlots) * nlev) * 3;
+                if (BY_GROUP) clear_slot(a, nlev);
+                process_group<S, Eval>(ev, A, g, a, smem, smem + kBoxMullerTable + tid);
+                if (BY_GROUP) store_slot(a, B.hier ? nlev : 1, T[lo].gsum + g * 3, n_groups * 3);
             }
-            if (!by_group) {
+            if (!BY_GROUP) {
                 __syncthreads();
-                write_chunk(acc, nlev, hier, A.partials, T[lo].n_chunks, item - T[lo].item0, A.n_paths, tid);
+                write_chunk(acc, nlev, B.hier, A.partials, T[lo].n_chunks, item - T[lo].item0, A.n_paths, tid);
                 __syncthreads();
             }
         }
@@ -131,9 +141,7 @@ struct BatchLauncher;
 
 template <int P>
 struct BatchLauncher<P, ShapeList<>> {
-    static hipError_t launch(int, const BatchTask*, int, uint64_t, unsigned long long*, uint32_t, int, const RngKey&, int, int,
-                             size_t, hipStream_t) {
-        return hipErrorInvalidValue;
+    static hipError_t launch(int, const BatchArgs&, int, size_t, hipStream_t) {
     }
     static int resident(int, size_t, int) { return 0; }
     static bool desc(int, ShapeDesc&) { return false; }
@@ -142,18 +150,19 @@ struct BatchLauncher<P, ShapeList<>> {
 template <int P, class S0, class... Ss>
 struct BatchLauncher<P, ShapeList<S0, Ss...>> {
     using Rest = BatchLauncher<P, ShapeList<Ss...>>;
-    static hipError_t launch(int idx, const BatchTask* tasks, int n_tasks, uint64_t n_items, unsigned long long* queue,
-                             uint32_t grab, int by_group, const RngKey& key, int hier, int grid, size_t lds, hipStream_t st) {
-        if (idx != 0) return Rest::launch(idx - 1, tasks, n_tasks, n_items, queue, grab, by_group, key, hier, grid, lds, st);
+    static hipError_t launch(int idx, const BatchArgs& B, int grid, size_t lds, hipStream_t st) {
+        if (idx != 0) return Rest::launch(idx - 1, B, grid, lds, st);
         QuarticEval64<P> ev{nullptr};
-        hipLaunchKernelGGL((k_batch<S0, QuarticEval64<P>>), dim3(grid), dim3(S0::BS), lds, st, tasks, n_tasks, n_items,
-                           queue, grab, by_group, key, hier, ev);
+        if (B.by_group)
+            hipLaunchKernelGGL((k_batch<S0, QuarticEval64<P>, true>), dim3(grid), dim3(S0::BS), lds, st, B, ev);
+        else
+            hipLaunchKernelGGL((k_batch<S0, QuarticEval64<P>, false>), dim3(grid), dim3(S0::BS), lds, st, B, ev);
         return hipGetLastError();
     }
     static int resident(int idx, size_t lds, int device) {
         if (idx != 0) return Rest::resident(idx - 1, lds, device);
         int per_cu = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch<S0, QuarticEval64<P>>, S0::BS, lds) !=
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch<S0, QuarticEval64<P>, false>, S0::BS, lds) !=
             hipSuccess)
             per_cu = 1;
         int ncu = 0;
@@ -169,23 +178,17 @@ struct BatchLauncher<P, ShapeList<S0, Ss...>> {
 
 // The tuned classes of level P (defined in pimc_batch_p<P>.hip).
 #define PIMC_BATCH_TUNED_DECL(P)                                                                                      \
-    hipError_t launch_batch_tuned_##P(bool n16, int idx, const BatchTask* tasks, int n_tasks, uint64_t n_items,        \
-                                      unsigned long long* queue, uint32_t grab, int by_group, const RngKey& key, int hier, int grid,  \
-                                      size_t lds, hipStream_t st);                                                      \
+    hipError_t launch_batch_tuned_##P(bool n16, int idx, const BatchArgs& B, int grid, size_t lds, hipStream_t st);   \
     int resident_batch_tuned_##P(bool n16, int idx, size_t lds, int device);
 
 #define PIMC_BATCH_TUNED_DEF(P)                                                                                       \
-    hipError_t launch_batch_tuned_##P(bool n16, int idx, const BatchTask* tasks, int n_tasks, uint64_t n_items,        \
-                                      unsigned long long* queue, uint32_t grab, int by_group, const RngKey& key, int hier, int grid,  \
-                                      size_t lds, hipStream_t st) {                                                     \
-        return n16 ? BatchLauncher<P, BatchShapesN16>::launch(idx, tasks, n_tasks, n_items, queue, grab, by_group, key, hier,    \
-                                                             grid, lds, st)                                             \
-                   : BatchLauncher<P, BatchShapesN32>::launch(idx, tasks, n_tasks, n_items, queue, grab, by_group, key, hier,    \
-                                                             grid, lds, st);                                            \
-    }                                                                                                                  \
-    int resident_batch_tuned_##P(bool n16, int idx, size_t lds, int device) {                                          \
-        return n16 ? BatchLauncher<P, BatchShapesN16>::resident(idx, lds, device)                                      \
-                   : BatchLauncher<P, BatchShapesN32>::resident(idx, lds, device);                                     \
+    hipError_t launch_batch_tuned_##P(bool n16, int idx, const BatchArgs& B, int grid, size_t lds, hipStream_t st) {  \
+        return n16 ? BatchLauncher<P, BatchShapesN16>::launch(idx, B, grid, lds, st)                                  \
+                   : BatchLauncher<P, BatchShapesN32>::launch(idx, B, grid, lds, st);                                 \
+    }                                                                                                                 \
+    int resident_batch_tuned_##P(bool n16, int idx, size_t lds, int device) {                                         \
+        return n16 ? BatchLauncher<P, BatchShapesN16>::resident(idx, lds, device)                                     \
+                   : BatchLauncher<P, BatchShapesN32>::resident(idx, lds, device);                                    \
     }
 
 PIMC_BATCH_TUNED_DECL(8)

@@ -1,26 +1,21 @@
 // How the estimation kernels share out the paths of a run, and the sums of a group of paths.
 //
 // A group is 64 consecutive paths, the lanes of one wave; a canonical chunk is 64 groups
-// (pimc_internal.hpp). Two kinds of work share one persistent kernel:
+// (pimc_split.hpp). Two kinds of work share one persistent kernel:
 //   * coarse chunks 0 .. n_coarse-1: a workgroup takes a whole chunk from a counter, its waves walk the
 //     chunk's groups and add their sums in LDS, and the chunk's record is written once;
 //   * fine groups, those of the chunks from n_coarse on: every wave walks groups by itself and stores
 //     each group's sums; k_group_chunks adds them into the chunk records afterwards. The first
 //     n_static fine groups are dealt to the waves in turn, the others go by ticket from a second counter.
 // Both add in the order fixed by the path indices, so a chunk's bits do not depend on its kind.
+// pimc_split.hpp decides how many of each there are.
 //
 // Why two kinds. A group costs from microseconds (N = 16) to milliseconds, and a GPU of 256 CUs holds
-// 2048 waves at two per SIMD. With whole chunks alone a run below 512 x 4096 = 2.1e6 paths left
-// workgroups without work, and above it the last round was part empty. Group sums are 24 bytes per
-// group and level, so a whole run of 1e9 paths cannot keep them; the last kFineBytes worth are enough
-// to fill every wave many times over.
-// Why two ways of sharing out. Tickets are 8 ns each for the whole GPU (2048 waves on one counter),
-// 16 us for a round of all waves: nothing beside groups of N >= 64 slices, much of the time of smaller
-// ones (a call with 1e5 paths at N = 16, every level: whole chunks 156 us, tickets 109 us, dealt 75
-// us). But waves drift apart, so the last rounds of long groups go by ticket.
-// Measured, calls with every level, whole chunks against this: 1e6 paths at N = 1024, p = 10
-// (Poeschl-Teller) 16.3 -> 13.3 ms; 3e5 at N = 64, p = 6 (sextic) 1.02 -> 0.28 ms; 5e4 at N = 64,
-// p = 18 (general mode) 234 -> 42 ms; 2e7 at N = 1024, p = 18 (quartic) 102 -> 96 ms.
+// 2048 waves at two per SIMD. With whole chunks alone a run below 512 x 4096 = 2.1e6 paths leaves
+// workgroups without work, and above it the last round is part empty.
+// Measured, calls with every level, whole chunks against this: 1e5 paths at N = 16, p = 4 156 -> 67 us; 1e6
+// at N = 1024, p = 10 (Poeschl-Teller) 16.3 -> 13.3 ms; 3e5 at N = 64, p = 6 (sextic) 1.02 -> 0.28 ms; 5e4 at
+// N = 64, p = 18 (general mode) 234 -> 42 ms; 2e7 at N = 1024, p = 18 (quartic) 102 -> 96 ms.
 #pragma once
 
 #include "pimc_device.hpp"
@@ -33,35 +28,36 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
     const uint32_t hi = __builtin_amdgcn_readfirstlane(uint32_t(v >> 32));
     return (uint64_t(hi) << 32) | lo;
 }
+__device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// Where lane 0 puts a group's level sums (sum d, sum d^2, non-finite count): added to an accumulator
-// slot in LDS, or stored to the group's place in device memory (stride: doubles between slots).
-struct GroupSink {
-    double* acc;                       // LDS, 3 doubles per level, or null
-    double* out;                       // device, else
-    uint64_t stride;
-};
-
-// The sums of one level over a group: d and d^2 by a wave butterfly, the non-finite count by a ballot.
-__device__ __forceinline__ void reduce_level(const GroupSink& k, int lane, int slot, double S, double shift, bool valid) {
+// Adds the sums of one level over a group to an accumulator slot a (LDS; sum d, sum d^2, non-finite count):
+// d and d^2 by a wave butterfly, the non-finite count by a ballot.
+__device__ __forceinline__ void reduce_level(double* a, int lane, double S, double shift, bool valid) {
     const double d = valid ? expm1(-(S - shift)) : 0.0;
     const bool bad = valid && !isfinite(d);
     const double sd = wave_sum(d);
     const double sd2 = wave_sum(d * d);
-    const double nb = double(__popcll(__ballot(bad)));
+    const unsigned long long badmask = __ballot(bad);
     if (lane == 0) {
-        if (k.acc) {
-            double* a = k.acc + slot * 3;
-            a[0] += sd;
-            a[1] += sd2;
-            a[2] += nb;
-        } else {
-            double* a = k.out + uint64_t(slot) * k.stride;
-            a[0] = sd;
-            a[1] = sd2;
-            a[2] = nb;
-        }
+        a[0] += sd;
+        a[1] += sd2;
+        a[2] += double(__popcll(badmask));
     }
+}
+
+// A wave's own accumulator slot: cleared before a group, and stored to the group's place in device memory
+// (`stride` doubles between levels) after it. Lane 0 adds in between; a wave's LDS accesses are in order.
+static_assert(PIMC_MAX_S + 1 <= 21, "a slot is at most 63 doubles, one per lane");
+__device__ __forceinline__ void clear_slot(double* a, int nlev) {
+    const int i = int(threadIdx.x & 63u);
+    if (i < nlev * 3) a[i] = 0.0;
+    __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ void store_slot(const double* a, int slots, double* out, uint64_t stride) {
+    const int i = int(threadIdx.x & 63u);
+    __builtin_amdgcn_wave_barrier();
+    if (i < slots * 3) out[uint64_t(i / 3) * stride + uint64_t(i % 3)] = a[i];
+    __builtin_amdgcn_wave_barrier();
 }
 
 // A whole chunk's record from its accumulator slots, by one thread per evaluated level (tid < slots).
@@ -83,39 +79,80 @@ __device__ __forceinline__ void write_chunk(const double* acc, int nlev, int hie
     o[3] = nb;
 }
 
-// The persistent loop of one workgroup of BS threads. run(group, sink) walks the 64 paths of a group
-// and reduces them into the sink (one call site: its code is the whole kernel); acc: the accumulator
-// slots in LDS, kChunkSlots * nlev * 3 doubles. Every wave of a workgroup leaves the coarse phase at
-// the same ticket, so its barriers are met by all; a fine ticket is asked for before the groups of the
-// one in hand are walked (the answer is back long before it is needed).
+// The loop of one workgroup of BS threads over whole chunks.
+template <int BS, class RunGroup>
+__device__ __forceinline__ void run_chunks(const PathWork& w, int nlev, int hier, uint64_t n_paths, double* partials,
+                                           double* acc, RunGroup run) {
+    __shared__ unsigned long long s_chunk;
+    const int tid = threadIdx.x;
+    const int wave = tid >> 6;
+    while (true) {
+        __syncthreads();
+        if (tid == 0) s_chunk = atomicAdd(w.queue, 1ull);
+        __syncthreads();
+        const uint64_t c = uniform_u64(s_chunk);
+        if (c >= w.n_chunks) break;
+        for (int i = tid; i < kChunkSlots * nlev * 3; i += BS) acc[i] = 0.0;
+        __syncthreads();
+        for (int g = wave; g < kChunkGroups; g += BS / 64) {
+            if ((c * kChunkGroups + uint64_t(g)) * 64 >= n_paths) break;   // wave-uniform: the rest of the chunk is empty
+            run(c * kChunkGroups + uint64_t(g), acc + (g % kChunkSlots) * nlev * 3);
+        }
+        __syncthreads();
+        write_chunk(acc, nlev, hier, partials, w.n_chunks, c, n_paths, tid);
+    }
+}
+
+// What the loop of a workgroup works by, in LDS. In registers (the launch's arguments are scalar) it would be
+// live over the walk, whose constants take all scalar registers: 70 more lane reads a group to bring it back,
+// 5 % of a call with 1e8 paths at N = 16, p = 1.
+struct SharedWork {
+    PathWork w;
+    uint64_t fine0, n_fine;            // first fine group, fine groups
+    unsigned long long chunk;          // the whole chunk in hand
+};
+
+// The persistent loop of one workgroup of BS threads. run(group, a) walks the 64 paths of a group
+// and adds their sums to the accumulator slot a (one call site: its code is the whole kernel); acc: the
+// slots in LDS, kChunkSlots * nlev * 3 doubles, a wave's own number among them. Every wave of a workgroup
+// leaves the coarse phase at the same ticket, so its barriers are met by all. A ticket for fine groups is asked for before the groups of
+// the one in hand are walked (the answer is back long before it is needed); one for a chunk only when the
+// workgroup is free, or the last chunks would go to workgroups that are still at their last but one.
 template <int BS, class RunGroup>
 __device__ __forceinline__ void run_groups(const PathWork& w, int nlev, int hier, uint64_t n_paths, double* partials,
                                            double* acc, RunGroup run) {
     constexpr int WAVES = BS / 64;
-    __shared__ unsigned long long s_chunk;
+    __shared__ SharedWork sw;
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const uint64_t fine0 = w.n_coarse * kChunkGroups;
-    const uint64_t n_fine = w.n_groups > fine0 ? w.n_groups - fine0 : 0;
-    auto take = [&]() -> unsigned long long {
+    if (tid == 0) {
+        const uint64_t f0 = w.n_coarse * kChunkGroups;
+        sw.w = w;
+        sw.fine0 = f0;
+        sw.n_fine = w.n_groups > f0 ? w.n_groups - f0 : 0;
+    }
+    __syncthreads();
+    auto take = [&]() -> unsigned long long {                      // the next ticket for fine groups (in lane 0)
         unsigned long long t = 0;
-        if ((tid & 63) == 0) t = atomicAdd(w.queue + 1, (unsigned long long)w.grab);
-        return w.n_static + t;
+        if ((tid & 63) == 0) t = atomicAdd(w.queue + 1, (unsigned long long)sw.w.grab);
+        return t;
     };
-    bool coarse = w.n_coarse > 0;
-    uint64_t deal = coarse ? w.n_static : uint64_t(blockIdx.x) * WAVES + uint64_t(wave);   // next group dealt to this wave
-    unsigned long long ticket = n_fine;
-    if (!coarse && w.n_static < n_fine) ticket = take();
+    bool coarse = uniform_u64(sw.w.n_coarse) > 0;
+    bool dealt = !coarse;                                          // the groups dealt to this wave are to come
+    unsigned long long ticket = 0;
+    if (!coarse && uniform_u64(sw.w.n_static) < uniform_u64(sw.n_fine)) ticket = take();
     while (true) {
-        uint64_t g, last, step, c = 0;
+        uint64_t g, last;
+        uint32_t step;
         if (coarse) {
+            __syncthreads();                                       // the chunk before is written
+            if (tid == 0) sw.chunk = atomicAdd(w.queue, 1ull);
             __syncthreads();
-            if (tid == 0) s_chunk = atomicAdd(w.queue, 1ull);
-            __syncthreads();
-            c = uniform_u64(s_chunk);
-            if (c >= w.n_coarse) {
+            const uint64_t c = uniform_u64(sw.chunk);
+            if (c >= uniform_u64(sw.w.n_coarse)) {
                 coarse = false;
-                if (w.n_static < n_fine) ticket = take();
+                if (uniform_u64(sw.n_fine) == 0) break;
+                ticket = take();
                 continue;
             }
             for (int i = tid; i < kChunkSlots * nlev * 3; i += BS) acc[i] = 0.0;
@@ -123,30 +160,31 @@ __device__ __forceinline__ void run_groups(const PathWork& w, int nlev, int hier
             g = c * kChunkGroups + uint64_t(wave);
             last = (c + 1) * kChunkGroups;
             step = WAVES;
-        } else if (deal < w.n_static) {
-            g = fine0 + deal;
-            last = fine0 + w.n_static;
-            step = uint64_t(gridDim.x) * WAVES;
-            deal = w.n_static;
+        } else if (dealt) {
+            dealt = false;
+            g = uint64_t(blockIdx.x) * WAVES + uint64_t(wave);
+            last = uniform_u64(sw.w.n_static);
+            step = gridDim.x * WAVES;
         } else {
-            const uint64_t f = uniform_u64(ticket);
-            if (f >= n_fine) break;
+            const uint64_t f = uniform_u64(sw.w.n_static) + uniform_u64(ticket);
+            if (f >= uniform_u64(sw.n_fine)) break;
             ticket = take();
-            g = fine0 + f;
-            last = g + w.grab;
+            g = uniform_u64(sw.fine0) + f;
+            last = g + uniform_u32(sw.w.grab);
             step = 1;
         }
-        if (last > w.n_groups) last = w.n_groups;
+        const uint64_t end = uniform_u64(sw.w.n_groups);
+        if (last > end) last = end;
         for (; g < last; g += step) {
-            GroupSink k;
-            k.acc = coarse ? acc + int(g % kChunkSlots) * nlev * 3 : nullptr;
-            k.out = w.gsum + (g - fine0) * 3;
-            k.stride = n_fine * 3;
-            run(g, k);
+            // a fine group's sums are formed in the slot of this wave's number
+            double* a = acc + (coarse ? int(g % kChunkSlots) : wave) * nlev * 3;
+            if (!coarse) clear_slot(a, nlev);
+            run(g, a);
+            if (!coarse && partials) store_slot(a, hier ? nlev : 1, sw.w.gsum + (g - sw.fine0) * 3, sw.n_fine * 3);
         }
         if (coarse) {
             __syncthreads();
-            write_chunk(acc, nlev, hier, partials, w.n_chunks, c, n_paths, tid);
+            write_chunk(acc, nlev, hier, partials, sw.w.n_chunks, uniform_u64(sw.chunk), n_paths, tid);
         }
     }
 }

@@ -19,6 +19,8 @@
 
 namespace pimc {
 
+template <int P> constexpr bool kWholeKernel<GenSliceEval<P>> = false;
+
 static_assert(PIMC_GEN_P > kGenInlineMaxP && PIMC_GEN_P <= kGenMaxP, "level of an out-of-line evaluator");
 static_assert(gen_subtree_levels(PIMC_GEN_P) == 3, "three-level subtrees above the inline levels");
 

@@ -17,6 +17,8 @@
 
 namespace pimc {
 
+template <int P> constexpr bool kWholeKernel<GenCompiledEval<P>> = false;
+
 static_assert(PIMC_GEN_HI <= kGenInlineMaxP, "inlined levels");
 
 namespace {

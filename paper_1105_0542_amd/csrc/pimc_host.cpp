@@ -472,12 +472,12 @@ int amplitude_core(pimc_ctx* c, const Problem& P, uint64_t n_samples, uint64_t s
         partials = work->partials;
         // the group sums take what the chunk records leave of the workspace
         const size_t left = work->partial_cap - partial_bytes;
-        pw = split_paths(n_samples, P.s, slots, std::min(left, kFineBytes), uint64_t(resident) * (kBlock / 64));
+        pw = split_paths(n_samples, P.s, slots, std::min(left, kFineBytes), uint64_t(resident), kBlock / 64);
         pw.gsum = partials + partial_bytes / 8;
     } else {
         st = ensure(c, reinterpret_cast<void**>(&c->d_partials), &c->partial_bytes, partial_bytes);
         if (st) return st;
-        pw = split_paths(n_samples, P.s, slots, kFineBytes, uint64_t(resident) * (kBlock / 64));
+        pw = split_paths(n_samples, P.s, slots, kFineBytes, uint64_t(resident), kBlock / 64);
         st = ensure(c, reinterpret_cast<void**>(&c->d_gsum), &c->gsum_bytes, group_sum_bytes(pw, slots));
         if (st) return st;
         pw.gsum = c->d_gsum;
@@ -552,7 +552,7 @@ int path_actions_core(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t str
     A.dump = c->d_dump;
     const int resident = resident_blocks(c, P);
     unsigned long long* const queue = A.work.queue;
-    A.work = split_paths(k_paths, P.s, 0, 0, uint64_t(resident) * (kBlock / 64));
+    A.work = split_paths(k_paths, P.s, 0, 0, uint64_t(resident), kBlock / 64);
     A.work.queue = queue;
     const int grid = work_grid(A.work, kBlock / 64, resident);
     HIP_TRY(c, launch_amplitude(A, P.kind, P.p, P.U, grid, c->stream));
@@ -896,10 +896,17 @@ int class_grid(const pimc_batch* b, const pimc_batch::Class& C) { return std::ma
 // The launch of class k's persistent kernel on `st` (its queue must be reset first).
 hipError_t launch_class(pimc_batch* b, size_t k, hipStream_t st) {
     const auto& C = b->classes[k];
-    RngKey key{uint32_t(b->seed), uint32_t(b->seed >> 32), 0u};
-    const int hier = (b->flags & PIMC_HIERARCHY) ? 1 : 0;
-    return launch_batch(b->d_tasks + C.first, C.n_tasks, C.n_work, b->d_queue + k, b->grab, b->d_gsum != nullptr, key, hier, C.p, C.n16,
-                        C.shape, class_grid(b, C), C.lds, st);
+    BatchArgs B{};
+    B.tasks = b->d_tasks + C.first;
+    B.n_items = C.n_work;
+    B.queue = b->d_queue + k;
+    B.key = RngKey{uint32_t(b->seed), uint32_t(b->seed >> 32), 0u};
+    B.grab = b->grab;
+    B.n_tasks = C.n_tasks;
+    B.by_group = b->d_gsum ? 1 : 0;
+    B.smax = C.smax;
+    B.hier = (b->flags & PIMC_HIERARCHY) ? 1 : 0;
+    return launch_batch(B, C.p, C.n16, C.shape, class_grid(b, C), C.lds, st);
 }
 
 // Shape idx for class k: its description, LDS bytes and resident workgroups.

@@ -7,22 +7,11 @@
 
 #include "pimc.h"
 #include "pimc_device.hpp"
+#include "pimc_split.hpp"
 
 namespace pimc {
 
 constexpr int kBlock = 256;            // threads per workgroup of the auxiliary kernels (4 waves)
-
-// Canonical chunk of the estimators: kChunkPaths consecutive path indices, in kChunkGroups groups of
-// 64 consecutive paths (the lanes of one wave). A group's per-level sums are a wave butterfly;
-// group g is added to accumulator slot g mod kChunkSlots, each slot in increasing g, and the chunk
-// sum is slot 0 + slot 1 + slot 2 + slot 3. The order is fixed by the path indices alone, so the
-// chunk sums -- and the amplitudes -- do not depend on the workgroup size (64, 128 or 256 lanes:
-// wave w of a workgroup of W waves takes groups w, w + W, ..., and no two waves share a slot), on
-// the subtree depth or slice batch of the walker, on N (level n of an s-run is bitwise the n-run),
-// or on which workgroup ran the chunk.
-constexpr uint32_t kChunkPaths = PIMC_CHUNK_PATHS;
-constexpr int kChunkGroups = int(kChunkPaths / 64);
-constexpr int kChunkSlots = 4;
 
 // Launch shape of the estimation walker: U bisection levels of each subtree in registers
 // (2^U + 1 points), BS threads per workgroup, occupancy target WPE waves per SIMD (register budget
@@ -40,50 +29,6 @@ struct Shape {
 // U = 5 needs more registers than 2 waves per SIMD leave and spills to scratch).
 template <int U>
 using DefaultShape = Shape<U, 256, 2, 16>;
-
-// The paths of one launch (pimc_chunks.hpp): chunks 0 .. n_coarse-1 whole, the groups of the others
-// (fine groups) one by one.
-struct PathWork {
-    uint64_t n_groups;                 // ceil(n_paths / 64)
-    uint64_t n_chunks;                 // ceil(n_paths / kChunkPaths)
-    uint64_t n_coarse;
-    uint64_t n_static;                 // fine groups dealt to the waves in turn (none when n_coarse > 0)
-    double* gsum;                      // device [slot][fine group][3], or null (per-path actions only)
-    unsigned long long* queue;         // device: the coarse and the fine counter, 0 at launch
-    uint32_t grab;                     // fine groups per ticket
-    uint64_t fine() const { return n_groups > n_coarse * kChunkGroups ? n_groups - n_coarse * kChunkGroups : 0; }
-};
-
-// Group sums a run may keep: 24 bytes per group and level, 993 chunks (63,552 groups) with the eleven
-// levels of N = 1024, thirty times the waves of the GPU.
-constexpr size_t kFineBytes = size_t(16) << 20;
-
-// Split of a run of n_paths paths of N = 2^s slices over `slots` evaluated levels: as many chunks from
-// the end fine as fine_bytes of group sums hold (all of them when slots = 0: nothing is summed). The
-// last two rounds of the `waves` resident waves go by single ticket when a group is long (N >= 64),
-// everything is dealt when it is short; short groups behind a coarse phase go by 16.
-inline PathWork split_paths(uint64_t n_paths, int s, int slots, size_t fine_bytes, uint64_t waves) {
-    PathWork w{};
-    w.n_groups = (n_paths + 63) / 64;
-    w.n_chunks = (n_paths + kChunkPaths - 1) / kChunkPaths;
-    const uint64_t fit = slots ? fine_bytes / (size_t(slots) * kChunkGroups * 24) : w.n_chunks;
-    w.n_coarse = w.n_chunks > fit ? w.n_chunks - fit : 0;
-    const bool is_short = s < 6;
-    w.grab = is_short && w.n_coarse ? 16 : 1;
-    if (!w.n_coarse) {
-        const uint64_t rounds = w.n_groups / (waves ? waves : 1);
-        w.n_static = is_short || rounds < 1 ? w.n_groups : (rounds > 2 ? (rounds - 2) * waves : 0);
-    }
-    return w;
-}
-// Bytes of its group sums.
-inline size_t group_sum_bytes(const PathWork& w, int slots) { return size_t(slots) * size_t(w.fine()) * 24; }
-// Workgroups of `waves_per_wg` waves that this work can occupy, at most `resident`.
-inline int work_grid(const PathWork& w, int waves_per_wg, int resident) {
-    const uint64_t wgs = w.n_coarse + ((w.fine() + w.grab - 1) / w.grab + uint64_t(waves_per_wg) - 1) / uint64_t(waves_per_wg);
-    const uint64_t most = uint64_t(resident < 1 ? 1 : resident);
-    return int(wgs < 1 ? 1 : (wgs < most ? wgs : most));
-}
 
 // Arguments of one estimation launch (passed by value in the kernel argument segment, so every
 // field is wave-uniform and scalar-loaded).
@@ -241,6 +186,20 @@ struct BatchTask {
     int s;
 };
 
+// Arguments of a class's launch (by value, wave-uniform).
+struct BatchArgs {
+    const BatchTask* tasks;            // device
+    uint64_t n_items;
+    uint64_t n_static;                 // items dealt to the waves in turn (by group)
+    unsigned long long* queue;         // device: the item counter, 0 at launch
+    RngKey key;                        // stream: the task's
+    uint32_t grab;                     // items per ticket
+    int n_tasks;
+    int by_group;
+    int smax;                          // largest s of the class
+    int hier;
+};
+
 // A launch shape as the host sees it.
 struct ShapeDesc {
     int U, BS, WPE, BATCH;
@@ -252,8 +211,7 @@ struct ShapeDesc {
 // only the default).
 int batch_shape_count(int p, bool n16);
 bool batch_shape(int p, bool n16, int idx, ShapeDesc& d);
-hipError_t launch_batch(const BatchTask* tasks, int n_tasks, uint64_t n_items, unsigned long long* queue, uint32_t grab,
-                        int by_group, const RngKey& key, int hier, int p, bool n16, int shape, int grid, size_t lds, hipStream_t st);
+hipError_t launch_batch(const BatchArgs& B, int p, bool n16, int shape, int grid, size_t lds, hipStream_t st);
 int batch_resident_blocks(int p, bool n16, int shape, size_t lds_bytes, int device);
 hipError_t launch_fill_u64(unsigned long long* p, int n, unsigned long long v, hipStream_t st);
 

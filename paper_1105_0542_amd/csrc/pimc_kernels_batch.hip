@@ -12,16 +12,11 @@ namespace {
 bool tuned_level(int p) { return p == 8 || p == 12 || p == 18; }
 
 template <int P>
-hipError_t launch_default(int p, bool n16, int idx, const BatchTask* tasks, int n_tasks, uint64_t n_items,
-                          unsigned long long* queue, uint32_t grab, int by_group, const RngKey& key, int hier, int grid, size_t lds,
-                          hipStream_t st) {
+hipError_t launch_default(int p, bool n16, int idx, const BatchArgs& B, int grid, size_t lds, hipStream_t st) {
     if constexpr (P <= kMaxP) {
-        if (p != P)
-            return launch_default<P + 1>(p, n16, idx, tasks, n_tasks, n_items, queue, grab, by_group, key, hier, grid, lds, st);
-        return n16 ? BatchLauncher<P, BatchDefaultN16>::launch(idx, tasks, n_tasks, n_items, queue, grab, by_group, key, hier, grid,
-                                                               lds, st)
-                   : BatchLauncher<P, BatchDefaultN32>::launch(idx, tasks, n_tasks, n_items, queue, grab, by_group, key, hier, grid,
-                                                               lds, st);
+        if (p != P) return launch_default<P + 1>(p, n16, idx, B, grid, lds, st);
+        return n16 ? BatchLauncher<P, BatchDefaultN16>::launch(idx, B, grid, lds, st)
+                   : BatchLauncher<P, BatchDefaultN32>::launch(idx, B, grid, lds, st);
     } else {
         return hipErrorInvalidValue;
     }
@@ -52,14 +47,12 @@ bool batch_shape(int p, bool n16, int idx, ShapeDesc& d) {
     return n16 ? BatchLauncher<1, BatchDefaultN16>::desc(idx, d) : BatchLauncher<1, BatchDefaultN32>::desc(idx, d);
 }
 
-hipError_t launch_batch(const BatchTask* tasks, int n_tasks, uint64_t n_items, unsigned long long* queue, uint32_t grab,
-                        int by_group, const RngKey& key, int hier, int p, bool n16, int shape, int grid, size_t lds, hipStream_t st) {
+hipError_t launch_batch(const BatchArgs& B, int p, bool n16, int shape, int grid, size_t lds, hipStream_t st) {
     switch (p) {
-        case 8: return launch_batch_tuned_8(n16, shape, tasks, n_tasks, n_items, queue, grab, by_group, key, hier, grid, lds, st);
-        case 12: return launch_batch_tuned_12(n16, shape, tasks, n_tasks, n_items, queue, grab, by_group, key, hier, grid, lds, st);
-        case 18: return launch_batch_tuned_18(n16, shape, tasks, n_tasks, n_items, queue, grab, by_group, key, hier, grid, lds, st);
-        default:
-            return launch_default<1>(p, n16, shape, tasks, n_tasks, n_items, queue, grab, by_group, key, hier, grid, lds, st);
+        case 8: return launch_batch_tuned_8(n16, shape, B, grid, lds, st);
+        case 12: return launch_batch_tuned_12(n16, shape, B, grid, lds, st);
+        case 18: return launch_batch_tuned_18(n16, shape, B, grid, lds, st);
+        default: return launch_default<1>(p, n16, shape, B, grid, lds, st);
     }
 }
 

@@ -1,0 +1,95 @@
+// How the paths of a run are shared out: the numbers that the kernels of pimc_chunks.hpp work by (host code).
+#pragma once
+
+#include <stddef.h>
+#include <stdint.h>
+
+#include <algorithm>
+
+#include "pimc.h"
+
+namespace pimc {
+
+// Canonical chunk of the estimators: kChunkPaths consecutive path indices, in kChunkGroups groups of
+// 64 consecutive paths (the lanes of one wave). A group's per-level sums are a wave butterfly;
+// group g is added to accumulator slot g mod kChunkSlots, each slot in increasing g, and the chunk
+// sum is slot 0 + slot 1 + slot 2 + slot 3. The order is fixed by the path indices alone, so the
+// chunk sums -- and the amplitudes -- do not depend on the workgroup size (64, 128 or 256 lanes:
+// wave w of a workgroup of W waves takes groups w, w + W, ..., and no two waves share a slot), on
+// the subtree depth or slice batch of the walker, on N (level n of an s-run is bitwise the n-run),
+// or on which workgroup ran the chunk.
+constexpr uint32_t kChunkPaths = PIMC_CHUNK_PATHS;
+constexpr int kChunkGroups = int(kChunkPaths / 64);
+constexpr int kChunkSlots = 4;
+
+// The paths of one launch (pimc_chunks.hpp): chunks 0 .. n_coarse-1 whole, the groups of the others
+// (fine groups) one by one.
+struct PathWork {
+    uint64_t n_groups;                 // ceil(n_paths / 64)
+    uint64_t n_chunks;                 // ceil(n_paths / kChunkPaths)
+    uint64_t n_coarse;
+    uint64_t n_static;                 // fine groups dealt to the waves in turn (none when n_coarse > 0)
+    double* gsum;                      // device [slot][fine group][3], or null (per-path actions only)
+    unsigned long long* queue;         // device: the coarse and the fine counter, 0 at launch
+    uint32_t grab;                     // fine groups per ticket
+    uint64_t fine() const { return n_groups > n_coarse * kChunkGroups ? n_groups - n_coarse * kChunkGroups : 0; }
+};
+
+// Group sums a run may keep: 24 bytes per group and level, 992 chunks (63,488 groups) with the eleven
+// levels of N = 1024.
+constexpr size_t kFineBytes = size_t(16) << 20;
+
+// A ticket costs 12.4 ns of the whole GPU (one address, measured as the time of runs that it bounds), 25 us
+// for one round of 2048 waves. The cheapest slice of a group takes a wave 0.22 us (quartic, p = 1, level s
+// alone), so a ticket should be worth kTicketSlices of them.
+constexpr uint32_t kTicketSlices = 128;
+inline uint32_t ticket_groups(int s) { return s >= 7 ? 1u : (s >= 3 ? kTicketSlices >> s : 16u); }
+
+// Whole chunks of a run of n_chunks chunks on wgs workgroups, R = n_chunks / wgs rounds.
+//   R <= 1: none, with chunks workgroups would have no work (1e6 paths, N = 256, p = 18: 1.19 ms, 0.99 by group);
+//   N <= 32: all, the tail of a chunk is short there and tickets for short groups are dear (5e6 paths, N = 8,
+//     p = 1: 0.18 ms, 0.23 with the last two rounds by group);
+//   else full rounds, and what remains, 0.4 to 1.4 rounds, by group (one to two from R = 3 on, where workgroups
+//     have drifted apart by a chunk): 5e6 paths, N = 256, p = 18, every level: 8.3 ms by chunk, 6.4; 1e7: 13.5 and
+//     12.4. A remainder of whole chunks beside groups is worse than either (3e6 paths, 1.43 rounds, 0.43 of
+//     them by chunk: 6.2 ms, 4.2 by chunk and 4.1 this way), the chunks then last longer than all the rest.
+inline uint64_t whole_chunks(uint64_t n_chunks, int s, uint64_t wgs) {
+    if (n_chunks <= wgs) return 0;
+    if (s <= 5) return n_chunks;
+    const uint64_t r10 = n_chunks * 10 / wgs;
+    return wgs * (r10 < 30 ? (r10 - 4) / 10 : r10 / 10 - 1);
+}
+
+// Split of a run of n_paths paths of N = 2^s slices over `slots` evaluated levels, on `resident` workgroups of
+// `wg_waves` waves; fine_bytes: room for group sums (slots = 0: nothing is summed, every group is fine). Behind
+// whole chunks the groups go by ticket. A run without them deals its groups to the waves in turn, the last
+// quarter of the rounds (two at least) by ticket because waves drift apart; short groups (N < 64) are all dealt,
+// as those rounds would take less than their tickets.
+inline PathWork split_paths(uint64_t n_paths, int s, int slots, size_t fine_bytes, uint64_t resident, int wg_waves) {
+    PathWork w{};
+    w.n_groups = (n_paths + 63) / 64;
+    w.n_chunks = (n_paths + kChunkPaths - 1) / kChunkPaths;
+    const uint64_t wgs = std::max<uint64_t>(resident, 1), waves = wgs * uint64_t(wg_waves);
+    if (slots) {
+        const uint64_t fit = fine_bytes / (size_t(slots) * kChunkGroups * 24);
+        w.n_coarse = whole_chunks(w.n_chunks, s, wgs);
+        if (w.n_chunks - w.n_coarse > fit) w.n_coarse = w.n_chunks - fit;
+    }
+    w.grab = ticket_groups(s);
+    if (!w.n_coarse) {
+        const uint64_t rounds = w.n_groups / waves, tail = std::max<uint64_t>(rounds / 4, 2);
+        if (rounds < 8 * w.grab) w.grab = 1;
+        w.n_static = s < 6 || rounds < 1 ? w.n_groups : (rounds > tail ? (rounds - tail) * waves : 0);
+    }
+    return w;
+}
+// Bytes of its group sums.
+inline size_t group_sum_bytes(const PathWork& w, int slots) { return size_t(slots) * size_t(w.fine()) * 24; }
+// Workgroups of `waves_per_wg` waves that this work can occupy, at most `resident`.
+inline int work_grid(const PathWork& w, int waves_per_wg, int resident) {
+    const uint64_t wgs = w.n_coarse + ((w.fine() + w.grab - 1) / w.grab + uint64_t(waves_per_wg) - 1) / uint64_t(waves_per_wg);
+    const uint64_t most = uint64_t(resident < 1 ? 1 : resident);
+    return int(wgs < 1 ? 1 : (wgs < most ? wgs : most));
+}
+
+}  // namespace pimc

@@ -524,7 +524,7 @@ int vector_amplitude_core(pimc_ctx* c, const VecProblem& P, uint64_t n_samples, 
     st = ensure(c, reinterpret_cast<void**>(&c->d_partials), &c->partial_bytes, size_t(slots) * n_chunks * 4 * 8);
     if (st) return st;
     const int resident = vector_resident(c, P);
-    PathWork pw = split_paths(n_samples, P.s, slots, kFineBytes, uint64_t(resident) * (kVecBlock / 64));
+    PathWork pw = split_paths(n_samples, P.s, slots, kFineBytes, uint64_t(resident), kVecBlock / 64);
     st = ensure(c, reinterpret_cast<void**>(&c->d_gsum), &c->gsum_bytes, group_sum_bytes(pw, slots));
     if (st) return st;
     pw.gsum = c->d_gsum;
@@ -594,7 +594,7 @@ int vector_path_actions_core(pimc_ctx* c, const VecProblem& P, uint64_t seed, ui
     A.dump = c->d_dump;
     const int resident = vector_resident(c, P);
     unsigned long long* const queue = A.work.queue;
-    A.work = split_paths(k_paths, P.s, 0, 0, uint64_t(resident) * (kVecBlock / 64));
+    A.work = split_paths(k_paths, P.s, 0, 0, uint64_t(resident), kVecBlock / 64);
     A.work.queue = queue;
     const int grid = work_grid(A.work, kVecBlock / 64, resident);
     HIP_TRY(c, P.poly ? launch_vector_poly(A, P.dim, P.U, grid, c->stream)

@@ -151,11 +151,11 @@ __device__ __forceinline__ void walk_path(const Eval& ev, const AmpArgs& A, cons
 }
 
 // ---------------------------------------------------------------------------- estimation kernel
-// One group: paths 64 g + lane of the run described by A. Its level sums go to the sink k (slot = level
-// with every level evaluated, else 0 for level s) when A.partials is set, the per-path level actions to
-// A.dump when that is. bm: the Box-Muller table, top: this lane's stack (both LDS).
+// One group: paths 64 g + lane of the run described by A. Its level sums are added to the accumulator slot
+// acc (level n at 3 n with every level evaluated, else level s at 0) when A.partials is set, the per-path
+// level actions go to A.dump when that is. bm: the Box-Muller table, top: this lane's stack (both LDS).
 template <class S, class Eval>
-__device__ __forceinline__ void process_group(const Eval& ev, const AmpArgs& A, uint64_t g, const GroupSink& k,
+__device__ __forceinline__ void process_group(const Eval& ev, const AmpArgs& A, uint64_t g, double* acc,
                                               const double* bm, double* top) {
     constexpr int U = S::U;
     constexpr int BS = S::BS;
@@ -175,16 +175,17 @@ __device__ __forceinline__ void process_group(const Eval& ev, const AmpArgs& A, 
     if (A.partials) {
         const const_ptr<double> shift = as_const(A.shift);
         if (A.hier) {
-            for (int n = 0; n < D; ++n) reduce_level(k, lane, n, top[n * BS], shift[n], valid);
+            for (int n = 0; n < D; ++n) reduce_level(acc + n * 3, lane, top[n * BS], shift[n], valid);
 #pragma unroll
-            for (int j = 0; j < U; ++j) reduce_level(k, lane, D + j, Ssub[j], shift[D + j], valid);
+            for (int j = 0; j < U; ++j) reduce_level(acc + (D + j) * 3, lane, Ssub[j], shift[D + j], valid);
         }
-        reduce_level(k, lane, A.hier ? D + U : 0, Ssub[U], shift[D + U], valid);
+        reduce_level(acc + (A.hier ? D + U : 0) * 3, lane, Ssub[U], shift[D + U], valid);
     }
 }
 
 // LDS of a workgroup: the Box-Muller table, the per-lane stacks, the accumulator slots.
-template <class S, class Eval>
+// WHOLE: a run of whole chunks alone.
+template <class S, class Eval, bool WHOLE>
 __global__ void __launch_bounds__(S::BS) __attribute__((amdgpu_waves_per_eu(S::WPE)))
 k_amplitude(AmpArgs A, Eval ev) {
     extern __shared__ double smem[];
@@ -192,15 +193,30 @@ k_amplitude(AmpArgs A, Eval ev) {
     __syncthreads();
     double* top = smem + kBoxMullerTable + threadIdx.x;
     double* acc = smem + kBoxMullerTable + size_t(3 * A.D + 2) * S::BS;
-    run_groups<S::BS>(A.work, A.s + 1, A.hier, A.n_paths, A.partials, acc, [&](uint64_t g, const GroupSink& k) __attribute__((always_inline)) {
-        process_group<S, Eval>(ev, A, g, k, smem, top);
-    });
+    auto run = [&](uint64_t g, double* a) __attribute__((always_inline)) {
+        process_group<S, Eval>(ev, A, g, a, smem, top);
+    };
+    if constexpr (WHOLE)
+        run_chunks<S::BS>(A.work, A.s + 1, A.hier, A.n_paths, A.partials, acc, run);
+    else
+        run_groups<S::BS>(A.work, A.s + 1, A.hier, A.n_paths, A.partials, acc, run);
 }
+
+// Whether an evaluator has the kernel for whole chunks alone: the quick ones, whose groups cost so little that
+// the other form's additional state shows (1e8 paths, p = 1: N = 16, every level 5.38 ms in the other form, 5.16
+// in this one; N = 2 0.97 and 0.91).
+template <class Eval> constexpr bool kWholeKernel = true;
 
 template <class S, class Eval>
 inline hipError_t launch_one(const AmpArgs& A, const Eval& ev, int grid, LaunchOn st) {
     const size_t lds = amp_lds_bytes(A.D, A.s, S::BS);
-    hipExtLaunchKernelGGL((k_amplitude<S, Eval>), dim3(grid), dim3(S::BS), lds, st.st, st.start, st.stop, 0, A, ev);
+    if constexpr (kWholeKernel<Eval>) {
+        if (A.partials && A.work.n_coarse == A.work.n_chunks) {
+            hipExtLaunchKernelGGL((k_amplitude<S, Eval, true>), dim3(grid), dim3(S::BS), lds, st.st, st.start, st.stop, 0, A, ev);
+            return hipGetLastError();
+        }
+    }
+    hipExtLaunchKernelGGL((k_amplitude<S, Eval, false>), dim3(grid), dim3(S::BS), lds, st.st, st.start, st.stop, 0, A, ev);
     return hipGetLastError();
 }
 
@@ -226,7 +242,7 @@ inline hipError_t launch_line(const AmpArgs& A, const Eval& ev, double* parts, h
 template <class S, class Eval>
 inline int resident_one(size_t lds, int device) {
     int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_amplitude<S, Eval>, S::BS, lds) != hipSuccess)
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_amplitude<S, Eval, false>, S::BS, lds) != hipSuccess)
         per_cu = 1;
     int ncu = 0;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) ncu = 256;

@@ -1,0 +1,39 @@
+"""The rules by which runs are shared out between whole chunks and groups (host code, no device use):
+every group once, within the room for group sums, and no more tickets than their groups' work covers."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1105_0542_amd", "csrc")
+TICKET_NS = 12.4               # of the whole GPU, one address
+SLICE_NS = 64 / 550.0          # of the whole GPU: 64 paths of one slice at the cheapest rate, 5.5e11 slices a second
+
+
+@pytest.fixture(scope="module")
+def lines(tmp_path_factory):
+    if shutil.which("g++") is None:
+        pytest.skip("no host compiler")
+    exe = str(tmp_path_factory.mktemp("split") / "check_split")
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-I", os.path.join(ROOT, "include"), "-I", CSRC,
+                    os.path.join(ROOT, "tests", "native", "check_split.cpp"), "-o", exe], check=True)
+    return [ln.split() for ln in subprocess.run([exe], check=True, capture_output=True, text=True).stdout.splitlines()]
+
+
+def test_runs(lines):
+    runs = [[int(x) for x in ln[1:]] for ln in lines if ln[0] == "run"]
+    assert len(runs) > 1000
+    kinds = set()
+    for wgs, s, slots, n, groups, chunks, coarse, fine, dealt, grab in runs:
+        case = (wgs, s, slots, n)
+        assert groups == -(-n // 64) and chunks == -(-n // 4096), case
+        assert 0 <= coarse <= chunks and coarse * 64 + fine == max(groups, coarse * 64), case
+        assert fine * slots * 24 <= 16 << 20 and grab >= 1, case
+        assert (coarse == 0 or slots > 0) and dealt <= fine and (dealt == 0 or coarse == 0), case
+        tickets = -(-(fine - dealt) // grab)
+        # two rounds of single tickets for the 4 waves of a workgroup may be waited for, not more
+        assert tickets * TICKET_NS <= (fine - dealt) * (1 << s) * SLICE_NS + 2 * 4 * wgs * TICKET_NS, case
+        kinds.add((coarse > 0, fine > 0, dealt > 0))
+    assert kinds >= {(False, True, True), (True, False, False), (True, True, False)}
