@@ -105,8 +105,7 @@ k_batch(BatchArgs B, Eval ev0) {
             ev.tab = T[lo].tab;
             const int nlev = A.s + 1;
             const uint64_t n_groups = (A.n_paths + 63) / 64;
-            // behind the deepest stack of the class: the waves of a workgroup may be in tasks of different N
-            double* acc = smem + kBoxMullerTable + size_t(3 * (B.smax - S::U) + 2) * S::BS;
+            double* acc = smem + kBoxMullerTable + size_t(3 * A.D + 2) * S::BS;
             uint64_t g = item - T[lo].item0, last, step = 1;
             if (BY_GROUP) {
                 g *= T[lo].block;
@@ -120,11 +119,10 @@ k_batch(BatchArgs B, Eval ev0) {
             }
             if (last > n_groups) last = n_groups;
             for (; g < last; g += step) {
-                // by group the sums are formed in the slot of this wave's number
-                double* a = acc + (BY_GROUP ? wave * (B.smax + 1) : int(g % kChunkSlots) * nlev) * 3;
-                if (BY_GROUP) clear_slot(a, nlev);
-                process_group<S, Eval>(ev, A, g, a, smem, smem + kBoxMullerTable + tid);
-                if (BY_GROUP) store_slot(a, B.hier ? nlev : 1, T[lo].gsum + g * 3, n_groups * 3);
+                process_group<S, Eval>(ev, A, g, [&]() __attribute__((always_inline)) {
+                    if constexpr (BY_GROUP) return GroupSink{false, nullptr, (gdouble*)T[lo].gsum + g * 3, n_groups * 3};
+                    return GroupSink{true, acc + int(g % kChunkSlots) * nlev * 3, nullptr, 0};
+                }, smem, smem + kBoxMullerTable + tid);
             }
             if (!BY_GROUP) {
                 __syncthreads();

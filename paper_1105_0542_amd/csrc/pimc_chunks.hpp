@@ -30,34 +30,36 @@ __device__ __forceinline__ uint64_t uniform_u64(uint64_t v) {
 }
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
 
-// Adds the sums of one level over a group to an accumulator slot a (LDS; sum d, sum d^2, non-finite count):
-// d and d^2 by a wave butterfly, the non-finite count by a ballot.
-__device__ __forceinline__ void reduce_level(double* a, int lane, double S, double shift, bool valid) {
+// Where lane 0 puts a group's level sums (sum d, sum d^2, non-finite count): added to an accumulator
+// slot in LDS (whole chunks), or stored to the group's place in device memory (stride: doubles between levels).
+typedef __attribute__((address_space(1))) double gdouble;
+struct GroupSink {
+    bool whole;
+    double* acc;                       // LDS, 3 doubles per level
+    gdouble* out;
+    uint64_t stride;
+};
+
+// The sums of one level over a group: d and d^2 by a wave butterfly, the non-finite count by a ballot.
+__device__ __forceinline__ void reduce_level(const GroupSink& k, int lane, int slot, double S, double shift, bool valid) {
     const double d = valid ? expm1(-(S - shift)) : 0.0;
     const bool bad = valid && !isfinite(d);
     const double sd = wave_sum(d);
     const double sd2 = wave_sum(d * d);
-    const unsigned long long badmask = __ballot(bad);
+    const double nb = double(__popcll(__ballot(bad)));
     if (lane == 0) {
-        a[0] += sd;
-        a[1] += sd2;
-        a[2] += double(__popcll(badmask));
+        if (k.whole) {
+            double* a = k.acc + slot * 3;
+            a[0] += sd;
+            a[1] += sd2;
+            a[2] += nb;
+        } else {
+            gdouble* a = k.out + uint64_t(slot) * k.stride;
+            a[0] = sd;
+            a[1] = sd2;
+            a[2] = nb;
+        }
     }
-}
-
-// A wave's own accumulator slot: cleared before a group, and stored to the group's place in device memory
-// (`stride` doubles between levels) after it. Lane 0 adds in between; a wave's LDS accesses are in order.
-static_assert(PIMC_MAX_S + 1 <= 21, "a slot is at most 63 doubles, one per lane");
-__device__ __forceinline__ void clear_slot(double* a, int nlev) {
-    const int i = int(threadIdx.x & 63u);
-    if (i < nlev * 3) a[i] = 0.0;
-    __builtin_amdgcn_wave_barrier();
-}
-__device__ __forceinline__ void store_slot(const double* a, int slots, double* out, uint64_t stride) {
-    const int i = int(threadIdx.x & 63u);
-    __builtin_amdgcn_wave_barrier();
-    if (i < slots * 3) out[uint64_t(i / 3) * stride + uint64_t(i % 3)] = a[i];
-    __builtin_amdgcn_wave_barrier();
 }
 
 // A whole chunk's record from its accumulator slots, by one thread per evaluated level (tid < slots).
@@ -96,7 +98,9 @@ __device__ __forceinline__ void run_chunks(const PathWork& w, int nlev, int hier
         __syncthreads();
         for (int g = wave; g < kChunkGroups; g += BS / 64) {
             if ((c * kChunkGroups + uint64_t(g)) * 64 >= n_paths) break;   // wave-uniform: the rest of the chunk is empty
-            run(c * kChunkGroups + uint64_t(g), acc + (g % kChunkSlots) * nlev * 3);
+            run(c * kChunkGroups + uint64_t(g), [&]() __attribute__((always_inline)) {
+                return GroupSink{true, acc + (g % kChunkSlots) * nlev * 3, nullptr, 0};
+            });
         }
         __syncthreads();
         write_chunk(acc, nlev, hier, partials, w.n_chunks, c, n_paths, tid);
@@ -112,10 +116,9 @@ struct SharedWork {
     unsigned long long chunk;          // the whole chunk in hand
 };
 
-// The persistent loop of one workgroup of BS threads. run(group, a) walks the 64 paths of a group
-// and adds their sums to the accumulator slot a (one call site: its code is the whole kernel); acc: the
-// slots in LDS, kChunkSlots * nlev * 3 doubles, a wave's own number among them. Every wave of a workgroup
-// leaves the coarse phase at the same ticket, so its barriers are met by all. A ticket for fine groups is asked for before the groups of
+// The persistent loop of one workgroup of BS threads. run(group, sink) walks the 64 paths of a group
+// and reduces them into sink() (one call site: its code is the whole kernel); acc: the accumulator
+// slots in LDS, kChunkSlots * nlev * 3 doubles. Every wave of a workgroup leaves the coarse phase at the same ticket, so its barriers are met by all. A ticket for fine groups is asked for before the groups of
 // the one in hand are walked (the answer is back long before it is needed); one for a chunk only when the
 // workgroup is free, or the last chunks would go to workgroups that are still at their last but one.
 template <int BS, class RunGroup>
@@ -176,11 +179,10 @@ __device__ __forceinline__ void run_groups(const PathWork& w, int nlev, int hier
         const uint64_t end = uniform_u64(sw.w.n_groups);
         if (last > end) last = end;
         for (; g < last; g += step) {
-            // a fine group's sums are formed in the slot of this wave's number
-            double* a = acc + (coarse ? int(g % kChunkSlots) : wave) * nlev * 3;
-            if (!coarse) clear_slot(a, nlev);
-            run(g, a);
-            if (!coarse && partials) store_slot(a, hier ? nlev : 1, sw.w.gsum + (g - sw.fine0) * 3, sw.n_fine * 3);
+            run(g, [&]() __attribute__((always_inline)) {
+                if (coarse) return GroupSink{true, acc + int(g % kChunkSlots) * nlev * 3, nullptr, 0};
+                return GroupSink{false, nullptr, (gdouble*)sw.w.gsum + (g - sw.fine0) * 3, sw.n_fine * 3};
+            });
         }
         if (coarse) {
             __syncthreads();

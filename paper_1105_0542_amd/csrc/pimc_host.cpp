@@ -904,7 +904,6 @@ hipError_t launch_class(pimc_batch* b, size_t k, hipStream_t st) {
     B.grab = b->grab;
     B.n_tasks = C.n_tasks;
     B.by_group = b->d_gsum ? 1 : 0;
-    B.smax = C.smax;
     B.hier = (b->flags & PIMC_HIERARCHY) ? 1 : 0;
     return launch_batch(B, C.p, C.n16, C.shape, class_grid(b, C), C.lds, st);
 }

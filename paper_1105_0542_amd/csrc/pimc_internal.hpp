@@ -196,7 +196,6 @@ struct BatchArgs {
     uint32_t grab;                     // items per ticket
     int n_tasks;
     int by_group;
-    int smax;                          // largest s of the class
     int hier;
 };
 

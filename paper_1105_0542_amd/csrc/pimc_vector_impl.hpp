@@ -604,10 +604,10 @@ __device__ __forceinline__ void walk_path(const Eval& ev, const VecArgs& A, cons
 }
 
 // ---------------------------------------------------------------------------- estimation kernel
-// One group: paths 64 g + lane (the group of the one-dimensional kernels); level sums to the slot acc,
+// One group: paths 64 g + lane (the group of the one-dimensional kernels); level sums to sink(),
 // per-path level actions to A.dump. bm: the Box-Muller table, top: this lane's stack (both LDS).
-template <int DIM, int U, class Eval>
-__device__ __forceinline__ void process_group(const Eval& ev, const VecArgs& A, uint64_t g, double* acc,
+template <int DIM, int U, class Eval, class Sink>
+__device__ __forceinline__ void process_group(const Eval& ev, const VecArgs& A, uint64_t g, Sink sink,
                                               const double* bm, double* top) {
     const int lane = threadIdx.x & 63;
     const int D = A.D;
@@ -623,13 +623,14 @@ __device__ __forceinline__ void process_group(const Eval& ev, const VecArgs& A, 
         for (int j = 0; j <= U; ++j) o[D + j] = (A.hier || j == U) ? Ssub[j] : 0.0;
     }
     if (A.partials) {
+        const GroupSink k = sink();
         const const_ptr<double> shift = as_const(A.shift);
         if (A.hier) {
-            for (int n = 0; n < D; ++n) reduce_level(acc + n * 3, lane, top[n * kVecBlock], shift[n], valid);
+            for (int n = 0; n < D; ++n) reduce_level(k, lane, n, top[n * kVecBlock], shift[n], valid);
 #pragma unroll
-            for (int j = 0; j < U; ++j) reduce_level(acc + (D + j) * 3, lane, Ssub[j], shift[D + j], valid);
+            for (int j = 0; j < U; ++j) reduce_level(k, lane, D + j, Ssub[j], shift[D + j], valid);
         }
-        reduce_level(acc + (A.hier ? D + U : 0) * 3, lane, Ssub[U], shift[D + U], valid);
+        reduce_level(k, lane, A.hier ? D + U : 0, Ssub[U], shift[D + U], valid);
     }
 }
 
@@ -642,8 +643,8 @@ k_amplitude_vec(VecArgs A, Eval ev) {
     __syncthreads();
     double* top = smem + kBoxMullerTable + threadIdx.x;
     double* acc = smem + kBoxMullerTable + size_t(vec_top_slots(DIM, A.D)) * kVecBlock;
-    run_groups<kVecBlock>(A.work, A.s + 1, A.hier, A.n_paths, A.partials, acc, [&](uint64_t g, double* a) __attribute__((always_inline)) {
-        process_group<DIM, U, Eval>(ev, A, g, a, smem, top);
+    run_groups<kVecBlock>(A.work, A.s + 1, A.hier, A.n_paths, A.partials, acc, [&](uint64_t g, auto sink) __attribute__((always_inline)) {
+        process_group<DIM, U, Eval>(ev, A, g, sink, smem, top);
     });
 }
 

@@ -151,11 +151,11 @@ __device__ __forceinline__ void walk_path(const Eval& ev, const AmpArgs& A, cons
 }
 
 // ---------------------------------------------------------------------------- estimation kernel
-// One group: paths 64 g + lane of the run described by A. Its level sums are added to the accumulator slot
-// acc (level n at 3 n with every level evaluated, else level s at 0) when A.partials is set, the per-path
-// level actions go to A.dump when that is. bm: the Box-Muller table, top: this lane's stack (both LDS).
-template <class S, class Eval>
-__device__ __forceinline__ void process_group(const Eval& ev, const AmpArgs& A, uint64_t g, double* acc,
+// One group: paths 64 g + lane of the run described by A. Its level sums go to sink() (slot = level
+// with every level evaluated, else 0 for level s) when A.partials is set, the per-path level actions to
+// A.dump when that is. bm: the Box-Muller table, top: this lane's stack (both LDS).
+template <class S, class Eval, class Sink>
+__device__ __forceinline__ void process_group(const Eval& ev, const AmpArgs& A, uint64_t g, Sink sink,
                                               const double* bm, double* top) {
     constexpr int U = S::U;
     constexpr int BS = S::BS;
@@ -173,13 +173,14 @@ __device__ __forceinline__ void process_group(const Eval& ev, const AmpArgs& A, 
         for (int j = 0; j <= U; ++j) o[D + j] = (A.hier || j == U) ? Ssub[j] : 0.0;
     }
     if (A.partials) {
+        const GroupSink k = sink();
         const const_ptr<double> shift = as_const(A.shift);
         if (A.hier) {
-            for (int n = 0; n < D; ++n) reduce_level(acc + n * 3, lane, top[n * BS], shift[n], valid);
+            for (int n = 0; n < D; ++n) reduce_level(k, lane, n, top[n * BS], shift[n], valid);
 #pragma unroll
-            for (int j = 0; j < U; ++j) reduce_level(acc + (D + j) * 3, lane, Ssub[j], shift[D + j], valid);
+            for (int j = 0; j < U; ++j) reduce_level(k, lane, D + j, Ssub[j], shift[D + j], valid);
         }
-        reduce_level(acc + (A.hier ? D + U : 0) * 3, lane, Ssub[U], shift[D + U], valid);
+        reduce_level(k, lane, A.hier ? D + U : 0, Ssub[U], shift[D + U], valid);
     }
 }
 
@@ -193,8 +194,8 @@ k_amplitude(AmpArgs A, Eval ev) {
     __syncthreads();
     double* top = smem + kBoxMullerTable + threadIdx.x;
     double* acc = smem + kBoxMullerTable + size_t(3 * A.D + 2) * S::BS;
-    auto run = [&](uint64_t g, double* a) __attribute__((always_inline)) {
-        process_group<S, Eval>(ev, A, g, a, smem, top);
+    auto run = [&](uint64_t g, auto sink) __attribute__((always_inline)) {
+        process_group<S, Eval>(ev, A, g, sink, smem, top);
     };
     if constexpr (WHOLE)
         run_chunks<S::BS>(A.work, A.s + 1, A.hier, A.n_paths, A.partials, acc, run);
