@@ -39,8 +39,8 @@ VARIANTS += [("pimc_general_inline.hip", ["-DPIMC_GEN_LO=1", "-DPIMC_GEN_HI=4"],
              ("pimc_general_inline.hip", ["-DPIMC_GEN_LO=5", "-DPIMC_GEN_HI=10"] + NO_LICM, "pimc_general_inline_5")]
 # One translation unit per dimension for the component evaluator's kernels, and one more for the
 # deepest subtree of d = 3 and 4 (empty where that depth is below the split).
-VARIANTS += [("pimc_vector_poly.hip", [f"-DPIMC_POLY_DIM={d}"] + (NO_LICM if d < 3 else []), f"pimc_vector_poly_d{d}") for d in (1, 2, 3, 4)]
-VARIANTS += [("pimc_vector_poly.hip", [f"-DPIMC_POLY_DIM={d}", "-DPIMC_POLY_DEEP=1"], f"pimc_vector_poly_d{d}_deep")
+VARIANTS += [("pimc_vector_poly.hip", [f"-DPIMC_POLY_DIM={d}"] + NO_LICM, f"pimc_vector_poly_d{d}") for d in (1, 2, 3, 4)]
+VARIANTS += [("pimc_vector_poly.hip", [f"-DPIMC_POLY_DIM={d}", "-DPIMC_POLY_DEEP=1"] + NO_LICM, f"pimc_vector_poly_d{d}_deep")
              for d in (3, 4)]
 
 # -ffp-contract=off: every fused multiply-add in the kernels is written as fma(); no other

@@ -414,13 +414,16 @@ __device__ __forceinline__ void hier_levels(const Eval& ev, int D, const double 
 }
 
 // The component evaluator is a long instruction sequence, and a copy of it (and of the normals) per batch of
-// a subtree is far more than the instruction cache holds: its subtrees are loops over the levels, with one
+// a subtree is far more than the instruction cache holds: its deep subtrees are loops over the levels, with one
 // copy per batch width and the points in scratch memory. d = 2, p = 10, N = 256, 5e5 paths: 13.6 -> 12.1 ms (with
 // subtrees of six levels; of five 13.7, and of five without the loops 13.6), p = 8 2.11 -> 1.83; d = 3, p = 5,
-// N = 128, 5e4 paths 1.23 -> 1.12 ms. One coordinate is faster unrolled (N = 128, p = 9, level s alone 362 us,
-// 465 in loops), and four (N = 128, p = 4: 0.76 ms, 1.14).
-template <class Eval> constexpr bool kRolled = false;
-template <int DIM> constexpr bool kRolled<PolyEvalRT<DIM>> = DIM == 2 || DIM == 3;
+// N = 128, 5e4 paths 1.23 -> 1.12 ms. Subtrees of two to four levels, those of N = 4..16, fit the registers and
+// are faster unrolled (2.1e6 paths, level s alone: d = 3, p = 2, N = 8 0.56 ms in loops, 0.26 unrolled; d = 2,
+// p = 2, N = 16 0.40 and 0.31), of five not (d = 2, p = 2, N = 32 0.70 and 0.81), and of one the same code is in
+// one place instead of three (d = 3, p = 5 0.33 and 0.42). One coordinate is faster unrolled (N = 128, p = 9,
+// level s alone 362 us, 465 in loops), and four (N = 128, p = 4: 0.76 ms, 1.14).
+template <class Eval, int U> constexpr bool kRolled = false;
+template <int DIM, int U> constexpr bool kRolled<PolyEvalRT<DIM>, U> = (DIM == 2 || DIM == 3) && (U == 1 || U >= 5);
 
 template <int DIM, int U, int B, class Eval>
 __device__ __forceinline__ void rolled_batch(const Eval& ev, int level, int sh, int b0,
@@ -492,7 +495,7 @@ __device__ __forceinline__ void run_subtree(const Eval& ev_in, const VecArgs& A,
         q[1 << U][c] = qR[c];
         q[1 << (U - 1)][c] = sg * zroot[c] + 0.5 * (qL[c] + qR[c]);
     }
-    if constexpr (kRolled<Eval>) {
+    if constexpr (kRolled<Eval, U>) {
         rolled_levels<DIM, U, Eval>(ev, A, src, root, D, q, Ssub);
         return;
     }
@@ -520,7 +523,7 @@ __device__ __forceinline__ void walk_path(const Eval& ev, const VecArgs& A, cons
         double unused[DIM];
         src.pair(0u, unused, z1);                    // node 1 = sine output of call 0
     }
-    if constexpr (!kRolled<Eval>) {
+    if constexpr (!kRolled<Eval, U>) {
         if (D == 0) {
             run_subtree<DIM, U, Eval>(ev, A, src, 1u, 0, a, b, z1, Ssub);
             return;
@@ -555,7 +558,7 @@ __device__ __forceinline__ void walk_path(const Eval& ev, const VecArgs& A, cons
             src.node(node, z);
         }
         double qm[DIM], zl[DIM], zr[DIM];
-        while (!kRolled<Eval> || D > 0) {
+        while (!kRolled<Eval, U> || D > 0) {
             if (A.hier) {
                 double qa1[1][DIM], qb1[1][DIM];
 #pragma unroll
@@ -581,7 +584,7 @@ __device__ __forceinline__ void walk_path(const Eval& ev, const VecArgs& A, cons
             node = 2u * node;
             ++L;
         }
-        if constexpr (kRolled<Eval>) {               // one copy: both sides, or the whole tree (D = 0)
+        if constexpr (kRolled<Eval, U>) {               // one copy: both sides, or the whole tree (D = 0)
             const int sides = D > 0 ? 2 : 1;
 #pragma unroll 1
             for (int side = 0; side < sides; ++side) {

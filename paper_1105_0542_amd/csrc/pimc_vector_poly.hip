@@ -3,9 +3,9 @@
 // subtrees of up to kPolyU1 (kPolyU, kPolyU3) levels make these the largest kernels of the vector mode). With
 // PIMC_POLY_DEEP it holds only the deepest subtree of that dimension, when that is kPolySplitU
 // levels or more, so that the deepest and the shallower kernels compile in parallel.
-// One and two coordinates are built without loop-invariant code motion on machine code (as
-// pimc_general_inline.hip): 6e5 paths, N = 256, d = 1, p = 8 1.10 -> 1.00 ms; d = 2, p = 10 14.9 -> 14.6 (before its levels were loops); three
-// and four coordinates the same with and without.
+// Built without loop-invariant code motion on machine code (as pimc_general_inline.hip), with and without it:
+// 6e5 paths, N = 256, d = 1, p = 8 1.02 and 0.98 ms; 5e5 paths, N = 256, d = 2, p = 10 12.0 both; 5e4 paths, N = 128,
+// d = 3, p = 5 1.13 and 1.03; 2.1e6 paths, N = 16, d = 4, p = 4, level s alone 1.88 and 1.31.
 #include "pimc_vector_impl.hpp"
 
 #ifndef PIMC_POLY_DIM
