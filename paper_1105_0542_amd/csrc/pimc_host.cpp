@@ -83,9 +83,10 @@ int pinned_stage(pimc_ctx* c, size_t need, unsigned char** out) {
     return PIMC_OK;
 }
 
-// One launch (k_seg_groups) up to this many chunks, all fine: 25 chunks x 5 levels 7 us against 6 + 3.5
-// us and a gap for the two; beyond, its one workgroup per level is slower than k_group_chunks' many.
-static bool short_run(const PathWork& w) { return w.n_coarse == 0 && w.n_chunks <= 128; }
+// One launch (k_seg_groups) up to kShortSegment chunks, all fine; beyond, its one workgroup per level is slower
+// than k_group_chunks' many and a second launch. Whole calls, N = 16, level s alone, one launch and two: 25
+// chunks 50.2 and 56.0 us, 64 54.9 and 60.0, 128 69.0 and 69.6, 192 82.3 and 79.3, 512 153 and 126.
+static bool short_run(const PathWork& w) { return w.n_coarse == 0 && w.n_chunks <= kShortSegment; }
 
 std::vector<unsigned char> run_segments(const PathWork& w, int slots, uint64_t n_paths, double* partials) {
     std::vector<unsigned char> out;
@@ -846,7 +847,9 @@ struct pimc_batch {
     BatchTask* d_tasks = nullptr;
     double* d_partials = nullptr;
     double* d_gsum = nullptr;                  // group sums (by group), else null
-    GroupSegment* d_gseg = nullptr;
+    GroupSegment* d_gseg = nullptr;            // the segments; with `pieces`, in pieces of kPieceChunks chunks
+    uint64_t n_gseg = 0;
+    bool pieces = false;                       // a long segment: chunk records first, then one reduction
     uint64_t* d_seg = nullptr;
     double* d_red = nullptr;
     unsigned long long* d_queue = nullptr;
@@ -930,9 +933,12 @@ int capture_graph(pimc_batch* b) {
     HIP_TRY_B(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
     hipError_t e = launch_fill_u64(b->d_queue, int(b->classes.size()), 0ull, b->stream);
     for (size_t k = 0; k < b->classes.size() && e == hipSuccess; ++k) e = launch_class(b, k, b->stream);
-    if (e == hipSuccess)
-        e = b->d_gsum ? launch_seg_groups(b->d_gseg, b->n_seg, b->d_red, b->stream)
-                      : launch_seg_reduce(b->d_partials, b->d_seg, b->d_seg + b->n_seg, b->n_seg, b->d_red, b->stream);
+    if (b->d_gsum && !b->pieces) {
+        if (e == hipSuccess) e = launch_seg_groups(b->d_gseg, b->n_gseg, b->d_red, b->stream);
+    } else {
+        if (e == hipSuccess && b->pieces) e = launch_group_records(b->d_gseg, b->n_gseg, b->stream);
+        if (e == hipSuccess) e = launch_seg_reduce(b->d_partials, b->d_seg, b->d_seg + b->n_seg, b->n_seg, b->d_red, b->stream);
+    }
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->h_red, b->d_red, b->n_seg * 4 * 8, hipMemcpyDeviceToHost, b->stream);
     hipGraph_t g = nullptr;
@@ -1108,7 +1114,6 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
     if ((st = dmalloc(reinterpret_cast<void**>(&b->d_partials), part_total * 4 * 8))) return fail(st);
     if (by_group) {
         if ((st = dmalloc(reinterpret_cast<void**>(&b->d_gsum), gsum_total * 24))) return fail(st);
-        if ((st = dmalloc(reinterpret_cast<void**>(&b->d_gseg), b->n_seg * sizeof(GroupSegment)))) return fail(st);
     }
     if ((st = dmalloc(reinterpret_cast<void**>(&b->d_seg), b->n_seg * 2 * 8))) return fail(st);
     if ((st = dmalloc(reinterpret_cast<void**>(&b->d_red), b->n_seg * 4 * 8))) return fail(st);
@@ -1161,14 +1166,21 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
     std::copy(seg_base.begin(), seg_base.end(), seg.begin());
     std::copy(seg_len.begin(), seg_len.end(), seg.begin() + b->n_seg);
     std::vector<GroupSegment> gseg;
-    if (by_group)
-        for (size_t pos = 0; pos < n_tasks; ++pos) {
-            const size_t i = order[pos];
-            const uint64_t groups = (tasks[i].n_samples + 63) / 64;
+    if (by_group) {
+        for (size_t i = 0; i < n_tasks; ++i)
+            if (t_chunks[i] > kShortSegment) b->pieces = true;
+        const uint64_t most = b->pieces ? kPieceChunks : kShortSegment;
+        for (size_t i : order) {
+            const uint64_t n = tasks[i].n_samples, groups = (n + 63) / 64;
             for (int k = 0; k < (hier ? b->t_s[i] + 1 : 1); ++k)
-                gseg.push_back(GroupSegment{b->d_gsum + t_gsum_off[i] + uint64_t(k) * groups * 3,
-                                            b->d_partials + seg_base[b->t_seg[i] + size_t(k)], tasks[i].n_samples});
+                for (uint64_t c = 0; c < t_chunks[i]; c += most)
+                    gseg.push_back(GroupSegment{b->d_gsum + t_gsum_off[i] + (uint64_t(k) * groups + c * kChunkGroups) * 3,
+                                                b->d_partials + seg_base[b->t_seg[i] + size_t(k)] + c * 4,
+                                                std::min(n - c * kChunkPaths, most * kChunkPaths)});
         }
+        b->n_gseg = gseg.size();
+        if ((st = dmalloc(reinterpret_cast<void**>(&b->d_gseg), b->n_gseg * sizeof(GroupSegment)))) return fail(st);
+    }
     HIP_TRY_B(b, hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking));
     HIP_TRY_B(b, hipEventCreate(&b->e0));
     HIP_TRY_B(b, hipEventCreate(&b->e1));

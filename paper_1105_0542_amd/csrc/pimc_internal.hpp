@@ -169,6 +169,11 @@ struct GroupSegment {
 };
 // Chunk records and canonical reduction of such segments: out[i][4] (all device).
 hipError_t launch_seg_groups(const GroupSegment* segs, uint64_t n_seg, double* out, hipStream_t st);
+// The chunk records alone, of pieces of at most kPieceChunks chunks (a long segment is several).
+constexpr uint64_t kPieceChunks = kBlock / 4;
+hipError_t launch_group_records(const GroupSegment* pieces, uint64_t n_pieces, hipStream_t st);
+// Above this many chunks a segment's records are formed by many workgroups instead of its own one.
+constexpr uint64_t kShortSegment = 128;
 
 // One task of a batch, as the persistent kernel reads it (device array, wave-uniform loads).
 struct BatchTask {

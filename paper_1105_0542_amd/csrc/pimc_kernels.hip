@@ -136,21 +136,35 @@ __global__ void __launch_bounds__(kBlock) k_seg_reduce(const double* __restrict_
 
 // The same from group sums: the workgroup first forms its segment's chunk records (64 quads), then
 // reduces them. One launch instead of two, for segments of few chunks.
-__global__ void __launch_bounds__(kBlock) k_seg_groups(const GroupSegment* __restrict__ segs, double* __restrict__ out) {
+__device__ __forceinline__ uint64_t group_records(const GroupSegment* __restrict__ segs) {
     const const_ptr<GroupSegment> S = as_const(segs) + blockIdx.x;
     const double* gsum = S->gsum;
     double* rec = S->records;
     const uint64_t n_paths = S->n_paths;
     const uint64_t n_groups = (n_paths + 63) / 64;
     const uint64_t n_chunks = (n_paths + kChunkPaths - 1) / kChunkPaths;
-    for (uint64_t c0 = 0; c0 < n_chunks; c0 += kBlock / 4) {
+    for (uint64_t c0 = 0; c0 < n_chunks; c0 += kPieceChunks) {
         const uint64_t c = c0 + (threadIdx.x >> 2);
         const bool live = c < n_chunks;
         const double v = chunk_component(gsum, c * kChunkGroups, n_groups, chunk_count(n_paths, c), live);
         if (live) rec[c * 4 + (threadIdx.x & 3u)] = v;
     }
+    return n_chunks;
+}
+
+__global__ void __launch_bounds__(kBlock) k_seg_groups(const GroupSegment* __restrict__ segs, double* __restrict__ out) {
+    const uint64_t n_chunks = group_records(segs);
     __syncthreads();
-    seg_reduce(rec, n_chunks, out + uint64_t(blockIdx.x) * 4);
+    seg_reduce((as_const(segs) + blockIdx.x)->records, n_chunks, out + uint64_t(blockIdx.x) * 4);
+}
+
+__global__ void __launch_bounds__(kBlock) k_group_records(const GroupSegment* __restrict__ pieces) { (void)group_records(pieces); }
+
+hipError_t launch_group_records(const GroupSegment* pieces, uint64_t n_pieces, hipStream_t st) {
+    if (n_pieces == 0) return hipSuccess;
+    if (n_pieces > 0x7fffffffull) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_group_records, dim3(uint32_t(n_pieces)), dim3(kBlock), 0, st, pieces);
+    return hipGetLastError();
 }
 
 hipError_t launch_seg_groups(const GroupSegment* segs, uint64_t n_seg, double* out, hipStream_t st) {

@@ -55,3 +55,20 @@ def test_chunk_sums_do_not_depend_on_the_share(ctx, route, s, flags, chunks):
         d = np.expm1(shift - S[:, level])
         tol = (4096 + 8) * 2.0 ** -53 * np.abs(d).sum()
         assert abs(got[-1, 1] - d.sum()) <= tol and abs(got[-1, 2] - (d * d).sum()) <= 2 * tol * max(1.0, np.abs(d).max())
+
+
+@pytest.mark.parametrize("flags", [0, P.FLAG_HIERARCHY])
+@pytest.mark.parametrize("big", [128 * CHUNK, 128 * CHUNK + 1, 200 * CHUNK - 63, 449 * CHUNK + 65])
+def test_batch_segments_of_many_chunks_equal_single_calls(ctx, big, flags):
+    """Up to 128 chunks a segment is reduced by one workgroup, beyond its records are formed in pieces of 64."""
+    rows = [(0, 1.0, 0.0, 0.7, 0.8, 16, 2, big, 3), (0, 1.0, 0.1, 0.5, 0.8, 16, 2, 4097, 4), (0, 1.0, 0.2, 0.5, 0.8, 64, 3, 70_001, 5)]
+    bt = P.Batch(ctx, [P.quartic(1.0, 2.0)], rows, 5, flags)
+    res, _, _ = bt.run()
+    again, _, _ = bt.run()
+    bt.close()
+    assert res.tobytes() == again.tobytes()
+    for i, (_, m, a, b, T, N, p, n, stream) in enumerate(rows):
+        one, _ = ctx.amplitude(P.quartic(1.0, 2.0), m, a, b, T, N, p, n, 5, stream, flags)
+        for level, r in enumerate(one):
+            got = res[i, level]
+            assert (got["amp"], got["err"], got["n"]) == (r.amp, r.err, r.n), (i, level)
