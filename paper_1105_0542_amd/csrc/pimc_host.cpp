@@ -808,9 +808,10 @@ int pimc_last_kernel_ms(pimc_ctx* c, double* ms) {
 }  // extern "C"
 
 // ============================================================================================ batch
-// Group sums a batch may keep (24 bytes per group and level): beyond, its items are whole chunks. A batch
-// of this size has 2.8e6 groups, a thousand rounds of the GPU's waves, and no longer needs the balance.
+// Group sums a batch may keep (24 bytes per group and level): the classes beyond go by whole chunk. Chunks of a
+// class that are looked at for that choice (any device has fewer workgroups resident than a quarter of it).
 static constexpr size_t kBatchGroupBytes = size_t(64) << 20;
+static constexpr size_t kBatchCosts = size_t(1) << 16;
 
 struct pimc_batch {
     pimc_ctx* ctx = nullptr;
@@ -835,7 +836,9 @@ struct pimc_batch {
         int n_tasks = 0;
         size_t first = 0;                      // first position in the device task array
         uint64_t n_items = 0;                  // canonical chunks
-        uint64_t n_work = 0;                   // queue items: blocks of groups (by group), else the chunks
+        bool by_group = false;                 // items are blocks of groups, else whole chunks
+        uint64_t n_work = 0;                   // items
+        uint64_t share = 0;                    // slices of groups per wave (by group)
         int smax = 0;                          // largest s of the class
         size_t lds = 0;
         int resident = 0;
@@ -846,10 +849,10 @@ struct pimc_batch {
     void* d_blob = nullptr;
     BatchTask* d_tasks = nullptr;
     double* d_partials = nullptr;
-    double* d_gsum = nullptr;                  // group sums (by group), else null
-    GroupSegment* d_gseg = nullptr;            // the segments; with `pieces`, in pieces of kPieceChunks chunks
+    double* d_gsum = nullptr;                  // group sums of the classes by group
+    GroupSegment* d_gseg = nullptr;            // their segments; with `pieces`, those in pieces of kPieceChunks chunks
     uint64_t n_gseg = 0;
-    bool pieces = false;                       // a long segment: chunk records first, then one reduction
+    bool pieces = false;                       // a class by chunk or a long segment: chunk records first, then one reduction
     uint64_t* d_seg = nullptr;
     double* d_red = nullptr;
     unsigned long long* d_queue = nullptr;
@@ -899,16 +902,18 @@ int class_grid(const pimc_batch* b, const pimc_batch::Class& C) { return std::ma
 // The launch of class k's persistent kernel on `st` (its queue must be reset first).
 hipError_t launch_class(pimc_batch* b, size_t k, hipStream_t st) {
     const auto& C = b->classes[k];
+    const int grid = class_grid(b, C);
     BatchArgs B{};
     B.tasks = b->d_tasks + C.first;
     B.n_items = C.n_work;
+    B.n_static = C.by_group ? batch_dealt(C.n_work, C.share, uint64_t(grid) * uint64_t(C.d.BS / 64)) : 0;
     B.queue = b->d_queue + k;
     B.key = RngKey{uint32_t(b->seed), uint32_t(b->seed >> 32), 0u};
     B.grab = b->grab;
     B.n_tasks = C.n_tasks;
-    B.by_group = b->d_gsum ? 1 : 0;
+    B.by_group = C.by_group ? 1 : 0;
     B.hier = (b->flags & PIMC_HIERARCHY) ? 1 : 0;
-    return launch_batch(B, C.p, C.n16, C.shape, class_grid(b, C), C.lds, st);
+    return launch_batch(B, C.p, C.n16, C.shape, grid, C.lds, st);
 }
 
 // Shape idx for class k: its description, LDS bytes and resident workgroups.
@@ -933,11 +938,11 @@ int capture_graph(pimc_batch* b) {
     HIP_TRY_B(b, hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
     hipError_t e = launch_fill_u64(b->d_queue, int(b->classes.size()), 0ull, b->stream);
     for (size_t k = 0; k < b->classes.size() && e == hipSuccess; ++k) e = launch_class(b, k, b->stream);
-    if (b->d_gsum && !b->pieces) {
-        if (e == hipSuccess) e = launch_seg_groups(b->d_gseg, b->n_gseg, b->d_red, b->stream);
-    } else {
-        if (e == hipSuccess && b->pieces) e = launch_group_records(b->d_gseg, b->n_gseg, b->stream);
+    if (b->pieces) {
+        if (e == hipSuccess) e = launch_group_records(b->d_gseg, b->n_gseg, b->stream);
         if (e == hipSuccess) e = launch_seg_reduce(b->d_partials, b->d_seg, b->d_seg + b->n_seg, b->n_seg, b->d_red, b->stream);
+    } else if (e == hipSuccess) {
+        e = launch_seg_groups(b->d_gseg, b->n_gseg, b->d_red, b->stream);
     }
     if (e == hipSuccess)
         e = hipMemcpyAsync(b->h_red, b->d_red, b->n_seg * 4 * 8, hipMemcpyDeviceToHost, b->stream);
@@ -1083,8 +1088,8 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
         blob.insert(blob.end(), b->t_shift[i].begin(), b->t_shift[i].end());
     }
     // partial slots and segments
-    std::vector<uint64_t> t_chunks(n_tasks), t_part_off(n_tasks), t_gsum_off(n_tasks);
-    uint64_t part_total = 0, gsum_total = 0;
+    std::vector<uint64_t> t_chunks(n_tasks), t_part_off(n_tasks);
+    uint64_t part_total = 0;
     std::vector<uint64_t> seg_base, seg_len;
     for (size_t pos = 0; pos < n_tasks; ++pos) {
         const size_t i = order[pos];
@@ -1097,13 +1102,41 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
             seg_len.push_back(t_chunks[i]);
         }
         part_total += uint64_t(slots) * t_chunks[i];
-        t_gsum_off[i] = gsum_total * 3;
-        gsum_total += uint64_t(slots) * ((tasks[i].n_samples + 63) / 64);
     }
-    const bool by_group = gsum_total <= kBatchGroupBytes / 24;
     b->n_seg = seg_base.size();
-    // ---- device buffers
+    // classes, and which of them go by group
     int st;
+    uint64_t gsum_total = 0;
+    std::vector<uint64_t> t_gsum_off(n_tasks, 0);
+    for (size_t pos = 0; pos < n_tasks;) {
+        pimc_batch::Class C;
+        C.p = tasks[order[pos]].p;
+        C.n16 = is_n16(order[pos]);
+        C.first = pos;
+        uint64_t sums = 0, slices = 0;
+        std::vector<uint64_t> cost;
+        for (; pos < n_tasks && tasks[order[pos]].p == C.p && is_n16(order[pos]) == C.n16; ++pos, ++C.n_tasks) {
+            const size_t i = order[pos];
+            const uint64_t groups = (tasks[i].n_samples + 63) / 64;
+            C.n_items += t_chunks[i];
+            C.smax = std::max(C.smax, b->t_s[i]);
+            t_gsum_off[i] = (gsum_total + sums) * 3;
+            sums += uint64_t(hier ? b->t_s[i] + 1 : 1) * groups;
+            slices += groups << b->t_s[i];
+            for (uint64_t c = 0; c < t_chunks[i] && cost.size() < kBatchCosts; ++c)
+                cost.push_back(std::min<uint64_t>(groups - c * kChunkGroups, kChunkGroups) << b->t_s[i]);
+        }
+        b->classes.push_back(C);
+        if (b->classes.size() > 64) return fail(batch_fail(b, PIMC_EUNSUPPORTED, "more than 64 kernel classes"));
+        if ((st = set_class_shape(b, b->classes.size() - 1, 0))) return fail(st);
+        auto& N = b->classes.back();
+        N.by_group = batch_by_group(cost, uint64_t(N.resident)) && gsum_total + sums <= kBatchGroupBytes / 24;
+        if (N.by_group) {
+            gsum_total += sums;
+            N.share = slices / (uint64_t(N.resident) * uint64_t(N.d.BS / 64));
+        }
+    }
+    // ---- device buffers
     auto dmalloc = [&](void** p, size_t bytes) -> int {
         const hipError_t e = hipMalloc(p, std::max<size_t>(bytes, 256));
         if (e != hipSuccess) return batch_fail(b, PIMC_ENOMEM, "hipMalloc(%zu): %s", bytes, hipGetErrorString(e));
@@ -1112,9 +1145,7 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
     if ((st = dmalloc(&b->d_blob, blob.size() * 8))) return fail(st);
     if ((st = dmalloc(reinterpret_cast<void**>(&b->d_tasks), n_tasks * sizeof(BatchTask)))) return fail(st);
     if ((st = dmalloc(reinterpret_cast<void**>(&b->d_partials), part_total * 4 * 8))) return fail(st);
-    if (by_group) {
-        if ((st = dmalloc(reinterpret_cast<void**>(&b->d_gsum), gsum_total * 24))) return fail(st);
-    }
+    if (gsum_total && (st = dmalloc(reinterpret_cast<void**>(&b->d_gsum), gsum_total * 24))) return fail(st);
     if ((st = dmalloc(reinterpret_cast<void**>(&b->d_seg), b->n_seg * 2 * 8))) return fail(st);
     if ((st = dmalloc(reinterpret_cast<void**>(&b->d_red), b->n_seg * 4 * 8))) return fail(st);
     if ((st = dmalloc(reinterpret_cast<void**>(&b->d_queue), 64 * 8))) return fail(st);
@@ -1137,57 +1168,48 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
         r.b = t.b * sm;
         r.n_paths = t.n_samples;
         r.n_chunks = t_chunks[i];
-        r.gsum = by_group ? b->d_gsum + t_gsum_off[i] : nullptr;
-        // a ticket costs about what 16 slices of a group do (pimc_chunks.hpp)
-        r.block = t.N >= 64 ? 1u : 64u / t.N;
         r.stream = t.stream;
         r.s = b->t_s[i];
     }
-    // classes and item numbering
-    for (size_t pos = 0; pos < n_tasks;) {
-        pimc_batch::Class C;
-        C.p = tasks[order[pos]].p;
-        C.n16 = is_n16(order[pos]);
-        C.first = pos;
-        while (pos < n_tasks && tasks[order[pos]].p == C.p && is_n16(order[pos]) == C.n16) {
-            dt[pos].item0 = C.n_work;
-            C.n_items += dt[pos].n_chunks;
-            C.n_work += by_group ? ((dt[pos].n_paths + 63) / 64 + dt[pos].block - 1) / dt[pos].block : dt[pos].n_chunks;
-            C.smax = std::max(C.smax, dt[pos].s);
-            ++C.n_tasks;
-            ++pos;
+    // item numbering, and the segments of the classes by group
+    std::vector<GroupSegment> gseg;
+    auto add_segments = [&](uint64_t most) {
+        for (const auto& C : b->classes)
+            for (size_t pos = C.first; C.by_group && pos < C.first + size_t(C.n_tasks); ++pos) {
+                const size_t i = order[pos];
+                const uint64_t n = tasks[i].n_samples, groups = (n + 63) / 64;
+                for (int k = 0; k < (hier ? b->t_s[i] + 1 : 1); ++k)
+                    for (uint64_t c = 0; c < t_chunks[i]; c += most)
+                        gseg.push_back(GroupSegment{b->d_gsum + t_gsum_off[i] + (uint64_t(k) * groups + c * kChunkGroups) * 3,
+                                                    b->d_partials + seg_base[b->t_seg[i] + size_t(k)] + c * 4,
+                                                    std::min(n - c * kChunkPaths, most * kChunkPaths)});
+            }
+    };
+    for (auto& C : b->classes) {
+        if (!C.by_group) b->pieces = true;
+        for (size_t pos = C.first; pos < C.first + size_t(C.n_tasks); ++pos) {
+            BatchTask& r = dt[pos];
+            const size_t i = order[pos];
+            r.gsum = C.by_group ? b->d_gsum + t_gsum_off[i] : nullptr;
+            r.block = C.by_group ? batch_block(r.s, C.share) : 0;
+            r.item0 = C.n_work;
+            C.n_work += C.by_group ? ((r.n_paths + 63) / 64 + r.block - 1) / r.block : r.n_chunks;
+            if (r.n_chunks > kShortSegment) b->pieces = true;
         }
-        b->classes.push_back(C);
     }
-    if (b->classes.size() > 64) return fail(batch_fail(b, PIMC_EUNSUPPORTED, "more than 64 kernel classes"));
-    for (size_t k = 0; k < b->classes.size(); ++k)
-        if ((st = set_class_shape(b, k, 0))) return fail(st);
+    add_segments(b->pieces ? kPieceChunks : kShortSegment);
+    b->n_gseg = gseg.size();
+    if (b->n_gseg && (st = dmalloc(reinterpret_cast<void**>(&b->d_gseg), b->n_gseg * sizeof(GroupSegment)))) return fail(st);
     std::vector<uint64_t> seg(b->n_seg * 2);
     std::copy(seg_base.begin(), seg_base.end(), seg.begin());
     std::copy(seg_len.begin(), seg_len.end(), seg.begin() + b->n_seg);
-    std::vector<GroupSegment> gseg;
-    if (by_group) {
-        for (size_t i = 0; i < n_tasks; ++i)
-            if (t_chunks[i] > kShortSegment) b->pieces = true;
-        const uint64_t most = b->pieces ? kPieceChunks : kShortSegment;
-        for (size_t i : order) {
-            const uint64_t n = tasks[i].n_samples, groups = (n + 63) / 64;
-            for (int k = 0; k < (hier ? b->t_s[i] + 1 : 1); ++k)
-                for (uint64_t c = 0; c < t_chunks[i]; c += most)
-                    gseg.push_back(GroupSegment{b->d_gsum + t_gsum_off[i] + (uint64_t(k) * groups + c * kChunkGroups) * 3,
-                                                b->d_partials + seg_base[b->t_seg[i] + size_t(k)] + c * 4,
-                                                std::min(n - c * kChunkPaths, most * kChunkPaths)});
-        }
-        b->n_gseg = gseg.size();
-        if ((st = dmalloc(reinterpret_cast<void**>(&b->d_gseg), b->n_gseg * sizeof(GroupSegment)))) return fail(st);
-    }
     HIP_TRY_B(b, hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking));
     HIP_TRY_B(b, hipEventCreate(&b->e0));
     HIP_TRY_B(b, hipEventCreate(&b->e1));
     HIP_TRY_B(b, hipMemcpyAsync(b->d_blob, blob.data(), blob.size() * 8, hipMemcpyHostToDevice, b->stream));
     HIP_TRY_B(b, hipMemcpyAsync(b->d_tasks, dt.data(), dt.size() * sizeof(BatchTask), hipMemcpyHostToDevice, b->stream));
     HIP_TRY_B(b, hipMemcpyAsync(b->d_seg, seg.data(), seg.size() * 8, hipMemcpyHostToDevice, b->stream));
-    if (by_group)
+    if (b->n_gseg)
         HIP_TRY_B(b, hipMemcpyAsync(b->d_gseg, gseg.data(), gseg.size() * sizeof(GroupSegment), hipMemcpyHostToDevice, b->stream));
     HIP_TRY_B(b, hipStreamSynchronize(b->stream));
     if ((st = capture_graph(b))) return fail(st);

@@ -16,5 +16,30 @@ int main() {
                                 (unsigned long long)n, (unsigned long long)w.n_groups, (unsigned long long)w.n_chunks,
                                 (unsigned long long)w.n_coarse, (unsigned long long)w.fine(), (unsigned long long)w.n_static, w.grab);
                 }
+    // classes of k equal tasks of 2^s slices beside k / 8 of 512 slices, long paths first
+    for (uint64_t wgs : {256, 512})
+        for (int s : {4, 5, 6, 8, 10})
+            for (int k : {1, 8, 40, 400, 5000, 50000})
+                for (uint64_t n : {2ull, 100ull, 4096ull, 20000ull, 100001ull, 2000000ull}) {
+                    std::vector<uint64_t> cost;
+                    uint64_t share = 0, items = 0;
+                    for (int t = 0; t < k / 8 + k; ++t) {
+                        const int st = t < k / 8 ? 9 : s;
+                        const uint64_t groups = (n + 63) / 64;
+                        share += groups << st;
+                        for (uint64_t c = 0; c * 64 < groups && cost.size() < 65536; ++c)
+                            cost.push_back(std::min<uint64_t>(groups - c * 64, 64) << st);
+                    }
+                    std::sort(cost.rbegin(), cost.rend());
+                    const uint64_t waves = 4 * wgs;
+                    share /= waves;
+                    for (int t = 0; t < k / 8 + k; ++t) {
+                        const uint32_t b = batch_block(t < k / 8 ? 9 : s, share);
+                        items += ((n + 63) / 64 + b - 1) / b;
+                    }
+                    std::printf("class %llu %d %d %llu %llu %d %llu %u %llu %llu\n", (unsigned long long)wgs, s, k, (unsigned long long)n,
+                                (unsigned long long)cost.size(), batch_by_group(cost, wgs) ? 1 : 0, (unsigned long long)share,
+                                batch_block(s, share), (unsigned long long)items, (unsigned long long)batch_dealt(items, share, waves));
+                }
     return 0;
 }

@@ -37,3 +37,21 @@ def test_runs(lines):
         assert tickets * TICKET_NS <= (fine - dealt) * (1 << s) * SLICE_NS + 2 * 4 * wgs * TICKET_NS, case
         kinds.add((coarse > 0, fine > 0, dealt > 0))
     assert kinds >= {(False, True, True), (True, False, False), (True, True, False)}
+
+
+def test_batch_classes(lines):
+    """Whole chunks where there are four or more for every workgroup, groups where there are fewer than
+    workgroups; items by ticket are worth their tickets."""
+    classes = [[int(x) for x in ln[1:]] for ln in lines if ln[0] == "class"]
+    assert len(classes) > 300
+    for wgs, s, k, n, chunks, by_group, share, block, items, dealt in classes:
+        case = (wgs, s, k, n)
+        if chunks >= 4 * wgs:
+            assert not by_group, case
+        if 2 * chunks < wgs:
+            assert by_group, case
+        assert block >= 1 and 0 <= dealt <= items, case
+        if dealt < items:
+            assert block * (1 << s) >= 128 and items - dealt >= min(items, 2 * 4 * wgs), case
+        assert dealt == items or block * (1 << s) * SLICE_NS > TICKET_NS, case
+    assert {c[5] for c in classes} == {0, 1} and any(c[9] < c[8] for c in classes)
