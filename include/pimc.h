@@ -339,8 +339,8 @@ int pimc_batch_run_to(pimc_batch *batch, pimc_level_result *out, int out_on_devi
 
 /* Scheduling of the persistent kernels: grid = resident workgroups * grid_mult_x2 / 2
  * (grid_mult_x2 in 1..8), each queue grab takes `grab` consecutive items (1..64): canonical chunks, or
- * a few groups of 64 paths where those sums of the batch are small. Changes only
- * scheduling: results are bitwise identical for every setting. Re-captures the graph. */
+ * blocks of groups of 64 paths in a class whose chunks are too few to keep the workgroups busy. Changes
+ * only scheduling: results are bitwise identical for every setting. Re-captures the graph. */
 int pimc_batch_set_tuning(pimc_batch *batch, int grid_mult_x2, uint32_t grab);
 
 /* A kernel class of a batch and its launch shape: subtree levels held in registers, workgroup
@@ -366,9 +366,9 @@ int pimc_batch_set_shape(pimc_batch *batch, int k, int shape);
 /* Autotuner: for every class, time each candidate launch shape on the class alone (one launch
  * each) and keep the fastest; then time grid_mult_x2 in {1, 2, 4} x grab in {1, 4, 16} on whole
  * replays. The choice is appended to the text cache file cache_path (may be NULL) under a key of
- * (GPU architecture, the classes, largest s, flags); a later call with a matching key -- for
- * example on a batch of the same tasks with more samples each -- applies the cached choice without
- * timing. */
+ * (GPU architecture, the classes and the kind of their items, largest s, flags); a later call with a
+ * matching key -- for example on a batch of the same tasks with more samples each, as long as its classes
+ * have items of the same kind -- applies the cached choice without timing. */
 int pimc_batch_autotune(pimc_batch *batch, const char *cache_path, int *grid_mult_x2, uint32_t *grab);
 
 int pimc_batch_destroy(pimc_batch *batch);

@@ -1312,12 +1312,13 @@ int pimc_batch_run(pimc_batch* b, pimc_level_result* out, double* ms) { return p
 int pimc_batch_autotune(pimc_batch* b, const char* cache_path, int* grid_mult_x2, uint32_t* grab) {
     if (!b) { set_thread_error("batch is NULL"); return PIMC_EINVAL; }
     HIP_TRY_B(b, hipSetDevice(b->ctx->device));
-    // cache key: device architecture, the classes (p, N = 16 or not), the largest s, flags
+    // cache key: device architecture, the classes (p, N = 16 or not, and what an item of theirs is: a whole chunk
+    // or a block of groups, as the choice counts items), the largest s, flags
     hipDeviceProp_t prop;
     HIP_TRY_B(b, hipGetDeviceProperties(&prop, b->ctx->device));
     std::ostringstream key;
     key << prop.gcnArchName << "|c";
-    for (const auto& C : b->classes) key << ":" << C.p << (C.n16 ? "n16" : "n32");
+    for (const auto& C : b->classes) key << ":" << C.p << (C.n16 ? "n16" : "n32") << (C.by_group ? "groups" : "chunks");
     key << "|s" << b->s_max << "|f" << b->flags;
     const size_t nc = b->classes.size();
     int st;
