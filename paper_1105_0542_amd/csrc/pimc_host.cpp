@@ -64,20 +64,26 @@ int ensure(pimc_ctx* c, void** buf, size_t* have, size_t need) {
     return PIMC_OK;
 }
 
-int pinned_stage(pimc_ctx* c, size_t need, unsigned char** out) {
+int upload_stage(pimc_ctx* c, size_t need, std::vector<unsigned char>& heap, unsigned char** out) {
     if (c->stage_busy) HIP_TRY(c, hipStreamSynchronize(c->stream));   // an earlier call ended on an error
     c->stage_busy = false;
-    if (kRedBytes + need > c->stage_bytes) {
+    const size_t pinned = kRedBytes + (need <= kStageBytes ? need : 0);
+    if (pinned > c->stage_bytes) {
         if (c->h_stage) HIP_TRY(c, hipHostFree(c->h_stage));
         c->h_stage = nullptr;
         c->stage_bytes = 0;
-        const size_t alloc = std::max(kRedBytes + need, size_t(1) << 16);
+        const size_t alloc = std::max(pinned, size_t(1) << 16);
         const hipError_t e = hipHostMalloc(reinterpret_cast<void**>(&c->h_stage), alloc, 0);
         if (e != hipSuccess) {
             c->h_stage = nullptr;
             return ctx_fail(c, PIMC_ENOMEM, "hipHostMalloc(%zu) failed: %s", alloc, hipGetErrorString(e));
         }
         c->stage_bytes = alloc;
+    }
+    if (need > kStageBytes) {
+        heap.resize(need);
+        *out = heap.data();
+        return PIMC_OK;
     }
     *out = c->h_stage + kRedBytes;
     return PIMC_OK;
@@ -321,7 +327,7 @@ int check_mpt(const pimc_mpt* V, double m, double a, double b, double T, uint32_
 }
 
 // Upload tables, per-level constants and the segments of the run's reduction (into the context's buffer,
-// by way of its pinned one and without waiting, or into the workspace); fill the kernel arguments except
+// by way of its pinned one and without waiting unless it is large, or into the workspace); fill the kernel arguments except
 // the output pointers. *segs_dev: where the segments are.
 int stage_problem(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t stream, AmpArgs& A,
                   const std::vector<unsigned char>& segs, const void** segs_dev, double** line_dev,
@@ -346,7 +352,7 @@ int stage_problem(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t stream,
     std::vector<unsigned char> heap(work ? total : 0);
     unsigned char* host = heap.data();
     if (!work) {
-        const int st = pinned_stage(c, total, &host);
+        const int st = upload_stage(c, total, heap, &host);
         if (st) return st;
     }
     std::memset(host, 0, total);
@@ -370,13 +376,11 @@ int stage_problem(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t stream,
         if (st) return st;
         prm = c->d_prm;
     }
-    if (!work) c->stage_busy = true;
+    c->stage_busy = heap.empty();
     HIP_TRY(c, hipMemcpyAsync(prm, host, total, hipMemcpyHostToDevice, c->stream));
-    if (work) {
-        // the host vectors must stay valid until the copies have read them
-        if (!segs.empty()) HIP_TRY(c, hipMemcpyAsync(work->seg, segs.data(), segs.size(), hipMemcpyHostToDevice, c->stream));
-        HIP_TRY(c, hipStreamSynchronize(c->stream));
-    }
+    if (work && !segs.empty()) HIP_TRY(c, hipMemcpyAsync(work->seg, segs.data(), segs.size(), hipMemcpyHostToDevice, c->stream));
+    // the host vectors must stay valid until the copies have read them
+    if (!heap.empty()) HIP_TRY(c, hipStreamSynchronize(c->stream));
     unsigned char* base = static_cast<unsigned char*>(prm);
     *segs_dev = work ? static_cast<const void*>(work->seg) : base + off_segs;
     *line_dev = reinterpret_cast<double*>(base + off_line);

@@ -24,6 +24,7 @@ struct pimc_ctx {
     uint64_t* d_seg = nullptr;      size_t seg_bytes = 0;
     std::vector<uint64_t> h_seg;    // segment base/len of the last proposal reduction (kept alive for the async copy)
     // pinned: the reduced sums and reference actions of a run (kRedBytes, written by its kernels), then what it uploads
+    // (upload_stage)
     unsigned char* h_stage = nullptr;  size_t stage_bytes = 0;
     bool stage_busy = false;        // a copy out of it may still be under way
     double* d_dump = nullptr;       size_t dump_bytes = 0;
@@ -48,10 +49,13 @@ int ctx_fail(pimc_ctx* c, int status, const char* fmt, ...);
 // Grow a device buffer to at least need bytes (contents are not kept).
 int ensure(pimc_ctx* c, void** buf, size_t* have, size_t need);
 
-// The context's pinned buffer, with room for the sums of a run and its reference actions and for `need` bytes to upload (at
-// *out); free for writing when this returns.
+// Host memory for `need` bytes to upload (at *out), free for writing when this returns: behind the sums of a run and
+// its reference actions in the context's pinned buffer, which the context keeps, up to kStageBytes; beyond (tables
+// of the component route and of the highest levels of the general mode) in `heap`, which the copy has to
+// be waited for with. A pinned upload saves the wait, some 15 us.
 constexpr size_t kRedBytes = size_t(PIMC_MAX_S + 1) * 5 * 8;   // four sums and the reference action per level
-int pinned_stage(pimc_ctx* c, size_t need, unsigned char** out);
+constexpr size_t kStageBytes = size_t(1) << 20;
+int upload_stage(pimc_ctx* c, size_t need, std::vector<unsigned char>& heap, unsigned char** out);
 // What the reduction of a run reads on the device (GroupSegment per slot for a short run, else base and
 // length per slot), and its launch: chunk records from the fine groups' sums, then out[slot][4].
 std::vector<unsigned char> run_segments(const pimc::PathWork& w, int slots, uint64_t n_paths, double* partials);

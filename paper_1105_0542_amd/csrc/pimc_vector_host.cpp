@@ -451,8 +451,9 @@ int stage_vector(pimc_ctx* c, const VecProblem& P, uint64_t seed, uint32_t strea
     // component route: the partial sums of the reference actions, on the device only
     const size_t off_line = (total + 15) & ~size_t(15);
     const size_t need = off_line + (P.poly ? nlev * kLineParts * 8 : 0);
+    std::vector<unsigned char> heap;
     unsigned char* host = nullptr;
-    int st = pinned_stage(c, total, &host);
+    int st = upload_stage(c, total, heap, &host);
     if (st) return st;
     std::memset(host, 0, total);
     std::memcpy(host, P.sig.data(), nlev * 8);
@@ -462,8 +463,9 @@ int stage_vector(pimc_ctx* c, const VecProblem& P, uint64_t seed, uint32_t strea
     if (!segs.empty()) std::memcpy(host + off_segs, segs.data(), segs.size());
     st = ensure(c, &c->d_prm, &c->prm_bytes, need);
     if (st) return st;
-    c->stage_busy = true;
+    c->stage_busy = heap.empty();
     HIP_TRY(c, hipMemcpyAsync(c->d_prm, host, total, hipMemcpyHostToDevice, c->stream));
+    if (!heap.empty()) HIP_TRY(c, hipStreamSynchronize(c->stream));     // it must outlive the copy
     *segs_dev = static_cast<unsigned char*>(c->d_prm) + off_segs;
     *line_dev = reinterpret_cast<double*>(static_cast<unsigned char*>(c->d_prm) + off_line);
     unsigned char* base = static_cast<unsigned char*>(c->d_prm);
