@@ -603,6 +603,7 @@ int vector_path_actions_core(pimc_ctx* c, const VecProblem& P, uint64_t seed, ui
                       : launch_vector(A, P.dim, P.p, P.U, P.specialized, grid, c->stream));
     HIP_TRY(c, hipMemcpyAsync(S_out, c->d_dump, size_t(k_paths) * nlev * 8, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
+    c->stage_busy = false;
     return PIMC_OK;
 }
 
