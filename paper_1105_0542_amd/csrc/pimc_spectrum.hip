@@ -311,11 +311,12 @@ __global__ void k_scale_by_norm(const double* __restrict__ w, uint32_t n, const 
 //   k_step_correct: the dots from all blocks' parts, w -= sum_c h_c Q_c, and the parts of the second
 //                   pass's dots; with LAST the part of |w|^2 instead;
 //   k_step_scale:   |w| from the parts, q_{j+1} = w / |w|.
-// Every block adds the parts for itself (lane = column, whole lines from L2). 8 bytes per column and pair
-// of blocks: 25 MB for 48 columns of n = 16384, 100 MB for n = 32768, and four times that per doubling,
-// so the fused form ends at kFuseBlocks row blocks and kFuseCols columns. GPU time of the chain without
-// the product, separate and fused, at 48 columns: n = 16384 35 and 21 us, n = 32768 57 and 43 us;
-// n = 300..8000, whole call: 1111 -> 850 us (300), 1200 -> 900 (1000), 1930 -> 1500 (8000),
+// Every block adds the parts for itself (lane = column, whole lines from L2): 8 bytes per column and pair
+// of blocks, 25 MB for 48 columns of n = 16384, 268 MB for 128 columns of n = 32768. So the fused form ends at
+// kFuseBlocks row blocks and kFuseCols columns (the LDS array of the dots). Lanczos steps 1..m of narrow
+// bands, separate and fused, ms: m = 48 n = 9000 2.15 and 1.57, 16384 2.34 and 1.67, 32768 3.03 and 2.41, 40000
+// 3.87 and 3.52, 60000 4.90 and 5.21; m = 128 n = 1024 5.97 and 4.23, 16384 7.82 and 5.28, 32768 11.0 and 8.6, 40000 12.6
+// and 11.9, 60000 15.0 and 18.0. Whole calls: 1111 -> 850 us (n = 300), 1200 -> 900 (1000), 1930 -> 1500 (8000),
 // 4550 -> 3700 (16384, 48 steps).
 constexpr int kStepWaves = 8;
 constexpr int kStepBlock = kStepWaves * 64;
