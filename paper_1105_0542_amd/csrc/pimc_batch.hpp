@@ -139,8 +139,7 @@ struct BatchLauncher;
 
 template <int P>
 struct BatchLauncher<P, ShapeList<>> {
-    static hipError_t launch(int, const BatchArgs&, int, size_t, hipStream_t) {
-    }
+    static hipError_t launch(int, const BatchArgs&, int, size_t, hipStream_t) { return hipErrorInvalidValue; }
     static int resident(int, size_t, int) { return 0; }
     static bool desc(int, ShapeDesc&) { return false; }
 };
