@@ -27,7 +27,7 @@ using BatchDefaultN16 = ShapeList<DefaultShape<4>>;
 // Persistent kernel over the items of one class (level p, launch shape), numbered task by task (task t
 // owns items item0[t] .. item0[t+1] - 1), so an item maps to its task by binary search over the
 // wave-uniform task records. An item is
-//   * by group (classes of few chunks): `block` consecutive groups, taken by one wave, whose sums are stored
+//   * by group (classes of few chunks, by batch_by_group): `block` consecutive groups, taken by one wave, whose sums are stored
 //     and added into the chunk records afterwards (pimc_chunks.hpp: the same sums as any other split). A
 //     task of 20,000 paths has 5 chunks, a class of 85 such tasks 425 of them for 512 resident
 //     workgroups, those with N = 512 16 times as long as those with N = 32. The first n_static items are

@@ -842,7 +842,9 @@ struct pimc_batch {
         uint64_t n_items = 0;                  // canonical chunks
         bool by_group = false;                 // items are blocks of groups, else whole chunks
         uint64_t n_work = 0;                   // items
+        uint64_t slices = 0;                   // of all its groups (by group)
         uint64_t share = 0;                    // slices of groups per wave (by group)
+        uint64_t ticket_items = 0;             // items of the last three quarters of the slices (by group)
         int smax = 0;                          // largest s of the class
         size_t lds = 0;
         int resident = 0;
@@ -910,7 +912,7 @@ hipError_t launch_class(pimc_batch* b, size_t k, hipStream_t st) {
     BatchArgs B{};
     B.tasks = b->d_tasks + C.first;
     B.n_items = C.n_work;
-    B.n_static = C.by_group ? batch_dealt(C.n_work, C.share, uint64_t(grid) * uint64_t(C.d.BS / 64)) : 0;
+    B.n_static = C.by_group ? batch_dealt(C.n_work, C.share, uint64_t(grid) * uint64_t(C.d.BS / 64), C.ticket_items) : 0;
     B.queue = b->d_queue + k;
     B.key = RngKey{uint32_t(b->seed), uint32_t(b->seed >> 32), 0u};
     B.grab = b->grab;
@@ -1117,7 +1119,7 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
         C.p = tasks[order[pos]].p;
         C.n16 = is_n16(order[pos]);
         C.first = pos;
-        uint64_t sums = 0, slices = 0;
+        uint64_t sums = 0, slices = 0, all_groups = 0;
         std::vector<uint64_t> cost;
         for (; pos < n_tasks && tasks[order[pos]].p == C.p && is_n16(order[pos]) == C.n16; ++pos, ++C.n_tasks) {
             const size_t i = order[pos];
@@ -1127,6 +1129,7 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
             t_gsum_off[i] = (gsum_total + sums) * 3;
             sums += uint64_t(hier ? b->t_s[i] + 1 : 1) * groups;
             slices += groups << b->t_s[i];
+            all_groups += groups;
             for (uint64_t c = 0; c < t_chunks[i] && cost.size() < kBatchCosts; ++c)
                 cost.push_back(std::min<uint64_t>(groups - c * kChunkGroups, kChunkGroups) << b->t_s[i]);
         }
@@ -1134,9 +1137,10 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
         if (b->classes.size() > 64) return fail(batch_fail(b, PIMC_EUNSUPPORTED, "more than 64 kernel classes"));
         if ((st = set_class_shape(b, b->classes.size() - 1, 0))) return fail(st);
         auto& N = b->classes.back();
-        N.by_group = batch_by_group(cost, uint64_t(N.resident)) && gsum_total + sums <= kBatchGroupBytes / 24;
+        N.by_group = batch_by_group(cost, all_groups, uint64_t(N.resident)) && gsum_total + sums <= kBatchGroupBytes / 24;
         if (N.by_group) {
             gsum_total += sums;
+            N.slices = slices;
             N.share = slices / (uint64_t(N.resident) * uint64_t(N.d.BS / 64));
         }
     }
@@ -1199,6 +1203,15 @@ int pimc_batch_create(pimc_ctx* c, const pimc_potential* systems, int n_systems,
             r.item0 = C.n_work;
             C.n_work += C.by_group ? ((r.n_paths + 63) / 64 + r.block - 1) / r.block : r.n_chunks;
             if (r.n_chunks > kShortSegment) b->pieces = true;
+        }
+        uint64_t left = C.by_group ? C.slices / 4 * 3 : 0;
+        uint64_t past = C.n_work;
+        for (size_t pos = C.first + size_t(C.n_tasks); left && pos-- > C.first;) {
+            const BatchTask& r = dt[pos];
+            const uint64_t item = uint64_t(r.block) << r.s, n = std::min(past - r.item0, (left + item - 1) / item);
+            C.ticket_items += n;
+            left -= std::min(left, n * item);
+            past = r.item0;
         }
     }
     add_segments(b->pieces ? kPieceChunks : kShortSegment);

@@ -96,11 +96,14 @@ inline int work_grid(const PathWork& w, int waves_per_wg, int resident) {
 }
 
 // Batches. The chunks of a class (the tasks of one level p that share a launch) go to workgroups in the order of
-// the tasks, long paths first; cost: slices of groups of each chunk. A class goes by group where that leaves
-// workgroups idle for more than a seventh of the time: a group on its own costs 5 to 9 % more than within a chunk
-// (its task is looked up and its sums are stored: 4 tasks of 2e7 paths, N = 64, p = 8 11.0 and 11.9 ms).
+// the tasks, long paths first; cost: slices of groups of each chunk; groups: groups of them all. A class goes by
+// group where that order would leave workgroups idle, for more than a seventh of the time below 64 slices a group
+// (on average) and a twentieth below 128, because a group on its own costs up to 9 % more than within a chunk there
+// (1500 tasks of 4096 paths, N = 32, p = 18 0.84 and 0.88 ms; 1024 of them, N = 64, two full rounds, 1.00 and 1.07); with longer
+// ones always, for the waves of a SIMD don't keep step and the last of few long chunks are walked alone (1400 tasks of 4096
+// paths, N = 32..512, p = 12 3.85 ms by chunk, 3.0 by group, where the order alone leaves 6 %).
 constexpr uint64_t kBatchChunks = 4;          // chunks per workgroup from which the idle end no longer matters
-inline bool batch_by_group(const std::vector<uint64_t>& cost, uint64_t wgs) {
+inline bool batch_by_group(const std::vector<uint64_t>& cost, uint64_t groups, uint64_t wgs) {
     if (cost.empty() || cost.size() >= kBatchChunks * wgs) return false;
     std::priority_queue<uint64_t, std::vector<uint64_t>, std::greater<uint64_t>> busy;     // when each workgroup is free
     uint64_t total = 0, end = 0;
@@ -114,19 +117,22 @@ inline bool batch_by_group(const std::vector<uint64_t>& cost, uint64_t wgs) {
         total += c;
         end = std::max(end, t);
     }
-    return 7 * end * wgs > 8 * total;
+    if (total >= 128 * groups) return true;
+    return total >= 64 * groups ? 20 * end * wgs > 21 * total : 7 * end * wgs > 8 * total;
 }
 
-// By group the items of a class, blocks of groups for single waves, are dealt in the same order, so that every
-// wave gets the same mix. share: slices of groups per wave. An item is an eighth of that, at most what a ticket
-// should be worth. Where it is less the items are all dealt, else the last quarter goes by ticket (two rounds
-// at least).
+// By group the items of a class, blocks of groups for single waves, are taken in the same order. share: slices
+// of groups per wave. An item is a sixteenth of that, but at least an eighth or what a ticket should be worth and
+// at most twice that. Where an eighth is less the items are all dealt, so that every wave gets the same mix; else
+// the items of the first quarter of the work are, and those of the rest go by ticket (two rounds at least). A
+// quarter of the items by ticket, the short ones: 85 tasks of 20,000 paths, N = 32..512, p = 18 1.21 ms, this way 1.14.
 inline uint32_t batch_block(int s, uint64_t share) {
-    const uint64_t q = std::min<uint64_t>(share / 8, kTicketSlices) >> s;
+    const uint64_t most = std::min<uint64_t>(std::max<uint64_t>(share / 16, kTicketSlices), 2 * kTicketSlices);
+    const uint64_t q = std::min(share / 8, most) >> s;
     return q < 1 ? 1u : uint32_t(q);
 }
-inline uint64_t batch_dealt(uint64_t n_items, uint64_t share, uint64_t waves) {
-    const uint64_t tail = std::max(2 * waves, n_items / 4);
+inline uint64_t batch_dealt(uint64_t n_items, uint64_t share, uint64_t waves, uint64_t ticket_items) {
+    const uint64_t tail = std::max(2 * waves, ticket_items);
     return share < 8 * kTicketSlices ? n_items : (n_items > tail ? n_items - tail : 0);
 }
 

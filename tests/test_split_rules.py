@@ -55,3 +55,17 @@ def test_batch_classes(lines):
             assert block * (1 << s) >= 128 and items - dealt >= min(items, 2 * 4 * wgs), case
         assert dealt == items or block * (1 << s) * SLICE_NS > TICKET_NS, case
     assert {c[5] for c in classes} == {0, 1} and any(c[9] < c[8] for c in classes)
+
+
+def test_batch_classes_of_long_paths(lines):
+    """Fewer than four chunks for every workgroup: by group from 128 slices a group on; full rounds of equal chunks of
+    shorter ones by chunk."""
+    mixes = [[int(x) for x in ln[1:]] for ln in lines if ln[0] == "mix"]
+    assert len(mixes) == 72
+    for k, kinds, s, mean, by_group in mixes:
+        if k >= 2048:
+            assert not by_group, (k, kinds, s)
+        elif mean >= 128:
+            assert by_group, (k, kinds, s)
+        elif kinds == 1 and k % 512 == 0:
+            assert not by_group, (k, kinds, s)
