@@ -50,15 +50,23 @@ inline uint32_t ticket_groups(int s) { return s >= 7 ? 1u : (s >= 3 ? kTicketSli
 
 // Whole chunks of a run of n_chunks chunks on wgs workgroups, R = n_chunks / wgs rounds.
 //   R <= 1: none, with chunks workgroups would have no work (1e6 paths, N = 256, p = 18: 1.19 ms, 0.99 by group);
-//   N <= 32: all, the tail of a chunk is short there and tickets for short groups are dear (5e6 paths, N = 8,
-//     p = 1: 0.18 ms, 0.23 with the last two rounds by group);
+//   N <= 32: from R = 4 on all, the tail of a chunk is short there and tickets for short groups are dear (2e7 paths,
+//     N = 8, p = 1: 1.1 times as long by group). Below that all where the last round is about half full, because one of the two
+//     workgroups of a CU gets ahead of the other and then has one chunk more; else none, all groups are dealt in
+//     turn. Time by chunk over dealt at R = 1.03, 1.25, 1.5, 1.75, 1.95, 2.05, 2.25, 2.5, 2.75, 3.1, 3.5, 4.1: quartic p = 18,
+//     N = 8, every level 1.37 1.22 1.07 1.08 1.00 1.13 1.06 0.99 1.05 1.03 0.94 0.99; N = 32, level s alone 1.20 1.07
+//     0.93 1.01 0.93 1.09 1.14 1.07 0.99 0.98 0.92 0.99; four coordinates, N = 8 1.19 1.04 0.94 1.25 1.17 1.12 1.06
+//     0.99 1.01 1.08 1.06 1.01;
 //   else full rounds, and what remains, 0.4 to 1.4 rounds, by group (one to two from R = 3 on, where workgroups
 //     have drifted apart by a chunk): 5e6 paths, N = 256, p = 18, every level: 8.3 ms by chunk, 6.4; 1e7: 13.5 and
 //     12.4. A remainder of whole chunks beside groups is worse than either (3e6 paths, 1.43 rounds, 0.43 of
 //     them by chunk: 6.2 ms, 4.2 by chunk and 4.1 this way), the chunks then last longer than all the rest.
 inline uint64_t whole_chunks(uint64_t n_chunks, int s, uint64_t wgs) {
     if (n_chunks <= wgs) return 0;
-    if (s <= 5) return n_chunks;
+    if (s <= 5) {
+        const uint64_t eighths = n_chunks * 8 / wgs;
+        return eighths >= 32 || eighths % 8 == 3 || eighths % 8 == 4 ? n_chunks : 0;
+    }
     const uint64_t r10 = n_chunks * 10 / wgs;
     return wgs * (r10 < 30 ? (r10 - 4) / 10 : r10 / 10 - 1);
 }
@@ -76,7 +84,7 @@ inline PathWork split_paths(uint64_t n_paths, int s, int slots, size_t fine_byte
     if (slots) {
         const uint64_t fit = fine_bytes / (size_t(slots) * kChunkGroups * 24);
         w.n_coarse = whole_chunks(w.n_chunks, s, wgs);
-        if (w.n_chunks - w.n_coarse > fit) w.n_coarse = w.n_chunks - fit;
+        if (w.n_chunks - w.n_coarse > fit) w.n_coarse = s <= 5 && w.n_chunks > wgs ? w.n_chunks : w.n_chunks - fit;
     }
     w.grab = ticket_groups(s);
     if (!w.n_coarse) {

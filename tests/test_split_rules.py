@@ -39,6 +39,21 @@ def test_runs(lines):
     assert kinds >= {(False, True, True), (True, False, False), (True, True, False)}
 
 
+def test_short_paths_by_chunk_or_by_group(lines):
+    """N <= 32: all by chunk from four rounds on and where the last is half full, else all by group."""
+    runs = [[int(x) for x in ln[1:]] for ln in lines if ln[0] == "run"]
+    runs = [r for r in runs if r[1] <= 5 and r[2] > 0 and r[5] > r[0]]
+    seen = set()
+    for wgs, s, slots, n, groups, chunks, coarse, fine, dealt, grab in runs:
+        assert coarse in (0, chunks), (wgs, s, slots, n)
+        if chunks == 513 and wgs == 512:
+            assert coarse == 0 and dealt == groups
+        if chunks >= 4 * wgs or 8 * chunks // wgs % 8 in (3, 4):
+            assert coarse == chunks
+        seen.add(coarse == 0)
+    assert seen == {True, False}
+
+
 def test_batch_classes(lines):
     """Whole chunks where there are four or more for every workgroup, groups where there are fewer than
     workgroups; items by ticket are worth their tickets."""
