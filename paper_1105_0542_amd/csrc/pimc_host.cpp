@@ -376,7 +376,7 @@ int stage_problem(pimc_ctx* c, const Problem& P, uint64_t seed, uint32_t stream,
         if (st) return st;
         prm = c->d_prm;
     }
-    c->stage_busy = heap.empty();
+    c->stage_busy = !work;
     HIP_TRY(c, hipMemcpyAsync(prm, host, total, hipMemcpyHostToDevice, c->stream));
     if (work && !segs.empty()) HIP_TRY(c, hipMemcpyAsync(work->seg, segs.data(), segs.size(), hipMemcpyHostToDevice, c->stream));
     // the host vectors must stay valid until the copies have read them

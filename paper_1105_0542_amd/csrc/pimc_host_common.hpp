@@ -26,7 +26,7 @@ struct pimc_ctx {
     // pinned: the reduced sums and reference actions of a run (kRedBytes, written by its kernels), then what it uploads
     // (upload_stage)
     unsigned char* h_stage = nullptr;  size_t stage_bytes = 0;
-    bool stage_busy = false;        // a copy out of it may still be under way
+    bool stage_busy = false;        // a copy out of it, or a kernel that writes sums to it, may still be under way
     double* d_dump = nullptr;       size_t dump_bytes = 0;
     double* d_gsum = nullptr;       size_t gsum_bytes = 0;     // group sums of the fine chunks (at most kFineBytes)
     hipEvent_t ev0 = nullptr, ev1 = nullptr;

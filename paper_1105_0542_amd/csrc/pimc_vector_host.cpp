@@ -463,7 +463,7 @@ int stage_vector(pimc_ctx* c, const VecProblem& P, uint64_t seed, uint32_t strea
     if (!segs.empty()) std::memcpy(host + off_segs, segs.data(), segs.size());
     st = ensure(c, &c->d_prm, &c->prm_bytes, need);
     if (st) return st;
-    c->stage_busy = heap.empty();
+    c->stage_busy = true;
     HIP_TRY(c, hipMemcpyAsync(c->d_prm, host, total, hipMemcpyHostToDevice, c->stream));
     if (!heap.empty()) HIP_TRY(c, hipStreamSynchronize(c->stream));     // it must outlive the copy
     *segs_dev = static_cast<unsigned char*>(c->d_prm) + off_segs;
