@@ -134,20 +134,23 @@ __device__ __forceinline__ void run_groups(const PathWork& w, int nlev, int hier
         sw.fine0 = f0;
         sw.n_fine = w.n_groups > f0 ? w.n_groups - f0 : 0;
     }
-    __syncthreads();
-    auto take = [&]() -> unsigned long long {                      // the next ticket for fine groups (in lane 0)
+    auto take = [&](uint32_t grab) -> unsigned long long {         // the next ticket for fine groups (in lane 0)
         unsigned long long t = 0;
-        if ((tid & 63) == 0) t = atomicAdd(w.queue + 1, (unsigned long long)sw.w.grab);
+        if ((tid & 63) == 0) t = atomicAdd(w.queue + 1, (unsigned long long)grab);
         return t;
     };
-    bool coarse = uniform_u64(sw.w.n_coarse) > 0;
-    bool dealt = !coarse;                                          // the groups dealt to this wave are to come
+    // Without a coarse phase the groups dealt to this wave come first. What they need is taken from the launch's
+    // arguments: a wave of a short run has one group, and each look into LDS before it costs that run 0.1 us.
+    bool coarse = w.n_coarse > 0, dealt = !coarse;
+    uint64_t g = uint64_t(blockIdx.x) * WAVES + uint64_t(wave), last = dealt ? w.n_static : 0;
+    uint32_t step = gridDim.x * WAVES;
     unsigned long long ticket = 0;
-    if (!coarse && uniform_u64(sw.w.n_static) < uniform_u64(sw.n_fine)) ticket = take();
+    if (dealt && w.n_static < w.n_groups) ticket = take(w.grab);
+    __syncthreads();
     while (true) {
-        uint64_t g, last;
-        uint32_t step;
-        if (coarse) {
+        if (dealt) {
+            dealt = false;
+        } else if (coarse) {
             __syncthreads();                                       // the chunk before is written
             if (tid == 0) sw.chunk = atomicAdd(w.queue, 1ull);
             __syncthreads();
@@ -155,7 +158,7 @@ __device__ __forceinline__ void run_groups(const PathWork& w, int nlev, int hier
             if (c >= uniform_u64(sw.w.n_coarse)) {
                 coarse = false;
                 if (uniform_u64(sw.n_fine) == 0) break;
-                ticket = take();
+                ticket = take(uniform_u32(sw.w.grab));
                 continue;
             }
             for (int i = tid; i < kChunkSlots * nlev * 3; i += BS) acc[i] = 0.0;
@@ -163,21 +166,17 @@ __device__ __forceinline__ void run_groups(const PathWork& w, int nlev, int hier
             g = c * kChunkGroups + uint64_t(wave);
             last = (c + 1) * kChunkGroups;
             step = WAVES;
-        } else if (dealt) {
-            dealt = false;
-            g = uint64_t(blockIdx.x) * WAVES + uint64_t(wave);
-            last = uniform_u64(sw.w.n_static);
-            step = gridDim.x * WAVES;
+            const uint64_t end = uniform_u64(sw.w.n_groups);
+            if (last > end) last = end;
         } else {
-            const uint64_t f = uniform_u64(sw.w.n_static) + uniform_u64(ticket);
-            if (f >= uniform_u64(sw.n_fine)) break;
-            ticket = take();
+            const uint64_t f = uniform_u64(sw.w.n_static) + uniform_u64(ticket), n = uniform_u64(sw.n_fine);
+            if (f >= n) break;
+            const uint32_t grab = uniform_u32(sw.w.grab);
+            ticket = take(grab);
             g = uniform_u64(sw.fine0) + f;
-            last = g + uniform_u32(sw.w.grab);
+            last = g + (n - f < grab ? n - f : grab);
             step = 1;
         }
-        const uint64_t end = uniform_u64(sw.w.n_groups);
-        if (last > end) last = end;
         for (; g < last; g += step) {
             run(g, [&]() __attribute__((always_inline)) {
                 if (coarse) return GroupSink{true, acc + int(g % kChunkSlots) * nlev * 3, nullptr, 0};

@@ -59,7 +59,7 @@ __global__ void __launch_bounds__(256) k_evolution_matrix(SpecTable tb, double L
 // further than sqrt(2 t kGaussCut) from the diagonal are zeros by definition, for the short times of
 // this method most of the matrix (t = 0.02, L = 8, n = 16384: 22 of up to 256 tiles a row, 177 MB of
 // 1078 MB). A zero tile's partial products are zeros, so the products have the bits of the whole
-// triangle's. Measured at that size: 179 -> 27.6 us a product (6.4 TB/s), matrix 590 -> 132 us, the whole
+// triangle's. Measured at that size: 179 -> 30.4 us a product (5.8 TB/s), matrix 590 -> 130 us, the whole
 // call (48 products) 13.2 -> 4.4 ms.
 
 // Tile t of the packed matrix: each thread computes kTile^2 / 256 elements, kMatCols consecutive
@@ -304,7 +304,7 @@ __global__ void k_scale_by_norm(const double* __restrict__ w, uint32_t n, const 
 }
 
 // ---------------------------------------------------------------------------- fused Lanczos step
-// A step is a chain of short dependent kernels, 4 to 7 us each beside a product of 28 us (n = 16384): row
+// A step is a chain of short dependent kernels, 4 to 7 us each beside a product of 30 us (n = 16384): row
 // sums, dots, correction, dots, correction, norm, scaling. Here they are four, a workgroup of 8 waves per
 // row block of kTile rows, each doing what the block can do with the rows that it has just formed:
 //   k_step_rows:    w = M q_j from the tile partials, and the block's part of every dot <Q_c, w>;

@@ -642,8 +642,7 @@ template <int DIM, int U, class Eval>
 __global__ void __launch_bounds__(kVecBlock) __attribute__((amdgpu_waves_per_eu(2)))
 k_amplitude_vec(VecArgs A, Eval ev) {
     extern __shared__ double smem[];
-    load_bm_table(smem, kVecBlock);
-    __syncthreads();
+    load_bm_table(smem, kVecBlock);     // the loops below begin with a barrier
     double* top = smem + kBoxMullerTable + threadIdx.x;
     double* acc = smem + kBoxMullerTable + size_t(vec_top_slots(DIM, A.D)) * kVecBlock;
     run_groups<kVecBlock>(A.work, A.s + 1, A.hier, A.n_paths, A.partials, acc, [&](uint64_t g, auto sink) __attribute__((always_inline)) {

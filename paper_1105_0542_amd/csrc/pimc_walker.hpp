@@ -190,8 +190,7 @@ template <class S, class Eval, bool WHOLE>
 __global__ void __launch_bounds__(S::BS) __attribute__((amdgpu_waves_per_eu(S::WPE)))
 k_amplitude(AmpArgs A, Eval ev) {
     extern __shared__ double smem[];
-    load_bm_table(smem, S::BS);
-    __syncthreads();
+    load_bm_table(smem, S::BS);     // the loops below begin with a barrier
     double* top = smem + kBoxMullerTable + threadIdx.x;
     double* acc = smem + kBoxMullerTable + size_t(3 * A.D + 2) * S::BS;
     auto run = [&](uint64_t g, auto sink) __attribute__((always_inline)) {
